@@ -96,9 +96,11 @@ struct NormPlan {
                         // 2 = whole-sample kernel (bf16, 128 < T <= 256),
                         // 3 = 256-row super blocks (bf16, T > 256);
                         // instantiation: bk::GemmVariant
-    int64_t tiles = 0;  // instantiation: output tiles per sample
-    int64_t ksplit = 1; // instantiation: K slices per tile (wide and narrow kernels)
-    int64_t tile_elems = 0;   // instantiation: floats of one K-split partial tile
+    int64_t tiles = 0;  // instantiation: output tiles per sample; ghost: super-block pairs
+    int64_t ksplit = 1; // instantiation: K slices per tile (wide and narrow kernels);
+                        // ghost (variants 0, 1): column slices per pair, ka of them of a
+    int64_t ka = 0;
+    int64_t tile_elems = 0;   // floats of one K-split partial tile (partial Gram)
     int64_t aff_chunks = 0;   // per-sample partials of the bias / affine sums (second run)
     bool fused_bias = false;  // ghost layer whose kernel also forms the bias sums (no second run)
 };
@@ -192,17 +194,24 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
 }
 
 // Workgroup count, and the K split of instantiated norms on the wide and
-// narrow kernels (a split layer reports one partial per slice-reduction chunk).
+// narrow kernels (a split layer reports one partial per slice-reduction chunk)
+// and of ghost layers whose column split (np.ksplit, split_small_ghost) is set.
 void finish_norm_plan(NormPlan& np, const bk_layer& L, int64_t B) {
+    if (np.path == Path::Ghost && np.var <= 1) {
+        const int64_t nsb = cdiv(L.T, bk::kSuper);
+        np.tiles = nsb * (nsb + 1) / 2;
+        np.tile_elems = bk::kGhostSplitTile;
+        np.npart = np.ksplit > 1 ? np.tiles * bk::kGhostSplitParts : np.tiles;
+    }
     if (np.path == Path::Inst && inst_splits(np.var)) {
         np.ksplit = inst_ksplit(B, np.tiles, L.T);
         if (np.ksplit > 1) np.npart = np.tiles * (np.tile_elems / bk::kSplitRedWG);
     }
-    np.nwg = np.path == Path::Inst ? B * np.tiles * np.ksplit : B * np.npart;
+    np.nwg = np.path == Path::Inst || np.ksplit > 1 ? B * np.tiles * np.ksplit : B * np.npart;
     const bool affine = L.kind == BK_NORM_AFFINE || (L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS));
     // A ghost layer on the 16-byte path with one 128-row block per sample
     // sums its bias terms while its g passes through LDS for the Gram.
-    np.fused_bias = np.path == Path::Ghost && np.var == 1 && L.T > 0 && L.T <= bk::kSuper &&
+    np.fused_bias = np.path == Path::Ghost && np.var == 1 && np.ksplit == 1 && L.T > 0 && L.T <= bk::kSuper &&
                     L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS) && L.p > 0;
     np.aff_chunks = affine && !np.fused_bias ? cdiv(L.p, bk::kAffineCols) : 0;
 }
@@ -265,13 +274,56 @@ void demote_small_full(std::vector<NormPlan>& plans, const bk_layer* layers, int
     }
 }
 
-// The norm plans of a launch's layers (norm_plan each, then the launch-wide
-// choice of demote_small_full).
+// The super-block pair kernel gives one workgroup per (layer, sample, pair),
+// each streaming its whole rows: with few samples most CUs idle (a head of
+// 50257 columns and 8 samples ran on 8 of 256 CUs).  When all such layers of a
+// call give fewer than kGhostSplitBelow workgroups (at 192 a split made a
+// float32 stack 1% slower, at 64 to 100 whole steps came out 3% to 18% faster),
+// their rows are cut into
+// column slices towards kGhostSplitTo workgroups, each slice at least
+// kGhostSplitChunks 128-byte chunks wide (its partial Gram, 48 KB written and
+// read back through the caches, against 256 KB of rows streamed).  The
+// partial Grams are only taken while the norms' workspace stays within
+// kGhostSplitWs, so that a call that fits the allocation-free scratch without
+// them still does.
+constexpr int64_t kGhostSplitBelow = 128, kGhostSplitTo = 512, kGhostSplitChunks = 16, kGhostSplitMax = 64;
+constexpr size_t kGhostSplitWs = (size_t)32 << 20;
+void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    auto small = [](const NormPlan& np) { return np.path == Path::Ghost && np.var <= 1 && np.nwg > 0; };
+    int64_t wg = 0;
+    for (const NormPlan& np : plans) wg += small(np) ? np.nwg : 0;
+    if (wg == 0 || wg >= kGhostSplitBelow) return;
+    const int64_t epc = 128 / (int64_t)elem_bytes(dt);
+    std::vector<NormPlan> split = plans;
+    size_t need = 0;
+    for (size_t l = 0; l < plans.size(); ++l) {
+        NormPlan& np = split[l];
+        if (small(np)) {
+            const int64_t ca = cdiv(layers[l].d, epc), cg = cdiv(layers[l].p, epc);
+            const int64_t ks = std::min({kGhostSplitTo / wg, (ca + cg) / kGhostSplitChunks, kGhostSplitMax});
+            if (ks >= 2 && ca > 0 && cg > 0) {
+                np.ksplit = ks;
+                np.ka = std::clamp<int64_t>((2 * ks * ca + ca + cg) / (2 * (ca + cg)), 1, ks - 1);
+                finish_norm_plan(np, layers[l], B);
+            }
+        }
+        need += norm_ws_bytes(np, B);
+    }
+    if (need <= kGhostSplitWs) plans.swap(split);
+}
+
+// The launch-wide choices over the norm plans of a call's layers.
+void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    demote_small_full(plans, layers, B);
+    split_small_ghost(plans, layers, dt, B);
+}
+
+// The norm plans of a call's layers (norm_plan each, then launch_wide).
 std::vector<NormPlan> norm_plans(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t B) {
     std::vector<NormPlan> v;
     v.reserve((size_t)n);
     for (int64_t l = 0; l < n; ++l) v.push_back(norm_plan(layers[l], dt, B));
-    demote_small_full(v, layers, B);
+    launch_wide(v, layers, dt, B);
     return v;
 }
 
@@ -387,6 +439,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
         // stack order left the XCDs up to ~20% apart in bytes.)
         a.remap = 0;
         for (const Item* it : v) a.remap |= it->np.npart > 1 ? 1 : 0;
+        a.tiles = tiles;
         if (!a.remap)
             std::stable_sort(v.begin(), v.end(), [&](const Item* x, const Item* y) {
                 auto cost = [&](const Item* it) {
@@ -409,6 +462,11 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
             g.wg_begin = (int32_t)wg;
             g.part_off = (int32_t)v[k]->part_off;
             g.Pb = v[k]->np.fused_bias ? L.Pb : nullptr;
+            g.ksplit = (int32_t)v[k]->np.ksplit;
+            g.ka = (int32_t)v[k]->np.ka;
+            g.tile_off = v[k]->tile_off;
+            g.red_begin = a.n_red;
+            if (g.ksplit > 1) a.n_red += (int32_t)(B * v[k]->np.npart);
             wg += v[k]->np.nwg;
         }
         if (wg > INT32_MAX) return fail(BK_ERR_NOT_SUPPORTED, "%s: grid too large", fn);
@@ -851,7 +909,7 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
     one[0].path = want;
     set_norm_variant(one[0], L, dt, B);
     finish_norm_plan(one[0], L, B);
-    demote_small_full(one, &L, B);
+    launch_wide(one, &L, dt, B);
     const NormPlan np = one[0];
     const size_t need = norm_ws_bytes(np, B);
     if (ws_bytes < need || (need > 0 && !ws))
@@ -897,6 +955,10 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
         g.p = (int32_t)L.p;
         g.nsb = ghost_nsb(L.T, np.var);
         g.npairs = (int32_t)np.npart;
+        g.ksplit = (int32_t)np.ksplit;
+        g.ka = (int32_t)np.ka;
+        a.tiles = part + align_up(norm_part_floats(np, B) * sizeof(float)) / sizeof(float);
+        a.n_red = np.ksplit > 1 ? (int32_t)(B * np.npart) : 0;
         e = launch_ghost_var(a, (int)np.nwg, dt == BK_BF16, want == Path::Embed, np.var, s);
     }
     if (e != hipSuccess) return hip_fail(e, "norm launch");
@@ -953,8 +1015,21 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
                 np.path = Path::Embed;
                 set_norm_variant(np, L, dt, B);
                 npart = std::max(npart, np.npart);
+                return align_up((size_t)(B * npart) * sizeof(float));
             }
-            return align_up((size_t)(B * npart) * sizeof(float));
+            // a column split's partial Grams, for aligned and unaligned rows
+            size_t need = align_up((size_t)(B * npart) * sizeof(float));
+            L.kind = BK_LINEAR;
+            for (uintptr_t mis : {(uintptr_t)0, (uintptr_t)4}) {
+                L.x = L.g = reinterpret_cast<const void*>(mis);
+                std::vector<NormPlan> one(1);
+                one[0].path = Path::Ghost;
+                set_norm_variant(one[0], L, dt, B);
+                finish_norm_plan(one[0], L, B);
+                launch_wide(one, &L, dt, B);
+                need = std::max(need, norm_ws_bytes(one[0], B));
+            }
+            return need;
         }
         case BK_OP_INST_NORM: {  // upper bound over the kernels (alignment is not known here)
             const size_t small = align_up((size_t)(B * cdiv(d, bk::kTile) * cdiv(p, bk::kTile)) * sizeof(float));

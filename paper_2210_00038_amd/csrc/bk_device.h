@@ -92,6 +92,37 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, ui
 }
 
 // ---------------------------------------------------------------------------
+// Rows that are not 16-byte aligned (row lengths or base pointers that are no
+// multiple of 16 bytes).  Global loads take any address that is a multiple of
+// the element size, so a lane still fetches 16 bytes at once; only the last,
+// partial piece of a row needs care: it is fetched from the row's last 16
+// bytes (tail_col) and shifted down afterwards (shift_tail), which also leaves
+// zeros past the row's end.  Rows hold at least 16 bytes.
+// ---------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ uint4 load16_any(const T* p) {
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ int tail_col(int k, int K) { return min(k, K - Elem<T>::per16); }
+// v = the 16 bytes at tail_col(k, K); returns the 16 bytes at k, zeros past K.
+template <typename T>
+__device__ __forceinline__ uint4 shift_tail(const uint4& v, int k, int K) {
+    const int s = (k - tail_col<T>(k, K)) * Elem<T>::bytes * 8;     // bits
+    uint64_t lo = (uint64_t)v.x | (uint64_t)v.y << 32, hi = (uint64_t)v.z | (uint64_t)v.w << 32;
+    if (s >= 64) {
+        lo = s >= 128 ? 0 : hi >> (s - 64);
+        hi = 0;
+    } else if (s > 0) {
+        lo = lo >> s | hi << (64 - s);
+        hi >>= s;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
+// ---------------------------------------------------------------------------
 // Workgroup barrier for LDS producer/consumer hand-offs.  It waits for this
 // wave's LDS (and scalar) operations only, not for its global loads still in
 // flight: those write the wave's own registers, so prefetches issued before

@@ -27,7 +27,14 @@ struct GhostLayer {
     int32_t npairs;     // nsb (nsb + 1) / 2 upper-triangle super-block pairs
     int32_t wg_begin;   // first workgroup of this layer in the launch
     int32_t part_off;   // first partial (float) of this layer in the workspace
-    int32_t pad;
+    // Column split (kGhostSplit* below): each (sample, pair) runs ksplit
+    // workgroups, slices [0, ka) on columns of a, the others on columns of g;
+    // their partial Grams go to GhostArgs::tiles from float tile_off on, and
+    // every pair has kGhostSplitParts partials.  ksplit 1: no split.
+    int32_t ksplit;
+    int32_t ka;
+    int32_t red_begin;  // first workgroup of the split's reduction
+    int64_t tile_off;
     // Linear layer with a bias, 16-byte rows and T <= 128: the per-sample
     // bias sums [B,p] go here and their squared norm joins the partials; else
     // nullptr.
@@ -37,9 +44,13 @@ constexpr int kMaxGhost = 64;
 struct GhostArgs {
     int32_t n, B;
     int32_t remap;      // 1: workgroup order remapped per XCD (xcd_remap)
+    int32_t n_red;      // workgroups of the column splits' reduction (0: no layer split)
     float* part;        // partial sums, [layer][sample][pair]
+    float* tiles;       // partial Grams of the column splits
     GhostLayer L[kMaxGhost];
 };
+constexpr int kGhostSplitTile = 128 * 128;   // floats of one partial Gram
+constexpr int kGhostSplitParts = 16;         // norm partials of a split pair: one per 32 x 32 sub-tile slot
 
 // ---- a^T diag(w) g GEMMs: instantiated norms and clipped gradients -------
 struct GemmLayer {

@@ -54,40 +54,40 @@ __device__ __forceinline__ WaveTiles wave_tiles(int wave, bool diag) {
     return t;
 }
 
-// 16 bytes of row r, starting at column k, of a [rows, K] matrix; zero outside.
-template <typename T, bool VEC>
-__device__ __forceinline__ uint4 load16(const T* X, int rows, int K, int r, int k) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r >= rows) return v;
-    const T* p = X + (size_t)r * (size_t)K + k;
-    if constexpr (VEC) {
-        if (k < K) v = *reinterpret_cast<const uint4*>(p);
-    } else {
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if constexpr (sizeof(T) == 2) {
-            const uint16_t* q = reinterpret_cast<const uint16_t*>(p);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (k + e < K) w[e >> 1] |= (uint32_t)q[e] << (16 * (e & 1));
-        } else {
-            const uint32_t* q = reinterpret_cast<const uint32_t*>(p);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (k + e < K) w[e] = q[e];
-        }
-        v = make_uint4(w[0], w[1], w[2], w[3]);
+// The K elements (fewer than 16 bytes) of a short row, zeros after them; at
+// column k > 0 there is nothing.
+template <typename T>
+__device__ __forceinline__ uint4 load_short_row(const T* row, int K, int k) {
+    uint64_t lo = 0, hi = 0;
+    constexpr int W = Elem<T>::bytes * 8;
+#pragma unroll 1
+    for (int e = k == 0 ? K - 1 : -1; e >= 0; --e) {
+        uint64_t x;
+        if constexpr (sizeof(T) == 2) x = row[e].bits;
+        else x = __float_as_uint(row[e]);
+        hi = hi << W | lo >> (64 - W);
+        lo = lo << W | x;
     }
-    return v;
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
-// Accumulate this wave's sub-tiles of X X^T, X = one sample's [rows, K] matrix,
-// rows of block R starting at rowR and of block C at rowC.
-template <typename T, bool VEC>
-__device__ __forceinline__ void gram(const T* __restrict__ X, int rows, int K, int rowR, int rowC,
-                                     bool diag, const WaveTiles& wt, f32x16_t acc[4],
-                                     uint4* __restrict__ lds) {
+// Accumulate this wave's sub-tiles of X X^T over the 128-byte column chunks
+// [ch0, ch1), X = one sample's [rows, K] matrix with rows of any alignment,
+// rows of block R starting at rowR and of block C at rowC.  On the diagonal
+// two register sets of chunks are in flight while a third is multiplied out of
+// LDS; off the diagonal a chunk is twice as large and one set is in flight.
+// HBM-bound once enough workgroups run (the column split below).  With 2-byte
+// loads (eight per 16 bytes) and whole rows per workgroup, the odd head 768 ->
+// 50257 (8 samples of 128 tokens, 104 MB of g) took 5.49 ms; with 16-byte loads
+// at any alignment and 24 column slices per sample 28 us (3.8 TB/s) and 15 us
+// for the reduction of the slices.
+template <typename T, bool DIAG>
+__device__ __forceinline__ void gram_rows(const T* __restrict__ X, int rows, int K, int rowR, int rowC, int ch0,
+                                          int ch1, const WaveTiles& wt, f32x16_t acc[4],
+                                          uint4* __restrict__ lds) {
     constexpr int EPV = Elem<T>::per16;       // elements per 16 bytes
     constexpr int EPC = 8 * EPV;              // elements per 128-byte chunk
+    constexpr int NP = DIAG ? 4 : 8;          // 16-byte pieces per thread and chunk
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -97,29 +97,37 @@ __device__ __forceinline__ void gram(const T* __restrict__ X, int rows, int K, i
     const int c16 = tid & 7, rq = tid >> 3;
     const int r = lane & 31, h = lane >> 5;
     uint4* ldsR = lds;
-    uint4* ldsC = diag ? lds : lds + kBlockU4;
-    const int nch = (K + EPC - 1) / EPC;
+    uint4* ldsC = DIAG ? lds : lds + kBlockU4;
+    const bool wide = K >= EPV;               // rows of at least 16 bytes
 
-    uint4 pr[8];
-    auto fetch = [&](int ch) {
-        const int k = ch * EPC + c16 * EPV;
+    const T* base[NP];                        // this thread's rows (row 0 where there is none)
+    bool ok[NP];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            pr[q] = load16<T, VEC>(X, rows, K, rowR + rq + 32 * q, k);
-            if (!diag) pr[4 + q] = load16<T, VEC>(X, rows, K, rowC + rq + 32 * q, k);
+    for (int q = 0; q < NP; ++q) {
+        const int row = (q < 4 ? rowR : rowC) + rq + 32 * (q & 3);
+        ok[q] = row < rows;
+        base[q] = X + (size_t)(ok[q] ? row : 0) * (size_t)K;
+    }
+    auto fetch = [&](uint4 (&pr)[NP], int ch) {
+        const int k = ch * EPC + c16 * EPV;
+        const int kc = tail_col<T>(k, K);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            pr[q] = make_uint4(0u, 0u, 0u, 0u);
+            if (ok[q] && ch < ch1) pr[q] = wide ? load16_any<T>(base[q] + kc) : load_short_row<T>(base[q], K, k);
         }
     };
-    fetch(0);
-    for (int ch = 0; ch < nch; ++ch) {
+    auto chunk = [&](uint4 (&pr)[NP], int ch) {
         lds_barrier();
+        if (wide && (ch + 1) * EPC > K) {     // the row's last chunk (uniform)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            ldsR[(rq + 32 * q) * kRowU4 + c16] = pr[q];
-            if (!diag) ldsC[(rq + 32 * q) * kRowU4 + c16] = pr[4 + q];
+            for (int q = 0; q < NP; ++q) pr[q] = shift_tail<T>(pr[q], ch * EPC + c16 * EPV, K);
         }
+#pragma unroll
+        for (int q = 0; q < NP; ++q) (q < 4 ? ldsR : ldsC)[(rq + 32 * (q & 3)) * kRowU4 + c16] = pr[q];
         lds_barrier();
-        if (ch + 1 < nch) fetch(ch + 1);
-        if ((wt.w[0] | wt.w[1] | wt.w[2] | wt.w[3]) == 0) continue;   // wave-uniform
+        fetch(pr, ch + (DIAG ? 2 : 1));
+        if ((wt.w[0] | wt.w[1] | wt.w[2] | wt.w[3]) == 0) return;   // wave-uniform
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int col = 2 * j + h;
@@ -135,6 +143,19 @@ __device__ __forceinline__ void gram(const T* __restrict__ X, int rows, int K, i
             Mfma<T>::step(acc[2], x1, y0);
             Mfma<T>::step(acc[3], x1, y1);
         }
+    };
+    uint4 p0[NP], p1[NP];
+    fetch(p0, ch0);
+    int ch = ch0;
+    if constexpr (DIAG) {
+        fetch(p1, ch0 + 1);
+        for (; ch + 1 < ch1; ch += 2) {
+            chunk(p0, ch);
+            chunk(p1, ch + 1);
+        }
+        if (ch < ch1) chunk(p0, ch);
+    } else {
+        for (; ch < ch1; ++ch) chunk(p0, ch);
     }
 }
 
@@ -171,7 +192,7 @@ constexpr int kRingBytes = 64 * 1024;        // LDS ring of gram_dl
 // fixed order.
 template <typename T, bool DIAG, int CW>
 __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K, int rowR, int rowC,
-                                        const WaveTiles& wt, f32x16_t acc[4], char* __restrict__ lds,
+                                        int ch0, int ch1, const WaveTiles& wt, f32x16_t acc[4], char* __restrict__ lds,
                                         float* __restrict__ cs = nullptr, float* bsq = nullptr,
                                         float* cbuf = nullptr) {
     static_assert(CW == 64 || CW == 128 || CW == 256, "chunk width");
@@ -196,7 +217,7 @@ __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, h = lane >> 5;
-    const int nch = (K + EPC - 1) / EPC;
+    const int nch = ch1 - ch0;                // chunks ch0 + (0 .. nch - 1) of the rows
     const uint32_t rowbytes = (uint32_t)K * (uint32_t)sizeof(T);
     // The host guarantees (rows + 128) * rowbytes < 2^31 for this path.
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(X, (uint32_t)rows * rowbytes);
@@ -219,10 +240,10 @@ __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K
 #pragma unroll
         for (int b = 0; b < SPC; ++b) {
             const uint32_t base = (uint32_t)(b == 0 ? rowR : rowC) * rowbytes +
-                                  (uint32_t)(ch * EPC) * (uint32_t)sizeof(T);
+                                  (uint32_t)((ch0 + ch) * EPC) * (uint32_t)sizeof(T);
 #pragma unroll
             for (int i = 0; i < LPB; ++i) {
-                const bool ok = ch * EPC + lcol[i] * EPV < K;
+                const bool ok = ch < nch && (ch0 + ch) * EPC + lcol[i] * EPV < K;
                 buffer_load16_lds(rs, ok ? base + roff[i] : kGhostOut, slot + b * SLOT + (4 * i + wave) * 1024);
             }
         }
@@ -292,7 +313,7 @@ __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K
         if (tid < EPC) {
             const float* cb = cbuf + (ch & 1) * 512 + tid;
             const float v = ((cb[0] + cb[128]) + cb[256]) + cb[384];
-            const int k = ch * EPC + tid;
+            const int k = (ch0 + ch) * EPC + tid;
             if (k < K) {
                 cs[k] = v;
                 *bsq += v * v;
@@ -327,15 +348,24 @@ __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K
     }
 }
 
+// Columns of a row that one chunk of gram_any covers (elements).
+template <typename T, bool VEC>
+__device__ __forceinline__ int gram_epc(bool diag) {
+    return (VEC ? (diag ? BK_GHOST_DIAG_CW : BK_GHOST_OFF_CW) : 128) / (int)sizeof(T);
+}
+
+// Gram of chunks [ch0, ch1) (of gram_epc columns each).
 template <typename T, bool VEC>
 __device__ __forceinline__ void gram_any(const T* __restrict__ X, int rows, int K, int rowR, int rowC,
-                                         bool diag, const WaveTiles& wt, f32x16_t acc[4], char* smem,
-                                         float* cs = nullptr, float* bsq = nullptr, float* cbuf = nullptr) {
+                                         bool diag, int ch0, int ch1, const WaveTiles& wt, f32x16_t acc[4],
+                                         char* smem, float* cs = nullptr, float* bsq = nullptr,
+                                         float* cbuf = nullptr) {
     if constexpr (VEC) {
-        if (diag) gram_dl<T, true, BK_GHOST_DIAG_CW>(X, rows, K, rowR, rowC, wt, acc, smem, cs, bsq, cbuf);
-        else gram_dl<T, false, BK_GHOST_OFF_CW>(X, rows, K, rowR, rowC, wt, acc, smem);
+        if (diag) gram_dl<T, true, BK_GHOST_DIAG_CW>(X, rows, K, rowR, rowC, ch0, ch1, wt, acc, smem, cs, bsq, cbuf);
+        else gram_dl<T, false, BK_GHOST_OFF_CW>(X, rows, K, rowR, rowC, ch0, ch1, wt, acc, smem);
     } else {
-        gram<T, VEC>(X, rows, K, rowR, rowC, diag, wt, acc, reinterpret_cast<uint4*>(smem));
+        if (diag) gram_rows<T, true>(X, rows, K, rowR, rowC, ch0, ch1, wt, acc, reinterpret_cast<uint4*>(smem));
+        else gram_rows<T, false>(X, rows, K, rowR, rowC, ch0, ch1, wt, acc, reinterpret_cast<uint4*>(smem));
     }
 }
 
@@ -769,7 +799,7 @@ __global__ __launch_bounds__(kFullThreads) void ghost_long_kernel(const GhostArg
 }
 
 template <typename T, bool EMBED, bool VEC>
-__global__ __launch_bounds__(256) void ghost_norm_kernel(const GhostArgs args) {
+__global__ __launch_bounds__(256, 2) void ghost_norm_kernel(const GhostArgs args) {
     // VEC: the ring of gram_dl; otherwise two padded blocks for gram.
     __shared__ __attribute__((aligned(16))) char smem[VEC ? kRingBytes : 2 * kBlockU4 * 16];
     uint4* lds = reinterpret_cast<uint4*>(smem);
@@ -786,13 +816,18 @@ __global__ __launch_bounds__(256) void ghost_norm_kernel(const GhostArgs args) {
     const GhostLayer& L = args.L[l];
     const int nT = L.T, d = L.d, p = L.p, nsb = L.nsb, npairs = L.npairs;
     const int local = wg - L.wg_begin;
-    const int sample = local / npairs;
-    int pair = local - sample * npairs;
+    const int ks = EMBED ? 1 : L.ksplit;                       // column slices per pair
+    const int unit = local / ks, slice = local - unit * ks;    // unit = (sample, pair)
+    const int units = ks > 1 ? npairs / kGhostSplitParts : npairs;
+    const int sample = unit / units;
+    int pair = unit - sample * units;
     int R = 0;
     while (pair >= nsb - R) { pair -= nsb - R; ++R; }
     const int C = R + pair;
     const bool diag = (R == C);
     const int rowR = R * kSuper, rowC = C * kSuper;
+    const int epc = gram_epc<T, VEC>(diag);
+    const int nchA = (d + epc - 1) / epc, nchG = (p + epc - 1) / epc;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     WaveTiles wt = wave_tiles(wave, diag);
@@ -813,7 +848,7 @@ __global__ __launch_bounds__(256) void ghost_norm_kernel(const GhostArgs args) {
         const int row = (t < kSuper) ? rowR + t : rowC + (t - kSuper);
         const int64_t id = (row < nT) ? ids[row] : (int64_t)-1;
         sid[t] = (id >= 0 && id < (int64_t)d) ? id : (int64_t)-1;
-        gram_any<T, VEC>(reinterpret_cast<const T*>(L.g) + off_g, nT, p, rowR, rowC, diag, wt, accG, smem);
+        gram_any<T, VEC>(reinterpret_cast<const T*>(L.g) + off_g, nT, p, rowR, rowC, diag, 0, nchG, wt, accG, smem);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if (!wt.w[s]) continue;
@@ -828,12 +863,29 @@ __global__ __launch_bounds__(256) void ghost_norm_kernel(const GhostArgs args) {
     } else {
         f32x16_t accA[4];
         const size_t off_a = (size_t)sample * (size_t)nT * (size_t)d;
-        gram_any<T, VEC>(reinterpret_cast<const T*>(L.x) + off_a, nT, d, rowR, rowC, diag, wt, accA, smem);
+        if (ks > 1) {
+            // This slice's part of one of the two Grams, to the workspace:
+            // sub-tile slot 4 wave + s as [16][64 lanes].
+            const bool isa = slice < L.ka;
+            const int j = isa ? slice : slice - L.ka, nj = isa ? L.ka : ks - L.ka, nch = isa ? nchA : nchG;
+            gram_any<T, VEC>(reinterpret_cast<const T*>(isa ? L.x : L.g) + (isa ? off_a : off_g), nT, isa ? d : p, rowR,
+                             rowC, diag, (int)((int64_t)j * nch / nj), (int)((int64_t)(j + 1) * nch / nj), wt, accG,
+                             smem);
+            float* out = args.tiles + L.tile_off + ((size_t)unit * ks + slice) * kGhostSplitTile;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (!wt.w[s]) continue;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) out[((4 * wave + s) * 16 + i) * 64 + lane] = accG[s][i];
+            }
+            return;
+        }
+        gram_any<T, VEC>(reinterpret_cast<const T*>(L.x) + off_a, nT, d, rowR, rowC, diag, 0, nchA, wt, accA, smem);
         // Bias of the layer (host: only with 16-byte rows and T <= 128, one
         // diagonal block per sample): its per-sample sums s = sum_t g_t go to
         // Pb and |s|^2 joins this workgroup's partial.
         float* cs = (VEC && L.Pb) ? L.Pb + (size_t)sample * p : nullptr;
-        gram_any<T, VEC>(reinterpret_cast<const T*>(L.g) + off_g, nT, p, rowR, rowC, diag, wt, accG, smem,
+        gram_any<T, VEC>(reinterpret_cast<const T*>(L.g) + off_g, nT, p, rowR, rowC, diag, 0, nchG, wt, accG, smem,
                          cs, &part, cbuf);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -846,7 +898,55 @@ __global__ __launch_bounds__(256) void ghost_norm_kernel(const GhostArgs args) {
     }
     const float tot = block_sum_256(part, red);
     if (threadIdx.x == 0)
-        args.part[(size_t)L.part_off + (size_t)sample * npairs + (local - sample * npairs)] = tot;
+        args.part[(size_t)L.part_off + (size_t)sample * npairs + (unit - sample * units)] = tot;
+}
+
+// Finishes the column splits: one workgroup per (layer, sample, pair, 32 x 32
+// sub-tile slot) adds the slot's slices of Gram(a) and of Gram(g), each in
+// slice order, and writes the weighted sum of their elementwise product as one
+// partial.  Slots without weight (below the diagonal, padding rows) give 0.
+__global__ __launch_bounds__(256) void ghost_split_reduce_kernel(const GhostArgs args) {
+    __shared__ float red[4];
+    const int wg = blockIdx.x;
+    const int l = find_desc(args.n, (int64_t)wg, [&](int k) { return args.L[k].red_begin; });
+    const GhostLayer& L = args.L[l];
+    const int job = wg - L.red_begin;
+    const int unit = job / kGhostSplitParts, slot = job - unit * kGhostSplitParts;
+    const int ks = L.ksplit, units = L.npairs / kGhostSplitParts, nsb = L.nsb;
+    int pair = unit - (unit / units) * units;
+    int R = 0;
+    while (pair >= nsb - R) { pair -= nsb - R; ++R; }
+    const int C = R + pair;
+    const int wave = slot >> 2, s = slot & 3;
+    const WaveTiles wt = wave_tiles(wave, R == C);
+    const int w = R * kSuper + (wt.r0 + (s >> 1)) * 32 >= L.T || C * kSuper + (wt.c0 + (s & 1)) * 32 >= L.T ? 0 : wt.w[s];
+    float v = 0.f;
+    if (w) {
+        const float* src = args.tiles + L.tile_off + (size_t)unit * ks * kGhostSplitTile + slot * 1024 + 4 * threadIdx.x;
+        float4 sum[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int q1 = o ? ks : L.ka;
+            sum[o] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q0 = o ? L.ka : 0; q0 < q1; q0 += 8) {
+                float4 t[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (q0 + j < q1) t[j] = *reinterpret_cast<const float4*>(src + (size_t)(q0 + j) * kGhostSplitTile);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (q0 + j < q1) {
+                        sum[o].x += t[j].x;
+                        sum[o].y += t[j].y;
+                        sum[o].z += t[j].z;
+                        sum[o].w += t[j].w;
+                    }
+            }
+        }
+        v = (float)w * (sum[0].x * sum[1].x + sum[0].y * sum[1].y + sum[0].z * sum[1].z + sum[0].w * sum[1].w);
+    }
+    const float tot = block_sum_256(v, red);
+    if (threadIdx.x == 0) args.part[(size_t)L.part_off + job] = tot;
 }
 
 }  // namespace
@@ -871,6 +971,7 @@ hipError_t launch_ghost(const GhostArgs& args, int n_wg, bool bf16, bool embed, 
         else       { if (vec) BK_GHOST(float, false, true); else BK_GHOST(float, false, false); }
     }
 #undef BK_GHOST
+    if (args.n_red > 0) hipLaunchKernelGGL(ghost_split_reduce_kernel, dim3(args.n_red), block, 0, s, args);
     return hipGetLastError();
 }
 

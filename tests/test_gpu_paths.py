@@ -1,0 +1,79 @@
+"""Kernel variants at the sizes where their tiles, slices and row tails end,
+against the float64 oracle.  Bounds: the float32 sums of exact products (bf16
+values multiply exactly in float32) stay within the norm and gradient guards
+of tolerances.py; float32 inputs within its gates."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tolerances import GRAD_GATE, GRAD_GUARD_EXACT, GRAD_GUARD_ROUNDED, NORM_GATE, NORM_GUARD  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.fixture(scope="module")
+def bk():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2210_00038_amd as m
+    return m
+
+
+def _rel(x, ref):
+    x, ref = np.asarray(x, np.float64), np.asarray(ref, np.float64)
+    return np.max(np.abs(x - ref) / np.maximum(np.abs(ref), 1e-300)) if ref.size else 0.0
+
+
+def _frob(x, ref):
+    x, ref = np.asarray(x, np.float64), np.asarray(ref, np.float64)
+    n = np.linalg.norm(ref)
+    return np.linalg.norm(x - ref) / n if n > 0 else np.linalg.norm(x)
+
+
+def _norm_bound(dtype):
+    return NORM_GATE["f32"] if dtype == F32 else NORM_GUARD
+
+
+def _draw(B, T, d, dtype, gen, scale=1.0, offset=0):
+    """[B, T, d] values; offset: elements by which the first one misses 16-byte alignment."""
+    buf = torch.empty(B * T * d + offset + 16, dtype=dtype, device=DEV)
+    x = buf[offset:offset + B * T * d].view(B, T, d)
+    v = (torch.randn(B, T, d, generator=gen) * scale).to(dtype)
+    x.copy_(v)
+    return x, v
+
+
+# One 128-row block or several, rows of any alignment or of 16-byte multiples,
+# few enough (sample, pair) workgroups that the rows are cut into column slices.
+@pytest.mark.parametrize("B,T,d,p,dtype,off", [
+    (2, 100, 1031, 4099, BF, 0),     # odd rows, slices with a ragged last chunk
+    (1, 128, 768, 5000, BF, 0),      # 16-byte rows, slices
+    (2, 130, 2051, 1025, F32, 0),    # two row blocks, odd float32 rows, slices
+    (2, 200, 1000, 1032, BF, 3),     # 16-byte row lengths, misaligned base
+    (3, 100, 7, 3, BF, 0),           # rows shorter than 16 bytes
+    (3, 70, 3, 41, F32, 0),
+    (2, 65, 8, 9, BF, 0),            # rows of exactly one piece, and one element more
+    (300, 66, 13, 71, BF, 0),        # enough workgroups: no slices
+])
+def test_ghost_rows_and_column_slices(bk, B, T, d, p, dtype, off):
+    gen = torch.Generator().manual_seed(B * 100 + T + d)
+    a, ah = _draw(B, T, d, dtype, gen, 1.0, off)
+    g, gh = _draw(B, T, p, dtype, gen, 1e-2, off)
+    a[B - 1].zero_()
+    ah[B - 1] = 0
+    ref = oracle.linear_norm_sq(ah, gh)
+    out = bk.bk_ghost_norm(a, g)
+    assert torch.equal(out, bk.bk_ghost_norm(a, g))
+    out = out.cpu().numpy()
+    assert out[B - 1] == 0.0 and _rel(out[:B - 1], ref[:B - 1]) <= _norm_bound(dtype)
+    # in a stack with a bias (its sums run apart when the rows are sliced)
+    Pb, norm = torch.empty(B, p, device=DEV), torch.empty(2, B, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "bias": True, "Pb": Pb}, {"x": a, "g": g}])
+    bk.bk_layer_norms(arr, 2, bk.BK_BF16 if dtype == BF else bk.BK_F32, B, norm)
+    sb = oracle.bias_sums(gh)
+    got = norm.cpu().numpy()
+    assert _frob(Pb.cpu().numpy(), sb) <= 1e-5
+    assert _rel(got[0], ref + (sb ** 2).sum(1)) <= _norm_bound(dtype)
+    assert _rel(got[1][:B - 1], ref[:B - 1]) <= _norm_bound(dtype)
