@@ -339,6 +339,12 @@ __global__ __launch_bounds__(256) void agemm_kernel(const GemmArgs args) {
 // in registers while the waves multiply.  LDS rows are padded to 576 / 320
 // bytes so that the four rows a 16-lane group reads fall on distinct banks.
 // The other workgroup on the CU covers this one's barriers.
+//
+// ANY (GemmVariant::WideAny): rows of any alignment.  Bound by the staging
+// path as the aligned form, plus loads that straddle cache lines: the head
+// 768 -> 50257 on 8 x 128 tokens takes 175 us (453 TFLOP/s) against 1140-1165 us
+// with the element loads of the 128 x 128 kernel, which now keeps only rows of
+// fewer than 8 columns.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kOut = 0xFFFFFFF0u;           // buffer offset that loads zeros
 constexpr int kBM = kWideM, kBN = kWideN, kBK = kWideK;
@@ -397,7 +403,7 @@ __device__ __forceinline__ uint32_t scale_bf16x2(uint32_t w, float c) {
 }
 
 
-template <bool INST>
+template <bool INST, bool ANY>
 __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args, int n_wg) {
     __shared__ __attribute__((aligned(16))) char ldsA[kBK * kSA];
     __shared__ __attribute__((aligned(16))) char ldsB[kBK * kSB];
@@ -442,17 +448,40 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.f;
 
+    // ANY: rows of any alignment, at least 8 columns each.  Every piece is a
+    // plain 16-byte load from inside its row: a piece past the last column
+    // reads the row's last 16 bytes (its tile columns are never stored or
+    // summed, unless it begins before the end, when it is shifted into place
+    // on its way to LDS), a row past the last one reads that one and is
+    // zeroed on its way to LDS.
+    const int colA = ANY ? tail_col<bf16_t>(m0 + ca, d) : 0, colB = ANY ? tail_col<bf16_t>(n0 + cb, p) : 0;
+    const bool edgeA = ANY && m0 + kBM > d, edgeB = ANY && n0 + kBN > p;   // uniform
+
     uint4 va[8], vb[4];
     float cw[4];
     auto fetch = [&](uint32_t k0) {
-        const __amdgpu_buffer_rsrc_t rA = rows_rsrc(baseA, rowA, k0, nrows, kBK);
-        const __amdgpu_buffer_rsrc_t rB = rows_rsrc(baseB, rowB, k0, nrows, kBK);
+        if constexpr (ANY) {
+            const bool last = k0 + kBK > nrows;                            // uniform
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            va[j] = buffer_load16(rA, offA == kOut ? kOut : offA + 8u * j * rowA);
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t k = k0 + (uint32_t)(ka + 8 * j);
+                va[j] = load16_any<bf16_t>(baseA + (size_t)(last ? min(k, nrows - 1u) : k) * (uint32_t)d + colA);
+            }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            vb[j] = buffer_load16(rB, offB == kOut ? kOut : offB + 16u * j * rowB);
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t k = k0 + (uint32_t)(kb + 16 * j);
+                vb[j] = load16_any<bf16_t>(baseB + (size_t)(last ? min(k, nrows - 1u) : k) * (uint32_t)p + colB);
+            }
+        } else {
+            const __amdgpu_buffer_rsrc_t rA = rows_rsrc(baseA, rowA, k0, nrows, kBK);
+            const __amdgpu_buffer_rsrc_t rB = rows_rsrc(baseB, rowB, k0, nrows, kBK);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                va[j] = buffer_load16(rA, offA == kOut ? kOut : offA + 8u * j * rowA);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                vb[j] = buffer_load16(rB, offB == kOut ? kOut : offB + 16u * j * rowB);
+        }
         if constexpr (!INST) {
             // Clip weight of each staged g row: C[k / T].  When T >= 64 the 64
             // rows of a stage span at most two samples (scalar split point).
@@ -480,6 +509,24 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
     if (st_begin < nst) fetch(st_begin * kBK);
     for (uint32_t st = st_begin; st < nst; ++st) {
         lds_barrier();
+        if constexpr (ANY) {
+            if (edgeA) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) va[j] = shift_tail<bf16_t>(va[j], m0 + ca, d);
+            }
+            if (edgeB) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) vb[j] = shift_tail<bf16_t>(vb[j], n0 + cb, p);
+            }
+            if ((st + 1) * kBK > nrows) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (st * kBK + (uint32_t)(ka + 8 * j) >= nrows) va[j] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (st * kBK + (uint32_t)(kb + 16 * j) >= nrows) vb[j] = make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             *reinterpret_cast<uint4*>(ldsA + (ka + 8 * j) * kSA + ca * 2) = va[j];
@@ -1373,7 +1420,7 @@ hipError_t launch_split_reduce(const GemmArgs& args, int n_wg, bool inst_norm, G
                                hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
     const dim3 grid(n_wg), block(256);
-    if (inst_norm && v == GemmVariant::Wide)
+    if (inst_norm && (v == GemmVariant::Wide || v == GemmVariant::WideAny))
         hipLaunchKernelGGL((split_reduce_kernel<kBM, kBN, true>), grid, block, 0, s, args);
     else if (!inst_norm && (v == GemmVariant::Grad || v == GemmVariant::GradDL))
         hipLaunchKernelGGL((split_reduce_kernel<kGM, kGN, false>), grid, block, 0, s, args);
@@ -1406,8 +1453,13 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
         return hipGetLastError();
     }
     if (v == GemmVariant::Wide) {
-        if (inst_norm) hipLaunchKernelGGL(agemm_bf16_kernel<true>, grid, block, 0, s, args, n_wg);
-        else hipLaunchKernelGGL(agemm_bf16_kernel<false>, grid, block, 0, s, args, n_wg);
+        if (inst_norm) hipLaunchKernelGGL((agemm_bf16_kernel<true, false>), grid, block, 0, s, args, n_wg);
+        else hipLaunchKernelGGL((agemm_bf16_kernel<false, false>), grid, block, 0, s, args, n_wg);
+        return hipGetLastError();
+    }
+    if (v == GemmVariant::WideAny) {
+        if (inst_norm) hipLaunchKernelGGL((agemm_bf16_kernel<true, true>), grid, block, 0, s, args, n_wg);
+        else hipLaunchKernelGGL((agemm_bf16_kernel<false, true>), grid, block, 0, s, args, n_wg);
         return hipGetLastError();
     }
     if (v == GemmVariant::Narrow32) {

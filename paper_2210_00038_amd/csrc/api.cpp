@@ -105,7 +105,7 @@ struct NormPlan {
     bool fused_bias = false;  // ghost layer whose kernel also forms the bias sums (no second run)
 };
 
-// Variants whose kernels can split a tile's contraction into K slices.
+// Variants whose instantiated norms split a tile's contraction into K slices.
 bool inst_splits(int var) {
     return var == (int)bk::GemmVariant::Wide || var == (int)bk::GemmVariant::Narrow32 ||
            var == (int)bk::GemmVariant::Narrow64;

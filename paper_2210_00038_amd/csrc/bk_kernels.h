@@ -121,7 +121,8 @@ struct NoiseArgs {
 constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by one workgroup
 
 // Kernel variant of the a^T g GEMMs for one layer:
-//  Scalar: element loads (rows not 16-byte multiples / unaligned), 128 x 128;
+//  Scalar: element loads (rows not 16-byte multiples / unaligned, that no
+//          other variant takes), 128 x 128;
 //  Vec   : 16-byte loads, register transpose, 128 x 128 (fp32, or huge bf16);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
 //  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads (T >= 64);
@@ -130,8 +131,9 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 //          kDLStageRows rows).
 //  Narrow32 / Narrow64: bf16, one side of d x p at most 32 / 64, tiles of
 //          256 along the long side (operands swapped when d < p).
-enum class GemmVariant { Scalar = 0, Vec = 1, Wide = 2, Grad = 3, GradDL = 4, Narrow32 = 5, Narrow64 = 6 };
-constexpr int kGemmVariants = 7;
+//  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns.
+enum class GemmVariant { Scalar = 0, Vec = 1, Wide = 2, Grad = 3, GradDL = 4, Narrow32 = 5, Narrow64 = 6, WideAny = 7 };
+constexpr int kGemmVariants = 8;
 constexpr int kDMaxB = 4096;
 constexpr int kDLStageRows = 32;   // k rows per stage of the GradDL kernel
 constexpr int kDLBuffers = 4;      // its LDS stage buffers (the ping-pong schedule takes four)

@@ -15,7 +15,8 @@ GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p) {
     switch (v) {
         case GemmVariant::Grad:
         case GemmVariant::GradDL: return {cdiv(d, kGradM), cdiv(p, kGradN), (int64_t)kGradM * kGradN, false};
-        case GemmVariant::Wide: return {cdiv(d, kWideM), cdiv(p, kWideN), (int64_t)kWideM * kWideN, false};
+        case GemmVariant::Wide:
+        case GemmVariant::WideAny: return {cdiv(d, kWideM), cdiv(p, kWideN), (int64_t)kWideM * kWideN, false};
         case GemmVariant::Narrow32:
         case GemmVariant::Narrow64: {
             const int64_t bn = v == GemmVariant::Narrow32 ? 32 : 64;
@@ -29,7 +30,8 @@ GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p) {
 GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, bool aligned) {
     const int64_t es = bf16 ? 2 : 4;
     const bool vec = aligned && (d * es) % 16 == 0 && (p * es) % 16 == 0;
-    if (!vec) return GemmVariant::Scalar;
+    // bf16 rows of any alignment, 8 columns or more on both sides.
+    if (!vec) return bf16 && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
     // The wide and narrow kernels address one K stage of rows at a time with
     // 32-bit buffer offsets (rows_rsrc): a stage must fit in 2^31 bytes.
     (void)rows;

@@ -38,7 +38,7 @@ def _norm_bound(dtype):
 
 def _draw(B, T, d, dtype, gen, scale=1.0, offset=0):
     """[B, T, d] values; offset: elements by which the first one misses 16-byte alignment."""
-    buf = torch.empty(B * T * d + offset + 16, dtype=dtype, device=DEV)
+    buf = torch.full((B * T * d + offset + 16,), float("nan"), dtype=dtype, device=DEV)
     x = buf[offset:offset + B * T * d].view(B, T, d)
     v = (torch.randn(B, T, d, generator=gen) * scale).to(dtype)
     x.copy_(v)
@@ -77,3 +77,31 @@ def test_ghost_rows_and_column_slices(bk, B, T, d, p, dtype, off):
     assert _frob(Pb.cpu().numpy(), sb) <= 1e-5
     assert _rel(got[0], ref + (sb ** 2).sum(1)) <= _norm_bound(dtype)
     assert _rel(got[1][:B - 1], ref[:B - 1]) <= _norm_bound(dtype)
+
+
+# bf16 rows of any alignment on the 256 x 128 tiles: ragged last pieces of
+# either operand, row counts around the 64-row stage, several tiles.
+@pytest.mark.parametrize("B,T,d,p,off", [
+    (2, 40, 8, 9, 0),          # one piece per row, one element more
+    (3, 64, 257, 131, 0),      # one column past a tile on both sides, whole stages
+    (3, 65, 255, 127, 0),      # one column short of a tile, one row past a stage
+    (5, 13, 1000, 15, 0),      # several samples per stage
+    (2, 130, 264, 136, 1),     # 16-byte row lengths, misaligned base
+    (130, 1, 300, 10, 0),      # one token a sample
+])
+def test_gemm_rows_of_any_alignment(bk, B, T, d, p, off):
+    gen = torch.Generator().manual_seed(B + 10 * T + d)
+    a, ah = _draw(B, T, d, BF, gen, 1.0, off)
+    g, gh = _draw(B, T, p, BF, gen, 1e-2, off)
+    # what lies around the rows must not reach the results
+    C = torch.rand(B, generator=gen) + 0.1
+    C[B // 2] = 0.0
+    G = bk.bk_weighted_grad(a, g, C.to(DEV))
+    assert _frob(G.cpu().numpy(), oracle.weighted_grad(ah, gh, C)) <= GRAD_GUARD_ROUNDED
+    C2 = torch.exp2(torch.randint(-3, 4, (B,), generator=gen).float())       # exact in bf16
+    G = bk.bk_weighted_grad(a, g, C2.to(DEV))
+    assert _frob(G.cpu().numpy(), oracle.weighted_grad(ah, gh, C2)) <= GRAD_GUARD_EXACT
+    norm, P = bk.bk_per_sample_grads(a, g)
+    assert torch.equal(norm, bk.bk_inst_norm(a, g))
+    assert _rel(norm.cpu().numpy(), oracle.linear_norm_sq(ah, gh)) <= NORM_GUARD
+    assert _frob(P.cpu().numpy(), oracle.per_sample_grads(ah, gh)) <= GRAD_GUARD_EXACT
