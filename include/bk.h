@@ -195,9 +195,11 @@ bk_status bk_per_sample_grads(const void* a, const void* g, bk_dtype dt, int64_t
 
 /* Weighted sum of stored per-sample gradients (App. B.5), BK-MixOpt's
  * clipped gradient on an instantiated layer:
- *   G[e] = sum_i C[i] P[i n + e]   for e in [0, n), i ascending, float32
- * (one fused multiply-add per sample).  P [B, n], C [B], G [n] float32
- * (device); B = 0 writes zeros.  Needs no workspace. */
+ *   G[e] = sum_i C[i] P[i n + e]   for e in [0, n), float32, one fused
+ * multiply-add per sample: i ascending, or, for B >= 16 and n <= 65536, 16
+ * interleaved runs of samples (i mod 16) whose sums are added in order.
+ * P [B, n], C [B], G [n] float32 (device); B = 0 writes zeros.  Needs no
+ * workspace. */
 bk_status bk_weighted_sum(const float* P, const float* C, int64_t B, int64_t n, float* G,
                           void* stream);
 

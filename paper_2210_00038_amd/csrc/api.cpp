@@ -725,6 +725,8 @@ size_t weighted_grads_ws(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t
 }
 
 // Appends one weighted-sum job (P [B, n] -> G [n]) to a grouped launch.
+// Short vectors over many samples (biases, LayerNorm affines: n <= 65536, at
+// least 16 samples) give each element 16 threads, which add every 16th sample.
 bk_status add_wsum_layer(bk::WsumArgs& w, int64_t& wg, const float* P, float* G, int64_t n, bool accum) {
     bk::WsumLayer& L = w.L[w.n++];
     L.P = P;
@@ -733,7 +735,8 @@ bk_status add_wsum_layer(bk::WsumArgs& w, int64_t& wg, const float* P, float* G,
     L.wg_begin = (uint32_t)wg;
     L.vec = (aligned16(P) && aligned16(G) && n % 4 == 0) ? 1u : 0u;
     L.accum = accum ? 1u : 0u;
-    wg += cdiv(n, bk::kWsumPerWG);
+    L.run = w.B >= bk::kWsumRuns && n <= 65536 ? (uint32_t)bk::kWsumRuns : 1u;
+    wg += cdiv(n, bk::kWsumPerWG / (int64_t)L.run);
     return BK_OK;
 }
 

@@ -153,6 +153,10 @@ struct GemmGeom {
 GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p);
 
 // ---- weighted sum of stored per-sample gradients -------------------------------
+// run == 1: a thread adds all samples of its 4 elements (1024 elements per
+// workgroup); run == kWsumRuns: 16 threads per group of 4 elements add every
+// 16th sample each, their sums added in order (64 elements per workgroup).
+constexpr int kWsumRuns = 16;
 struct WsumLayer {
     const float* P;     // [B, n]
     float* G;           // [n]
@@ -160,7 +164,7 @@ struct WsumLayer {
     uint32_t wg_begin;
     uint32_t vec;       // P, G 16-byte aligned and 4 | n
     uint32_t accum;     // add to G instead of writing it
-    uint32_t pad;
+    uint32_t run;       // 1 or kWsumRuns
 };
 constexpr int kMaxWsum = 100;
 struct WsumArgs {
@@ -168,7 +172,7 @@ struct WsumArgs {
     const float* C;
     WsumLayer L[kMaxWsum];
 };
-constexpr int kWsumPerWG = 1024;    // elements per workgroup
+constexpr int kWsumPerWG = 1024;    // elements per workgroup (divided by WsumLayer::run)
 
 // ---- convolution data preparation ------------------------------------------
 struct UnfoldShape {

@@ -105,3 +105,25 @@ def test_gemm_rows_of_any_alignment(bk, B, T, d, p, off):
     assert torch.equal(norm, bk.bk_inst_norm(a, g))
     assert _rel(norm.cpu().numpy(), oracle.linear_norm_sq(ah, gh)) <= NORM_GUARD
     assert _frob(P.cpu().numpy(), oracle.per_sample_grads(ah, gh)) <= GRAD_GUARD_EXACT
+
+
+# Short vectors over at least 16 samples: 16 interleaved runs of samples per
+# element (64 elements a workgroup); longer vectors or fewer samples: one run.
+@pytest.mark.parametrize("B,n,accum", [
+    (16, 64, False), (17, 63, False), (1000, 1000, True), (33, 1, False), (15, 64, True), (16, 65536, False),
+    (16, 65540, True)])
+def test_weighted_sum_runs(bk, B, n, accum):
+    gen = torch.Generator().manual_seed(B + n)
+    P = torch.randn(B, n, generator=gen)
+    C = torch.rand(B, generator=gen) + 0.05
+    G = bk.bk_weighted_sum(P.to(DEV), C.to(DEV))
+    # B float32 products and additions: at most (B + 1) roundings of 2^-24 each
+    assert _frob(G.cpu().numpy(), oracle.weighted_sum(P.numpy(), C.numpy())) <= (B + 1) * 2.0 ** -24
+    if accum and n <= 1024:           # as the bias of a layer that accumulates
+        x = torch.zeros(B, 1, n, dtype=BF, device=DEV)
+        Gb = torch.randn(n, generator=gen).to(DEV)
+        want = Gb + G
+        arr = bk.make_layers([{"x": x, "g": x, "G": torch.zeros(n, n, device=DEV), "bias": True, "Gb": Gb,
+                               "Pb": P.to(DEV), "accumulate": True}])
+        bk.bk_weighted_grads(arr, 1, C.to(DEV), bk.BK_BF16, B)
+        assert torch.equal(Gb, want)
