@@ -94,7 +94,8 @@ struct NormPlan {
     int64_t npart;      // partials per sample
     int var;            // kernel variant: ghost 0 = scalar, 1 = 16-byte loads,
                         // 2 = whole-sample kernel (bf16, 128 < T <= 256),
-                        // 3 = 256-row super blocks (bf16, T > 256);
+                        // 3 = 256-row super blocks (bf16, T > 256),
+                        // 4, 5 = few tokens (T <= 32, T <= 64; any alignment);
                         // instantiation: bk::GemmVariant
     int64_t tiles = 0;  // instantiation: output tiles per sample; ghost: super-block pairs
     int64_t ksplit = 1; // instantiation: K slices per tile (wide and narrow kernels);
@@ -141,6 +142,14 @@ int64_t narrow_grad_ksplit(int64_t tiles, int64_t nst) {
 int64_t dl_stages_per_sample(int64_t T) { return cdiv(T, bk::kDLStageRows); }
 bool dl_padding_ok(int64_t T) { return 8 * (cdiv(T, 16) * 16) <= 9 * T; }   // at most 1/8 padding
 
+// Whether a ghost layer's rows of a and g can be read 16 bytes at a time with
+// 32-bit buffer offsets (one sample's rows plus a super block of padding).
+bool ghost_rows16(const bk_layer& L, bk_dtype dt) {
+    const int64_t es = (int64_t)elem_bytes(dt);
+    return aligned16(L.x) && (L.d * es) % 16 == 0 && aligned16(L.g) && (L.p * es) % 16 == 0 &&
+           (L.T + bk::kSuper) * std::max(L.d, L.p) * es < ((int64_t)1 << 31);
+}
+
 void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
     const size_t es = elem_bytes(dt);
     if (np.path == Path::Affine) {
@@ -165,12 +174,13 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
     } else {
         const int64_t nsb = cdiv(L.T, bk::kSuper);
         np.npart = nsb * (nsb + 1) / 2;
-        const bool xv = np.path == Path::Embed || (aligned16(L.x) && (L.d * es) % 16 == 0);
-        // The 16-byte path addresses one sample's rows (plus a super block of
-        // padding) with 32-bit buffer offsets.
         const int64_t K = np.path == Path::Embed ? L.p : std::max(L.d, L.p);
-        const bool fits = (L.T + bk::kSuper) * K * (int64_t)es < ((int64_t)1 << 31);
-        np.var = (xv && fits && aligned16(L.g) && (L.p * es) % 16 == 0) ? 1 : 0;
+        if (np.path == Path::Embed) {   // rows of g only
+            const bool fits = (L.T + bk::kSuper) * K * (int64_t)es < ((int64_t)1 << 31);
+            np.var = (fits && aligned16(L.g) && (L.p * es) % 16 == 0) ? 1 : 0;
+        } else {
+            np.var = ghost_rows16(L, dt) ? 1 : 0;
+        }
         // bf16 16-byte rows with T > 128: the kernels over 256-row super
         // blocks (their 32-bit offsets reach 256 rows past T): 128 < T <= 256
         // streams every row once (one partial per sample); longer T has nsb
@@ -180,6 +190,11 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
             const int64_t nsb = cdiv(L.T, bk::kLongSuper);
             np.var = L.T <= 2 * bk::kSuper ? 2 : 3;
             np.npart = np.var == 2 ? 1 : nsb * nsb;
+        }
+        // Few tokens: whole samples packed into 32- or 64-row blocks.
+        if (np.path == Path::Ghost && L.T > 0 && L.T <= bk::kGhostSmallT) {
+            np.var = L.T <= 32 ? 4 : 5;
+            np.npart = 1;
         }
         // An embedding with rows of g in 16-byte multiples: the id join
         // (every row of g read once, no T x T work) instead of the masked
@@ -207,12 +222,14 @@ void finish_norm_plan(NormPlan& np, const bk_layer& L, int64_t B) {
         np.ksplit = inst_ksplit(B, np.tiles, L.T);
         if (np.ksplit > 1) np.npart = np.tiles * (np.tile_elems / bk::kSplitRedWG);
     }
-    np.nwg = np.path == Path::Inst || np.ksplit > 1 ? B * np.tiles * np.ksplit : B * np.npart;
+    const bool small = np.path == Path::Ghost && np.var >= 4;
+    np.nwg = small ? cdiv(B, bk::ghost_small_samples(L.T)) : np.path == Path::Inst || np.ksplit > 1 ? B * np.tiles * np.ksplit : B * np.npart;
     const bool affine = L.kind == BK_NORM_AFFINE || (L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS));
     // A ghost layer on the 16-byte path with one 128-row block per sample
     // sums its bias terms while its g passes through LDS for the Gram.
-    np.fused_bias = np.path == Path::Ghost && np.var == 1 && np.ksplit == 1 && L.T > 0 && L.T <= bk::kSuper &&
-                    L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS) && L.p > 0;
+    // So does the few-token kernel.
+    np.fused_bias = np.path == Path::Ghost && ((np.var == 1 && np.ksplit == 1) || small) && L.T > 0 &&
+                    L.T <= bk::kSuper && L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS) && L.p > 0;
     np.aff_chunks = affine && !np.fused_bias ? cdiv(L.p, bk::kAffineCols) : 0;
 }
 
@@ -227,11 +244,14 @@ size_t norm_ws_bytes(const NormPlan& np, int64_t B) {
 
 // Launch of a ghost-norm variant (NormPlan::var) and the super-block count
 // its descriptors carry.
+int32_t ghost_small(bool embed, int var) { return !embed && var >= 4 ? var - 3 : 0; }
 hipError_t launch_ghost_var(const bk::GhostArgs& a, int n_wg, bool bf16, bool embed, int var, hipStream_t s) {
     if (embed && var >= 2) return bk::launch_embed_join(a, n_wg, bf16, var == 2 ? 8 : 32, s);
-    return var >= 2 ? bk::launch_ghost_full(a, n_wg, var == 3, s) : bk::launch_ghost(a, n_wg, bf16, embed, var == 1, s);
+    return var == 2 || var == 3 ? bk::launch_ghost_full(a, n_wg, var == 3, s)
+                                : bk::launch_ghost(a, n_wg, bf16, embed, var == 1, s);
 }
 int32_t ghost_nsb(int64_t T, int var) {
+    if (var >= 4) return bk::ghost_small_samples(T);
     return (int32_t)cdiv(T, var == 2 ? bk::kFullSub : var == 3 ? bk::kLongSuper : bk::kSuper);
 }
 
@@ -312,9 +332,29 @@ void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_
     if (need <= kGhostSplitWs) plans.swap(split);
 }
 
+// The few-token kernel streams the whole rows of its samples in one
+// workgroup; layers of long rows (d + p of kSmallLongRow bytes or more) whose
+// launch gives fewer than kGhostSplitBelow workgroups go back to the pair
+// kernel, which split_small_ghost cuts into column slices.
+constexpr int64_t kSmallLongRow = 16384;
+void demote_long_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    int64_t wg = 0;
+    for (const NormPlan& np : plans) wg += np.path == Path::Ghost && np.var >= 4 ? np.nwg : 0;
+    if (wg == 0 || wg >= kGhostSplitBelow) return;
+    for (size_t l = 0; l < plans.size(); ++l) {
+        NormPlan& np = plans[l];
+        const bk_layer& L = layers[l];
+        const int64_t es = (int64_t)elem_bytes(dt);
+        if (np.path != Path::Ghost || np.var < 4 || (L.d + L.p) * es < kSmallLongRow) continue;
+        np.var = ghost_rows16(L, dt) ? 1 : 0;
+        finish_norm_plan(np, L, B);
+    }
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     demote_small_full(plans, layers, B);
+    demote_long_small(plans, layers, dt, B);
     split_small_ghost(plans, layers, dt, B);
 }
 
@@ -440,6 +480,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
         a.remap = 0;
         for (const Item* it : v) a.remap |= it->np.npart > 1 ? 1 : 0;
         a.tiles = tiles;
+        a.small = ghost_small(embed, var);
         if (!a.remap)
             std::stable_sort(v.begin(), v.end(), [&](const Item* x, const Item* y) {
                 auto cost = [&](const Item* it) {
@@ -517,7 +558,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
     // a group larger than one launch's descriptor table is cut into launches
     // of near-equal layer counts (no small last launch).
     for (int kind = 0; kind < 3; ++kind)
-        for (int var = 0; var < (kind == 2 ? bk::kGemmVariants : 4); ++var) {
+        for (int var = 0; var < (kind == 2 ? bk::kGemmVariants : 6); ++var) {
             const Path want = kind == 0 ? Path::Ghost : kind == 1 ? Path::Embed : Path::Inst;
             std::vector<const Item*> all;
             for (const Item& it : items)
@@ -962,6 +1003,7 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
         g.ka = (int32_t)np.ka;
         a.tiles = part + align_up(norm_part_floats(np, B) * sizeof(float)) / sizeof(float);
         a.n_red = np.ksplit > 1 ? (int32_t)(B * np.npart) : 0;
+        a.small = ghost_small(want == Path::Embed, np.var);
         e = launch_ghost_var(a, (int)np.nwg, dt == BK_BF16, want == Path::Embed, np.var, s);
     }
     if (e != hipSuccess) return hip_fail(e, "norm launch");

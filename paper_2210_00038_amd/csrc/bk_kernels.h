@@ -45,10 +45,14 @@ struct GhostArgs {
     int32_t n, B;
     int32_t remap;      // 1: workgroup order remapped per XCD (xcd_remap)
     int32_t n_red;      // workgroups of the column splits' reduction (0: no layer split)
+    int32_t small;      // few tokens: 32-row blocks (1: T <= 32, GhostLayer::nsb samples per
+                        // workgroup, 2: T <= 64) with one partial per sample; 0: super-block pairs
     float* part;        // partial sums, [layer][sample][pair]
     float* tiles;       // partial Grams of the column splits
     GhostLayer L[kMaxGhost];
 };
+constexpr int kGhostSmallT = 64;             // longest T of the few-token kernel
+inline int ghost_small_samples(int64_t T) { return T <= 16 ? (int)(32 / T) : 1; }
 constexpr int kGhostSplitTile = 128 * 128;   // floats of one partial Gram
 constexpr int kGhostSplitParts = 16;         // norm partials of a split pair: one per 32 x 32 sub-tile slot
 

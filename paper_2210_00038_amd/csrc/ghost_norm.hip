@@ -901,6 +901,271 @@ __global__ __launch_bounds__(256, 2) void ghost_norm_kernel(const GhostArgs args
         args.part[(size_t)L.part_off + (size_t)sample * npairs + (unit - sample * units)] = tot;
 }
 
+// ---------------------------------------------------------------------------
+// Ghost norms of few tokens (T <= 64), rows of any alignment.
+//
+// The 128-row pair kernel fills its LDS ring and its MFMA tiles with padding
+// here: at T = 1 one row of 128 is real.  Rows of consecutive samples are
+// contiguous, so a 256-thread workgroup takes S = 32 / T whole samples (one
+// for T > 16) as one block of 32 NSUB rows (NSUB = 2 for T > 32), streams the
+// columns of a and then of g through LDS in chunks of 512 / NSUB bytes per row
+// (16 KB), two register sets of loads in flight, and gives every wave a quarter
+// of each chunk's MFMA k steps: a wave holds both whole Grams (upper triangle
+// of 32 x 32 sub-tiles) of its share of the columns, and the four shares are
+// added through LDS at the end.  Off the S diagonal T x T blocks the products
+// of the packed Gram belong to no sample and are left out.  HBM-bound; several
+// workgroups fit a CU, so the barriers of one are covered by the others.
+// Measured against the pair kernel: classifier stack of three layers at T = 1,
+// 1024 samples 158 -> 18 us; 36 encoder layers at T = 37, 64 samples (600 MB)
+// 172 -> 106 us (5.7 TB/s); one 64 x 64 float32 layer at T = 16 12 -> 7 us.
+//
+// Bias sums (Pb): one sample per workgroup: row groups of 8 NSUB threads per
+// 16-byte column, added by shuffles and through LDS; several samples: each
+// thread adds the T rows of its (sample, column).  Fixed orders throughout.
+// ---------------------------------------------------------------------------
+template <typename T, int NSUB>
+__global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(const GhostArgs args) {
+    constexpr int EPV = Elem<T>::per16;
+    constexpr int CPR = 32 / NSUB;                // 16-byte columns per row and chunk
+    constexpr int EPC = CPR * EPV;                // elements per row and chunk
+    constexpr int ROWU4 = CPR + 1;                // padded LDS row (odd: rows on distinct bank groups)
+    constexpr int RPP = 256 / CPR;                // rows per pass of the workgroup's loads
+    constexpr int NP = 32 * NSUB / RPP;           // loads per thread and chunk
+    constexpr int NT = NSUB == 1 ? 1 : 3;         // upper-triangle sub-tiles
+    constexpr int KS = CPR / 2 / 4;               // MFMA k steps (32 bytes) per wave and chunk
+    static_assert(NP == 4, "16 KB chunks");
+    __shared__ __attribute__((aligned(16))) uint4 buf[32 * NSUB * ROWU4];
+    __shared__ float cbuf[4 * EPC];
+    __shared__ float bs[32];                      // squared bias sums of the workgroup's samples
+    __shared__ float red[4];
+
+    const int wg = blockIdx.x;
+    const int l = find_desc(args.n, (int64_t)wg, [&](int k) { return args.L[k].wg_begin; });
+    const GhostLayer& L = args.L[l];
+    const int nT = L.T, d = L.d, p = L.p, S = L.nsb;
+    const int s0 = (wg - L.wg_begin) * S, ns = min(S, args.B - s0);   // first sample, samples here
+    const int nr = ns * nT;                                           // rows here
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int c16 = tid % CPR, rq = tid / CPR;
+    const int nca = (d + EPC - 1) / EPC, nv = nca + (p + EPC - 1) / EPC;
+    const T* A = reinterpret_cast<const T*>(L.x) + (size_t)s0 * nT * d;
+    const T* G = reinterpret_cast<const T*>(L.g) + (size_t)s0 * nT * p;
+    float* Pb = L.Pb ? L.Pb + (size_t)s0 * p : nullptr;
+    const bool pb16 = p % 4 == 0 && (reinterpret_cast<uintptr_t>(Pb) & 15u) == 0;
+
+    // Chunk v (a's, then g's): this thread's pieces are column c16 of rows
+    // rq + RPP j.
+    auto fetch = [&](uint4 (&pr)[NP], int v) {
+        const bool isa = v < nca;
+        const T* X = isa ? A : G;
+        const int K = isa ? d : p, k = (isa ? v : v - nca) * EPC + c16 * EPV, kc = tail_col<T>(k, K);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            pr[j] = make_uint4(0u, 0u, 0u, 0u);
+            const int row = rq + RPP * j;
+            if (row < nr && v < nv) {
+                const T* q = X + (size_t)row * K;
+                pr[j] = K >= EPV ? load16_any<T>(q + kc) : load_short_row<T>(q, K, k);
+            }
+        }
+    };
+    auto unpack = [&](const uint4& v, float c[EPV]) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (sizeof(T) == 2) {
+                c[2 * e] += __uint_as_float(w[e] << 16);
+                c[2 * e + 1] += __uint_as_float(w[e] & 0xFFFF0000u);
+            } else {
+                c[e] += __uint_as_float(w[e]);
+            }
+        }
+    };
+    float bsq[4] = {0.f, 0.f, 0.f, 0.f};          // this thread's squared bias sums, of up to 4 samples
+    // Several samples: thread (c16, rq) sums samples rq, rq + RPP, ...
+    auto bias_direct = [&](int ch) {
+        const int k = ch * EPC + c16 * EPV;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int s = rq + RPP * m;
+            if (s >= ns || k >= p) continue;
+            float c[EPV];
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) c[e] = 0.f;
+            for (int t = 0; t < nT; ++t) unpack(buf[(s * nT + t) * ROWU4 + c16], c);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) bsq[m] += c[e] * c[e];      // columns past p are zeros
+            float* q = Pb + (size_t)s * p + k;
+#pragma unroll
+            for (int e = 0; e < EPV; e += 4) {
+                if (pb16 && k + e + 4 <= p) {
+                    *reinterpret_cast<float4*>(q + e) = make_float4(c[e], c[e + 1], c[e + 2], c[e + 3]);
+                } else {
+#pragma unroll
+                    for (int f = 0; f < 4; ++f)
+                        if (k + e + f < p) q[e + f] = c[e + f];
+                }
+            }
+        }
+    };
+    // One sample: row groups, then (bias_done, after a barrier) the waves.
+    auto bias_groups = [&]() {
+        float c[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) c[e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) unpack(buf[(rq + RPP * j) * ROWU4 + c16], c);
+#pragma unroll
+        for (int off = CPR; off < 64; off <<= 1)
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) c[e] += __shfl_xor(c[e], off, 64);
+        if (lane < CPR) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) cbuf[wave * EPC + lane * EPV + e] = c[e];
+        }
+    };
+    auto bias_done = [&](int ch) {
+        const int k = ch * EPC + tid;
+        if (tid < EPC && k < p) {
+            const float v = ((cbuf[tid] + cbuf[EPC + tid]) + cbuf[2 * EPC + tid]) + cbuf[3 * EPC + tid];
+            Pb[k] = v;
+            bsq[0] += v * v;
+        }
+    };
+    auto chunk = [&](uint4 (&pr)[NP], int v, f32x16_t* acc) {
+        const bool isa = v < nca;
+        const int K = isa ? d : p, ch = isa ? v : v - nca;
+        lds_barrier();
+        if (!isa && ch > 0 && Pb && S == 1) bias_done(ch - 1);
+        if (K >= EPV && (ch + 1) * EPC > K) {     // the rows' last chunk (uniform)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) pr[j] = shift_tail<T>(pr[j], ch * EPC + c16 * EPV, K);
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j) buf[(rq + RPP * j) * ROWU4 + c16] = pr[j];
+        lds_barrier();
+        fetch(pr, v + 2);
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            const int col = 2 * (KS * wave + j) + h;
+            const uint4 x0 = buf[r * ROWU4 + col];
+            Mfma<T>::step(acc[0], x0, x0);
+            if constexpr (NSUB == 2) {
+                const uint4 x1 = buf[(32 + r) * ROWU4 + col];
+                Mfma<T>::step(acc[1], x0, x1);
+                Mfma<T>::step(acc[2], x1, x1);
+            }
+        }
+        if (!isa && Pb) {
+            if (S == 1) bias_groups();
+            else bias_direct(ch);
+        }
+    };
+    f32x16_t acc[2][NT];                          // Gram(a), Gram(g)
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[o][t][i] = 0.f;
+    uint4 p0[NP], p1[NP];
+    fetch(p0, 0);
+    fetch(p1, 1);
+    // a's chunks, then g's; the register sets alternate by chunk.
+    int v = 0;
+    for (; v + 1 < nca; v += 2) {
+        chunk(p0, v, acc[0]);
+        chunk(p1, v + 1, acc[0]);
+    }
+    if (v < nca) {                                // odd nca: g starts on the second set
+        chunk(p0, v++, acc[0]);
+        for (; v + 1 < nv; v += 2) {
+            chunk(p1, v, acc[1]);
+            chunk(p0, v + 1, acc[1]);
+        }
+        if (v < nv) chunk(p1, v, acc[1]);
+    } else {
+        for (; v + 1 < nv; v += 2) {
+            chunk(p0, v, acc[1]);
+            chunk(p1, v + 1, acc[1]);
+        }
+        if (v < nv) chunk(p0, v, acc[1]);
+    }
+    lds_barrier();
+    if (Pb && S == 1 && nv > nca) bias_done(nv - nca - 1);
+
+    // Add the four waves' shares and multiply the Grams; with several samples
+    // (NSUB == 1) the products go to prod[row][col].
+    float* shr = reinterpret_cast<float*>(buf);   // [4 waves][16][64]
+    float part = bsq[0];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        float x[2][4];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) shr[(wave * 16 + i) * 64 + lane] = acc[o][t][i];
+            __syncthreads();
+            float4 sum = *reinterpret_cast<const float4*>(shr + 4 * tid);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const float4 q = *reinterpret_cast<const float4*>(shr + 1024 * w + 4 * tid);
+                sum.x += q.x;
+                sum.y += q.y;
+                sum.z += q.z;
+                sum.w += q.w;
+            }
+            x[o][0] = sum.x;
+            x[o][1] = sum.y;
+            x[o][2] = sum.z;
+            x[o][3] = sum.w;
+            __syncthreads();
+        }
+        const float w = t == 1 ? 2.f : 1.f;       // the off-diagonal sub-tile counts twice
+        if (S == 1) {
+            part += w * ((x[0][0] * x[1][0] + x[0][1] * x[1][1]) + (x[0][2] * x[1][2] + x[0][3] * x[1][3]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = tid >> 4, ln = (4 * tid + j) & 63;
+                shr[acc_row(i, ln) * 33 + (ln & 31)] = x[0][j] * x[1][j];
+            }
+        }
+    }
+    float* out = args.part + (size_t)L.part_off + s0;
+    if (S == 1) {
+        const float tot = block_sum_256(part, red);
+        if (tid == 0) *out = tot;
+        return;
+    }
+    // Squared bias sums of each sample: the threads of its columns, in order.
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        float b = bsq[m];
+#pragma unroll
+        for (int off = 1; off < CPR && off < 64; off <<= 1) b += __shfl_xor(b, off, 64);
+        const int s = rq + RPP * m;
+        if (c16 == 0 && s < 32) bs[s] = b;
+    }
+    __syncthreads();
+    // Column c of the products: rows of its own sample.
+    if (tid < 32) {
+        const int c = tid, q0 = c / nT * nT;
+        float sum = 0.f;
+        if (c < nr)
+            for (int t = 0; t < nT; ++t) sum += shr[(q0 + t) * 33 + c];
+        cbuf[c] = sum;
+    }
+    __syncthreads();
+    if (tid < ns) {
+        float sum = 0.f;
+        for (int t = 0; t < nT; ++t) sum += cbuf[tid * nT + t];
+        out[tid] = sum + bs[tid];
+    }
+}
+
 // Finishes the column splits: one workgroup per (layer, sample, pair, 32 x 32
 // sub-tile slot) adds the slot's slices of Gram(a) and of Gram(g), each in
 // slice order, and writes the weighted sum of their elementwise product as one
@@ -962,6 +1227,16 @@ hipError_t launch_ghost(const GhostArgs& args, int n_wg, bool bf16, bool embed, 
                         hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
     const dim3 grid(n_wg), block(256);
+    if (args.small) {
+        if (bf16) {
+            if (args.small == 1) hipLaunchKernelGGL((ghost_small_kernel<bf16_t, 1>), grid, block, 0, s, args);
+            else hipLaunchKernelGGL((ghost_small_kernel<bf16_t, 2>), grid, block, 0, s, args);
+        } else {
+            if (args.small == 1) hipLaunchKernelGGL((ghost_small_kernel<float, 1>), grid, block, 0, s, args);
+            else hipLaunchKernelGGL((ghost_small_kernel<float, 2>), grid, block, 0, s, args);
+        }
+        return hipGetLastError();
+    }
 #define BK_GHOST(T, E, V) hipLaunchKernelGGL((ghost_norm_kernel<T, E, V>), grid, block, 0, s, args)
     if (bf16) {
         if (embed) { if (vec) BK_GHOST(bf16_t, true, true); else BK_GHOST(bf16_t, true, false); }

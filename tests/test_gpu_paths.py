@@ -107,6 +107,48 @@ def test_gemm_rows_of_any_alignment(bk, B, T, d, p, off):
     assert _frob(P.cpu().numpy(), oracle.per_sample_grads(ah, gh)) <= GRAD_GUARD_EXACT
 
 
+# Few tokens: 32 / T whole samples to a 32-row block up to T = 16, one sample
+# to a 32- or 64-row block up to T = 64; the last block partly filled, rows of
+# every alignment, one chunk of columns and several, a bias in the same pass.
+@pytest.mark.parametrize("dtype", [BF, F32])
+@pytest.mark.parametrize("B,T,d,p,off", [
+    (1, 1, 64, 40, 0),         # one sample, one token
+    (70, 1, 768, 1000, 0),     # 32 samples a block, six in the last one
+    (33, 1, 591, 675, 0),      # odd rows
+    (5, 2, 7, 1300, 0),        # rows shorter than 16 bytes beside long ones
+    (9, 5, 300, 260, 1),       # 6 samples a block (30 rows), misaligned base
+    (7, 16, 256, 264, 0),      # two samples a block
+    (3, 17, 520, 72, 0),       # one sample a block from here on
+    (4, 32, 100, 257, 0),
+    (3, 33, 264, 129, 0),      # two 32-row blocks, one row in the second
+    (2, 64, 1032, 1000, 0),
+    (2, 50, 4000, 5000, 0),    # long rows, few workgroups: column slices of the pair kernel
+])
+def test_ghost_few_tokens(bk, B, T, d, p, off, dtype):
+    gen = torch.Generator().manual_seed(B * 100 + T + d)
+    a, ah = _draw(B, T, d, dtype, gen, 1.0, off)
+    g, gh = _draw(B, T, p, dtype, gen, 1e-2, off)
+    if B > 1:
+        a[B - 1].zero_()
+        ah[B - 1] = 0
+    ref = oracle.linear_norm_sq(ah, gh)
+    out = bk.bk_ghost_norm(a, g)
+    assert torch.equal(out, bk.bk_ghost_norm(a, g))
+    out = out.cpu().numpy()
+    n = max(1, B - 1)
+    assert _rel(out[:n], ref[:n]) <= _norm_bound(dtype) and (B == 1 or out[B - 1] == 0.0)
+    if not oracle.use_ghost(T, d, p):
+        return
+    Pb, norm = torch.full((B, p), float("nan"), device=DEV), torch.empty(2, B, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "bias": True, "Pb": Pb}, {"x": a, "g": g}])
+    bk.bk_layer_norms(arr, 2, bk.BK_BF16 if dtype == BF else bk.BK_F32, B, norm)
+    sb = oracle.bias_sums(gh)
+    got = norm.cpu().numpy()
+    assert _frob(Pb.cpu().numpy(), sb) <= 1e-6
+    assert _rel(got[0], ref + (sb ** 2).sum(1)) <= _norm_bound(dtype)
+    assert _rel(got[1][:n], ref[:n]) <= _norm_bound(dtype)
+
+
 # Short vectors over at least 16 samples: 16 interleaved runs of samples per
 # element (64 elements a workgroup); longer vectors or fewer samples: one run.
 @pytest.mark.parametrize("B,n,accum", [
