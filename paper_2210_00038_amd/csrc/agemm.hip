@@ -396,10 +396,15 @@ __device__ __forceinline__ void store_partial_tile(float* P, const f32x16_t (&ac
         for (int y = 0; y < 2; ++y) put_acc_x4(P, TN, r0 + 32 * x, TM, c0 + 32 * y, TN, lane, acc[x][y], scale, false);
 }
 
-// Two bf16 in one word, each multiplied by c, rounded to nearest even.
-__device__ __forceinline__ uint32_t scale_bf16x2(uint32_t w, float c) {
-    const f32x2_t f = {__uint_as_float(w << 16) * c, __uint_as_float(w & 0xFFFF0000u) * c};
+// Two bf16 in one word, multiplied by c0 (low) and c1, rounded to nearest even.
+__device__ __forceinline__ uint32_t scale_bf16x2(uint32_t w, float c0, float c1) {
+    const f32x2_t f = {__uint_as_float(w << 16) * c0, __uint_as_float(w & 0xFFFF0000u) * c1};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+}
+__device__ __forceinline__ uint32_t scale_bf16x2(uint32_t w, float c) { return scale_bf16x2(w, c, c); }
+// Four bf16 times four weights.
+__device__ __forceinline__ uint2 scale_half(const uint2& v, const float4& w) {
+    return make_uint2(scale_bf16x2(v.x, w.x, w.y), scale_bf16x2(v.y, w.z, w.w));
 }
 
 
@@ -809,228 +814,7 @@ __global__ __launch_bounds__(256, 2) void anarrow_kernel(const GemmArgs args, in
     }
 }
 
-// ---------------------------------------------------------------------------
-// Clipped-gradient kernel for 16-byte aligned bf16 rows: one 256 x 256 output
-// tile per 512-thread workgroup, one workgroup per CU.  Compared with two
-// 256 x 128 workgroups on a CU, a stage moves a third fewer bytes from L2 per
-// MFMA.  Waves (wm, wn), wm in 0..1, wn in 0..3, own 128 x 64 sub-tiles (4 x 2
-// MFMA 32x32x16 accumulators), read with the same LDS transpose reads.
-//
-// Two LDS buffers: while the waves multiply stage s out of one buffer, the
-// registers holding stage s + 1 (loaded during stage s - 1) are written to the
-// other one, and the loads of stage s + 2 are issued.  One barrier per stage.
-// The instruction order inside a stage is fixed by hand (sched_barrier
-// fences): left to itself the compiler clusters the 48 transpose reads, the
-// LDS stores and the global loads into blocks, and the in-order issue of each
-// wave then leaves the MFMA pipe idle.  Only launched for T >= 64.
-// ---------------------------------------------------------------------------
 constexpr int kGM = kGradM, kGN = kGradN;
-constexpr int kSG = 256 * 2 + 64;                // bytes per staged k-row (both operands)
-constexpr int kGOp = kBK * kSG;                  // one operand of one stage
-constexpr int kGStage = 2 * kGOp;
-
-__global__ __launch_bounds__(512, 1) void agrad_bf16_kernel(const GemmArgs args, int n_remap) {
-    __shared__ __attribute__((aligned(16))) char lds[2 * kGStage];
-
-    // As agrad_dl_kernel: the first n_remap workgroups XCD-remapped, the
-    // tail of K slices in launch order.
-    const int wg = (int)blockIdx.x < n_remap ? xcd_remap(blockIdx.x, n_remap) : (int)blockIdx.x;
-    const int l = find_desc(args.n, (int64_t)wg, [&](int k) { return args.L[k].wg_begin; });
-    const GemmLayer& L = args.L[l];
-    const int nT = L.T, d = L.d, p = L.p, tn = L.tn;
-    const int local = wg - L.wg_begin, sf = L.split_from;
-    const int ks = local < sf ? 1 : max(L.ksplit, 1);
-    const int rel = local < sf ? 0 : (local - sf) / ks;              // split tile, from split_from
-    const int tile = local < sf ? local : sf + rel;
-    const int slice = local < sf ? 0 : (local - sf) - rel * ks;
-    const int mt = tile / tn, nt = tile - mt * tn;
-    const int m0 = mt * kGM, n0 = nt * kGN;
-
-    // The host guarantees (nrows + 3 kBK) * row bytes < 2^31 for this kernel
-    // (its registers leave no room to rebase the rows stage by stage).
-    const uint32_t nrows = (uint32_t)args.B * (uint32_t)nT;
-    const uint32_t rowA = (uint32_t)d * 2u, rowB = (uint32_t)p * 2u;
-    const __amdgpu_buffer_rsrc_t rA = make_rsrc(L.a, nrows * rowA);
-    const __amdgpu_buffer_rsrc_t rB = make_rsrc(L.g, nrows * rowB);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 2, wn = wave & 3;
-    // Staging: each operand tile is 64 rows x 32 chunks of 16 B; thread t
-    // moves chunk t % 32 of rows t / 32 + 16 j, j = 0..3.  Rows past the last
-    // one fall outside the buffer resource and load as zeros, and so do
-    // chunks past the last column (out-of-range offset).
-    const int cc = (tid & 31) * 8, kr = tid >> 5;
-    const uint32_t offA = (m0 + cc < d) ? (uint32_t)kr * rowA + (uint32_t)(m0 + cc) * 2u : kOut;
-    const uint32_t offB = (n0 + cc < p) ? (uint32_t)kr * rowB + (uint32_t)(n0 + cc) * 2u : kOut;
-
-    f32x16_t acc[4][2];
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.f;
-
-    // Register staging of one stage (rows [k0, k0 + 64)): chunk j of a (va)
-    // and of g (vb) for rows kr + 16 j.  Rows at or past nrows load zeros, so
-    // the stages after the last one need no branch.  The host launches this
-    // kernel only for T >= 64, so the 64 rows span at most two samples: the
-    // first `split` rows belong to sample fq, the rest to fq + 1, with clip
-    // weights c0 and c1 (loaded through the vector memory path: a scalar load
-    // would make the waits for it drain the LDS reads as well).
-    const __amdgpu_buffer_rsrc_t rC = make_rsrc(args.C, (uint32_t)args.B * 4u);
-    uint4 va[4], vb[4];
-    float c0 = 0.f, c1 = 0.f;
-    uint32_t split = 0;
-    // This workgroup's stages (K slice `slice` of `ks`).
-    const uint32_t nst_all = (nrows + kBK - 1) / kBK;
-    const uint32_t st_begin = (uint32_t)((uint64_t)slice * nst_all / (uint32_t)ks);
-    const uint32_t st_end = (uint32_t)((uint64_t)(slice + 1) * nst_all / (uint32_t)ks);
-    // next fetch: first row, its sample, row in sample
-    uint32_t fk0 = st_begin * kBK, fq = fk0 / (uint32_t)nT, frem = fk0 - fq * (uint32_t)nT;
-    auto load_a = [&](int j) { va[j] = buffer_load16(rA, offA == kOut ? kOut : offA + (fk0 + 16u * j) * rowA); };
-    auto load_b = [&](int j) { vb[j] = buffer_load16(rB, offB == kOut ? kOut : offB + (fk0 + 16u * j) * rowB); };
-    auto load_c = [&]() {
-        // Samples past B read zeros (their rows are zero too).
-        c0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rC, fq * 4u, 0, 0));
-        c1 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rC, fq * 4u + 4u, 0, 0));
-        split = (uint32_t)nT - frem;
-        fk0 += kBK;
-        frem += kBK;
-        if (frem >= (uint32_t)nT) {
-            frem -= (uint32_t)nT;
-            ++fq;
-        }
-    };
-    auto store_a = [&](char* A, int j) {
-        *reinterpret_cast<uint4*>(A + (kr + 16 * j) * kSG + cc * 2) = va[j];
-    };
-    auto store_b = [&](char* Bt, int j) {
-        const float cw = ((uint32_t)(kr + 16 * j) < split) ? c0 : c1;
-        const uint4 v = vb[j];
-        *reinterpret_cast<uint4*>(Bt + (kr + 16 * j) * kSG + cc * 2) =
-            make_uint4(scale_bf16x2(v.x, cw), scale_bf16x2(v.y, cw), scale_bf16x2(v.z, cw),
-                       scale_bf16x2(v.w, cw));
-    };
-
-    // One stage out of buffer BUF (a compile-time constant).  The issue order
-    // is laid out by hand, one slot per MFMA, each slot fenced off from the
-    // next: slot i of step kk issues MFMA (x, y) = (i / 2, i % 2) of step kk
-    // and its share of the 12 transpose reads of the next step: an even slot
-    // one half of a g fragment (double-buffered), an odd slot both halves of
-    // a fragment x, whose two MFMAs of this step have then been issued (one
-    // buffer).  In step 0, slot i also writes register chunk i of stage
-    // st + 1 to the other LDS buffer and reloads that register with stage
-    // st + 2.
-    //
-    // The barrier sits between steps 2 and 3: the reads of step 3 were issued
-    // (and are waited for) before it, so every read of this buffer is done
-    // before the next stage overwrites it, and the stage st + 1 data written
-    // in step 0 is complete after it, so step 3 reads the first fragments of
-    // stage st + 1 and the next stage starts with MFMAs.  (After the last
-    // stage the writes and reads go to a buffer nobody uses.)
-    uint2 fa[4][2], fb[2][2][2];
-    auto read_a = [&](const char* A, int kk, int x, int h) {
-        fa[x][h] = frag_tr_half<kSG>(A, 16 * kk, 128 * wm + 32 * x, lane, h);
-    };
-    auto read_b = [&](const char* Bt, int kk, int y, int h) {
-        fb[kk & 1][y][h] = frag_tr_half<kSG>(Bt, 16 * kk, 64 * wn + 32 * y, lane, h);
-    };
-    auto stage = [&](auto buf_c) {
-        constexpr int BUF = decltype(buf_c)::value;
-        const char* A = lds + BUF * kGStage;
-        const char* Bt = A + kGOp;
-        char* An = lds + (BUF ^ 1) * kGStage;
-        char* Bn = An + kGOp;
-#pragma unroll
-        for (int kk = 0; kk < kBK / 16; ++kk) {
-            const int cur = kk & 1;
-            // Source of the reads in this step: step kk + 1 of this stage, or
-            // step 0 of the next one.
-            const char* RA = kk + 1 < kBK / 16 ? A : An;
-            const char* RB = kk + 1 < kBK / 16 ? Bt : Bn;
-            const int rk = (kk + 1) & 3;
-            if (kk == kBK / 16 - 1) lds_barrier();
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int x = i >> 1, y = i & 1;
-                const uint2 al = fa[x][0], ah = fa[x][1], bl = fb[cur][y][0], bh = fb[cur][y][1];
-                Mfma<bf16_t>::step(acc[x][y], make_uint4(al.x, al.y, ah.x, ah.y), make_uint4(bl.x, bl.y, bh.x, bh.y));
-                if (i & 1) {
-                    read_a(RA, rk, x, 0);
-                    read_a(RA, rk, x, 1);
-                } else {
-                    read_b(RB, rk, i >> 2, (i >> 1) & 1);
-                }
-                if (kk == 0) {
-                    if (i < 4) {
-                        store_a(An, i);
-                        load_a(i);
-                    } else {
-                        store_b(Bn, i - 4);
-                        load_b(i - 4);
-                        if (i == 7) load_c();
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-
-    const uint32_t nst = st_end - st_begin;
-    if (nst > 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            load_a(j);
-            load_b(j);
-        }
-        load_c();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            store_a(lds, j);
-            store_b(lds + kGOp, j);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            load_a(j);
-            load_b(j);
-        }
-        load_c();
-    }
-    lds_barrier();
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        read_a(lds, 0, x, 0);
-        read_a(lds, 0, x, 1);
-    }
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-        read_b(lds + kGOp, 0, y, 0);
-        read_b(lds + kGOp, 0, y, 1);
-    }
-    uint32_t st = 0;
-    for (; st + 1 < nst; st += 2) {
-        stage(std::integral_constant<int, 0>{});
-        stage(std::integral_constant<int, 1>{});
-    }
-    if (st < nst) stage(std::integral_constant<int, 0>{});
-
-    if (ks > 1) {
-        store_partial_tile<kGM, kGN>(args.tiles + L.ptile_off + ((size_t)rel * ks + slice) * (kGM * kGN),
-                                     acc, 128 * wm, 64 * wn, lane, 1.f);
-        return;
-    }
-    float* G = L.G;
-    const bool add = L.accum != 0;
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int n = n0 + 64 * wn + 32 * y + (lane & 31);
-            if (n < p) put_col16(G, (size_t)p, 1, m0 + 128 * wm + 32 * x, d, n, lane, acc[x][y], 1.f, add);
-        }
-}
-
 constexpr int kDRow = 512;                       // bytes per staged k-row
 constexpr int kDKS = kDLStageRows;               // k rows per stage
 constexpr int kDNB = kDLBuffers;                 // LDS stage buffers
@@ -1059,11 +843,12 @@ struct StagePos {
 };
 
 // ---------------------------------------------------------------------------
-// Clipped-gradient kernel for bf16 rows when the stage height KS (32) divides
-// T: 256 x 256 tiles on 512 threads, waves of 128 x 64 as in
-// agrad_bf16_kernel, but both operand tiles go from HBM straight into LDS
-// (LDS DMA: no staging registers, no LDS store instructions) and the clip
-// weights are applied to the accumulators instead of to g.  A stage then lies
+// Clipped-gradient kernel for 16-byte aligned bf16 rows: one 256 x 256 output
+// tile per 512-thread workgroup, one workgroup per CU; waves (wm, wn), wm in
+// 0..1, wn in 0..3, own 128 x 64 sub-tiles (4 x 2 MFMA 32x32x16 accumulators).
+// Both operand tiles go from HBM straight into LDS (LDS DMA: no staging
+// registers, no LDS store instructions).  kDLGrad: every sample starts a
+// stage, and the clip weights are applied to the accumulators instead of to g.  A stage then lies
 // inside one sample.  The accumulators hold S / c, S being the weighted sum
 // so far and c the weight of the last sample whose weight is nonzero:
 // entering sample j with C_j != 0 multiplies them by c / C_j, and the
@@ -1090,6 +875,17 @@ struct StagePos {
 // passed; a stage's buffer is complete once every wave has waited for its
 // DMA of it before the barrier that precedes the first reads of it.
 //
+// kDLFlat (GemmVariant::Grad; T < 64, or padding every sample to 16-row steps
+// would add over 1/8): the stages run over the flat rows of the batch and the
+// weights go onto g's fragments, rounded to bf16 (C_i g), as each wave reads
+// them; the 32 weights of a stage's rows sit in a small LDS ring, written two
+// stages ahead by one wave.  Bound by the memory phase, which the 80 scaling
+// instructions per stage make longer than the MFMA phase (1.2 us a stage
+// against 0.9 with rare rescales).  Against the register-staged kernels it
+// replaced: 36 encoder layers at T = 37, 64 samples (201 GFLOP) 295-310 us (256
+// x 128 tiles, two workgroups per CU) -> 265 us; at T = 70, 32 samples about
+// 3% faster (256 x 256 tiles).
+//
 // INST (per-sample gradient instantiation, App. B.4.1): workgroup = (sample,
 // tile), its stages those of the one sample, no weights (every other stage
 // loads zeros); the epilogue sums the squares of the tile's d x p entries
@@ -1100,11 +896,14 @@ constexpr int kDOp = kDKS * kDRow;               // one operand of one stage
 constexpr int kDStage = 2 * kDOp;
 constexpr int kDKK = kDKS / 16;                  // 16-row MFMA steps per stage
 constexpr int kDPW = kDKS / 8;                   // DMA instructions per wave per stage
+constexpr int kDLGrad = 0, kDLInst = 1, kDLFlat = 2;
 
-template <bool INST>
+template <int MODE>
 __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, int n_remap) {
+    constexpr bool INST = MODE == kDLInst, FLAT = MODE == kDLFlat;
     __shared__ __attribute__((aligned(16))) char lds[kDNB * kDStage];
     __shared__ float ctab[INST ? 8 : kDMaxB + 1];   // INST: the epilogue's wave sums
+    __shared__ __attribute__((aligned(16))) float wtab[FLAT ? kDNB * kDKS : 4];   // weights of a stage's rows
 
     // The first n_remap workgroups in contiguous runs per XCD; the tail (the
     // K slices of the last round's tiles) in launch order, so that it is
@@ -1130,6 +929,7 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
     // rows are addressed stage by stage.
     const int B = args.B;
     const uint32_t rowA = (uint32_t)d * 2u, rowB = (uint32_t)p * 2u;
+    const uint32_t nrows = (uint32_t)B * (uint32_t)nT;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1154,9 +954,10 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
     // DMA piece i (i < NI: a, else g) of stage `pos` into the buffer at
     // `buf`; `zero` (the stage's sample has weight 0, or lies past the batch)
     // loads zeros.
+    // FLAT: the stage's rows are rows kDKS pos.in .. of the whole batch.
     auto dma = [&](char* buf, const StagePos& pos, bool zero, int i) {
-        const uint32_t s0 = pos.smp * (uint32_t)nT;
-        const uint32_t k0 = s0 + pos.in * kDKS, kend = s0 + (uint32_t)nT;
+        const uint32_t s0 = FLAT ? 0u : pos.smp * (uint32_t)nT;
+        const uint32_t k0 = s0 + pos.in * kDKS, kend = FLAT ? nrows : s0 + (uint32_t)nT;
         if (i < NI) {
             const uint32_t o = (offA[i] == kOut || zero) ? kOut : offA[i];
             dma16_asm(rows_raw_rsrc(L.a, rowA, k0, kend, kDKS), o, buf + (8 * i + wave) * 1024);
@@ -1175,11 +976,12 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.f;
 
-    const uint32_t spt = ((uint32_t)nT + kDKS - 1) / kDKS;   // stages per sample
-    const uint32_t nst_all = (uint32_t)B * spt;
+    // Stages per sample (FLAT: of the whole batch, one run of rows).
+    const uint32_t spt = ((FLAT ? nrows : (uint32_t)nT) + kDKS - 1) / kDKS;
+    const uint32_t nst_all = FLAT ? spt : (uint32_t)B * spt;
     // The last stage of a sample holds at most 16 rows (16-row MFMA steps,
     // the second one all zeros): its second step is skipped.
-    const bool short_last = (uint32_t)nT - (spt - 1) * kDKS <= 16u;
+    const bool short_last = (FLAT ? nrows : (uint32_t)nT) - (spt - 1) * kDKS <= 16u;
     // This workgroup's stages (K slice `slice` of `ks`; INST: its sample's).
     const uint32_t st_begin = INST ? (uint32_t)sample * spt : (uint32_t)((uint64_t)slice * nst_all / (uint32_t)ks);
     const uint32_t st_end = INST ? (uint32_t)(sample + 1) * spt
@@ -1188,23 +990,34 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
     // 0 elsewhere).
     auto cw_of = [&](const StagePos& pos) {
         if constexpr (INST) return pos.smp == (uint32_t)sample ? 1.f : 0.f;
+        else if constexpr (FLAT) return 1.f;
         else return ctab[min(pos.smp, (uint32_t)B)];
+    };
+    // FLAT: the clip weight of row r of stage st, into the stage's slot.
+    auto put_weight = [&](uint32_t st, uint32_t r) {
+        const uint32_t row = st * kDKS + r;
+        wtab[(st % kDNB) * kDKS + r] = ctab[row < nrows ? row / (uint32_t)nT : (uint32_t)B];
     };
 
     float c_last = 0.f;   // weight of the last sample with a nonzero weight
     static_assert(kDNB == 4 && kDKK == 2 && kDPW == 4, "ping-pong ring");
     const bool late = wave >= 4;
     uint2 fa[kDKK][4][2], fb[kDKK][2][2];
-    StagePos pos0{st_begin / spt, st_begin % spt};        // stage st
+    StagePos pos0{FLAT ? 0u : st_begin / spt, FLAT ? st_begin : st_begin % spt};        // stage st
     StagePos posD = pos0;                                  // stage st + 3
     __syncthreads();      // clip weights in LDS
+    if constexpr (FLAT) {
+        if (tid < 2 * kDKS) put_weight(st_begin + tid / kDKS, tid % kDKS);
+        c_last = 1.f;
+    }
     // Prologue: stages st_begin .. st_begin + 2 into buffers 0 .. 2.
 #pragma unroll
     for (int b = 0; b < kDNB - 1; ++b) {
         const bool z = cw_of(posD) == 0.f;
 #pragma unroll
         for (int i = 0; i < kDPW; ++i) dma(lds + b * kDStage, posD, z, i);
-        posD.next(spt);
+        if constexpr (FLAT) ++posD.in;
+        else posD.next(spt);
     }
     wait_vmcnt<(kDNB - 2) * kDPW>();
     lds_barrier();
@@ -1221,19 +1034,52 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
         // Memory phase: the stage's fragments, then (entering a sample, or at
         // the slice's first stage) the accumulators times c_last / c (c != 0).
         const bool two = !(short_last && pos0.in + 1u == spt);   // second step
+        if constexpr (FLAT) {
+            // g's fragments and their rows' weights: a lane's four k values of
+            // half h are rows 16 kk + 8 (lane / 32) + 4 h + 0 .. 3 of the
+            // stage.  They are scaled (and rounded to bf16) while a's
+            // fragments are on their way; between the MFMAs of the first step
+            // the second step's scaling was 20% slower.
+            const float* wrow = wtab + (st % kDNB) * kDKS + 8 * (lane >> 5);
+            float4 w[kDKK][2];
 #pragma unroll
-        for (int kk = 0; kk < kDKK; ++kk) {
-            if (kk > 0 && !two) break;
+            for (int kk = 0; kk < kDKK; ++kk)
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+                for (int h = 0; h < 2; ++h) w[kk][h] = *reinterpret_cast<const float4*>(wrow + 16 * kk + 4 * h);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) fa[kk][x][h] = frag_dl_half(A, 16 * kk, 128 * wm + 32 * x, lane, h);
+            for (int kk = 0; kk < kDKK; ++kk)
 #pragma unroll
-            for (int y = 0; y < 2; ++y)
+                for (int y = 0; y < 2; ++y)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) fb[kk][y][h] = frag_dl_half(Bt, 16 * kk, 64 * wn + 32 * y, lane, h);
+                    for (int h = 0; h < 2; ++h) fb[kk][y][h] = frag_dl_half(Bt, 16 * kk, 64 * wn + 32 * y, lane, h);
+#pragma unroll
+            for (int kk = 0; kk < kDKK; ++kk)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) fa[kk][x][h] = frag_dl_half(A, 16 * kk, 128 * wm + 32 * x, lane, h);
+#pragma unroll
+            for (int kk = 0; kk < kDKK; ++kk)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) fb[kk][y][h] = scale_half(fb[kk][y][h], w[kk][h]);
+            if (wave == (int)(st & 7u) && lane < kDKS) put_weight(st + 2, lane);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < kDKK; ++kk) {
+                if (kk > 0 && !two) break;
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) fa[kk][x][h] = frag_dl_half(A, 16 * kk, 128 * wm + 32 * x, lane, h);
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) fb[kk][y][h] = frag_dl_half(Bt, 16 * kk, 64 * wn + 32 * y, lane, h);
+            }
         }
-        if (!INST && (pos0.in == 0u || st == st_begin)) {
+        if (!INST && !FLAT && (pos0.in == 0u || st == st_begin)) {
             const float c = cw_of(pos0);
             const bool nz = c != 0.f;
             const float r = nz ? c_last / c : 1.f;
@@ -1267,8 +1113,13 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        pos0.next(spt);
-        posD.next(spt);
+        if constexpr (FLAT) {
+            ++pos0.in;
+            ++posD.in;
+        } else {
+            pos0.next(spt);
+            posD.next(spt);
+        }
     };
     const uint32_t nst = st_end;
     uint32_t st = st_begin;
@@ -1440,16 +1291,12 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
     if (n_wg <= 0) return hipSuccess;
     const dim3 grid(n_wg), block(256);
     const bool vec = v != GemmVariant::Scalar;
-    if (v == GemmVariant::Grad) {
-        if (inst_norm) return hipErrorInvalidValue;
+    if (v == GemmVariant::Grad || v == GemmVariant::GradDL) {
+        if (inst_norm && v == GemmVariant::Grad) return hipErrorInvalidValue;
         const int nr = n_remap > 0 && n_remap < n_wg ? n_remap : n_wg;
-        hipLaunchKernelGGL(agrad_bf16_kernel, grid, dim3(512), 0, s, args, nr);
-        return hipGetLastError();
-    }
-    if (v == GemmVariant::GradDL) {
-        const int nr = n_remap > 0 && n_remap < n_wg ? n_remap : n_wg;
-        if (inst_norm) hipLaunchKernelGGL(agrad_dl_kernel<true>, grid, dim3(512), 0, s, args, nr);
-        else hipLaunchKernelGGL(agrad_dl_kernel<false>, grid, dim3(512), 0, s, args, nr);
+        if (v == GemmVariant::Grad) hipLaunchKernelGGL(agrad_dl_kernel<kDLFlat>, grid, dim3(512), 0, s, args, nr);
+        else if (inst_norm) hipLaunchKernelGGL(agrad_dl_kernel<kDLInst>, grid, dim3(512), 0, s, args, nr);
+        else hipLaunchKernelGGL(agrad_dl_kernel<kDLGrad>, grid, dim3(512), 0, s, args, nr);
         return hipGetLastError();
     }
     if (v == GemmVariant::Wide) {

@@ -297,16 +297,16 @@ void demote_small_full(std::vector<NormPlan>& plans, const bk_layer* layers, int
 // The super-block pair kernel gives one workgroup per (layer, sample, pair),
 // each streaming its whole rows: with few samples most CUs idle (a head of
 // 50257 columns and 8 samples ran on 8 of 256 CUs).  When all such layers of a
-// call give fewer than kGhostSplitBelow workgroups (at 192 a split made a
-// float32 stack 1% slower, at 64 to 100 whole steps came out 3% to 18% faster),
-// their rows are cut into
+// call give fewer than kGhostSplitBelow workgroups, their rows are cut into
 // column slices towards kGhostSplitTo workgroups, each slice at least
 // kGhostSplitChunks 128-byte chunks wide (its partial Gram, 48 KB written and
-// read back through the caches, against 256 KB of rows streamed).  The
-// partial Grams are only taken while the norms' workspace stays within
+// read back through the caches, against 256 KB of rows streamed), if that
+// gives at least kGhostSplitMin of them: the second kernel takes 15 us or more,
+// so that two slices for each of 96 workgroups lost (27 us against 21 + 18).
+// The partial Grams are only taken while the norms' workspace stays within
 // kGhostSplitWs, so that a call that fits the allocation-free scratch without
 // them still does.
-constexpr int64_t kGhostSplitBelow = 128, kGhostSplitTo = 512, kGhostSplitChunks = 16, kGhostSplitMax = 64;
+constexpr int64_t kGhostSplitBelow = 64, kGhostSplitTo = 512, kGhostSplitMin = 4, kGhostSplitChunks = 16, kGhostSplitMax = 64;
 constexpr size_t kGhostSplitWs = (size_t)32 << 20;
 void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     auto small = [](const NormPlan& np) { return np.path == Path::Ghost && np.var <= 1 && np.nwg > 0; };
@@ -321,7 +321,7 @@ void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_
         if (small(np)) {
             const int64_t ca = cdiv(layers[l].d, epc), cg = cdiv(layers[l].p, epc);
             const int64_t ks = std::min({kGhostSplitTo / wg, (ca + cg) / kGhostSplitChunks, kGhostSplitMax});
-            if (ks >= 2 && ca > 0 && cg > 0) {
+            if (ks >= kGhostSplitMin && ca > 0 && cg > 0) {
                 np.ksplit = ks;
                 np.ka = std::clamp<int64_t>((2 * ks * ca + ca + cg) / (2 * (ca + cg)), 1, ks - 1);
                 finish_norm_plan(np, layers[l], B);
@@ -335,17 +335,26 @@ void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_
 // The few-token kernel streams the whole rows of its samples in one
 // workgroup; layers of long rows (d + p of kSmallLongRow bytes or more) whose
 // launch gives fewer than kGhostSplitBelow workgroups go back to the pair
-// kernel, which split_small_ghost cuts into column slices.
-constexpr int64_t kSmallLongRow = 16384;
-void demote_long_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
-    int64_t wg = 0;
-    for (const NormPlan& np : plans) wg += np.path == Path::Ghost && np.var >= 4 ? np.nwg : 0;
-    if (wg == 0 || wg >= kGhostSplitBelow) return;
+// kernel, which split_small_ghost cuts into column slices.  So do all of them
+// when they would not fill the chip in a launch of their own next to one of
+// the pair kernel (kSmallMixedBelow workgroups, at most kSmallMixedB samples:
+// the late layers and the classifier of ResNet-18 with 16 samples, 53 us in one
+// launch against 29 + 33 + 12 us in three).
+constexpr int64_t kSmallLongRow = 16384, kSmallMixedBelow = 256, kSmallMixedB = 64;
+void demote_few_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    int64_t wg = 0, pair = 0;
+    for (const NormPlan& np : plans) {
+        if (np.path != Path::Ghost) continue;
+        if (np.var >= 4) wg += np.nwg;
+        else if (np.var <= 1) pair += np.nwg;
+    }
+    const bool mixed = pair > 0 && wg < kSmallMixedBelow && B <= kSmallMixedB;
+    if (wg == 0 || (wg >= kGhostSplitBelow && !mixed)) return;
     for (size_t l = 0; l < plans.size(); ++l) {
         NormPlan& np = plans[l];
         const bk_layer& L = layers[l];
         const int64_t es = (int64_t)elem_bytes(dt);
-        if (np.path != Path::Ghost || np.var < 4 || (L.d + L.p) * es < kSmallLongRow) continue;
+        if (np.path != Path::Ghost || np.var < 4 || (!mixed && (L.d + L.p) * es < kSmallLongRow)) continue;
         np.var = ghost_rows16(L, dt) ? 1 : 0;
         finish_norm_plan(np, L, B);
     }
@@ -354,7 +363,7 @@ void demote_long_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     demote_small_full(plans, layers, B);
-    demote_long_small(plans, layers, dt, B);
+    demote_few_small(plans, layers, dt, B);
     split_small_ghost(plans, layers, dt, B);
 }
 
@@ -635,19 +644,43 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
 
 // Kernel variant of a linear layer's clipped gradient: narrow layers with
 // T >= 64 run on the narrow kernel (shorter T on the wide one), the other
-// Wide layers with T >= 64 on the 256 x 256 kernels, with the weights on the
-// accumulators when B fits the kernel's LDS table and padding each sample to
-// 16-row steps adds at most 1/8 to its rows, else on g.
+// Wide layers on the 256 x 256 LDS-DMA kernel when B fits its LDS weight table:
+// with the weights on the accumulators (GradDL) for T >= 64 when padding each
+// sample to 16-row steps adds at most 1/8 to its rows, else with the weights on
+// g's fragments over the flat rows of the batch (Grad).
 bk::GemmVariant grad_variant(const bk_layer& L, bool bf16, int64_t B) {
     const auto v = bk::gemm_variant(bf16, L.d, L.p, B * L.T, aligned16(L.x) && aligned16(L.g));
     if (is_narrow(v)) return L.T < 64 ? bk::GemmVariant::Wide : v;   // narrow kernel: T >= 64
-    if (v != bk::GemmVariant::Wide || L.T < 64) return v;
-    if (dl_padding_ok(L.T) && B <= bk::kDMaxB) return bk::GemmVariant::GradDL;
-    // The register-staged 256 x 256 kernel addresses all B T rows (and three
-    // stages of 64 past them) with 32-bit offsets; longer layers take the
-    // wide kernel, which addresses one stage at a time.
-    const bool fits = (B * L.T + 3 * 64) * std::max(L.d, L.p) * (bf16 ? 2 : 4) < ((int64_t)1 << 31);
-    return fits ? bk::GemmVariant::Grad : bk::GemmVariant::Wide;
+    if (v != bk::GemmVariant::Wide || B > bk::kDMaxB) return v;
+    return L.T >= 64 && dl_padding_ok(L.T) ? bk::GemmVariant::GradDL : bk::GemmVariant::Grad;
+}
+
+// Layers whose clipped gradient is a GEMM.
+bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 && !keeps_grads(L); }
+
+// The variants of a call's layers.  Few 256 x 256 tiles of few rows leave CUs
+// idle and cost a launch of their own: unless the call's layers of T < 64 give
+// kFlatMinTiles of them or have kFlatMinRows rows (enough for K slices), they
+// run on the 256 x 128 tiles, two to a CU (a small ResNet at 224 x 224, 7
+// samples: 14 + 10 us in one launch and 29 in two; 36 encoder layers of 64 x 37
+// rows, 648 tiles: 265 us against 295-310).
+constexpr int64_t kFlatMinTiles = 128, kFlatMinRows = 4096;
+std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B) {
+    std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
+    int64_t tiles = 0, rows = 0;
+    auto flat = [&](int64_t l) { return v[(size_t)l] == bk::GemmVariant::Grad && layers[l].T < 64; };
+    for (int64_t l = 0; l < n; ++l) {
+        if (!gemm_grad(layers[l])) continue;
+        v[(size_t)l] = grad_variant(layers[l], bf16, B);
+        if (!flat(l)) continue;
+        const bk::GemmGeom geo = bk::gemm_geom(bk::GemmVariant::Grad, layers[l].d, layers[l].p);
+        tiles += geo.tm * geo.tn;
+        rows = std::max(rows, B * layers[l].T);
+    }
+    if (tiles < kFlatMinTiles && rows < kFlatMinRows)
+        for (int64_t l = 0; l < n; ++l)
+            if (flat(l)) v[(size_t)l] = bk::GemmVariant::Wide;
+    return v;
 }
 
 // Tiles and K slices of a linear layer's clipped gradient on variant v
@@ -665,8 +698,10 @@ GradPlan grad_plan(const bk_layer& L, bk::GemmVariant v, int64_t B) {
     const bk::GemmGeom geo = bk::gemm_geom(v, L.d, L.p);
     GradPlan g{geo.tm, geo.tn, 1, geo.tile_elems, geo.swap};
     if (v == bk::GemmVariant::Grad || v == bk::GemmVariant::GradDL) {
+        // Layers of T < 64 take no slices of their own (only plan_tail's, whose
+        // partial tiles always fit the allocation-free scratch).
         const int64_t nst = v == bk::GemmVariant::Grad ? cdiv(B * L.T, 64) : B * dl_stages_per_sample(L.T);
-        g.ksplit = grad_ksplit(g.tm * g.tn, nst);
+        g.ksplit = L.T < 64 ? 1 : grad_ksplit(g.tm * g.tn, nst);
     } else if (is_narrow(v)) {
         g.ksplit = narrow_grad_ksplit(g.tm * g.tn, cdiv(B * L.T, 64));
     }
@@ -703,7 +738,9 @@ constexpr int64_t kTailMaxSplit = 16;    // K slices per tail tile, at most
 // at least kTailMinStages stages) and moved behind every other tile in
 // launch order: the slices are dispatched last and fill the CUs together
 // once the full rounds are done.  They are taken from the layer with the
-// most tiles, which goes last.
+// most tiles, which goes last.  A launch of no whole round (N tiles, at most
+// half the CUs) splits every layer's tiles the same way (a classifier stack of
+// 36 tiles with 4096 samples of one token: seven slices each).
 void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     if (g.e.empty()) return;
     const int64_t T0 = layers[g.e[0].l].T;
@@ -715,10 +752,15 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
         if (g.e[k].gp.tiles() > g.e[best].gp.tiles()) best = k;
     }
     const int64_t r = N % cus;
-    if (r == 0 || 2 * r > cus || g.e[best].gp.tiles() < r) return;
+    const bool all = N == r;             // no whole round
+    if (r == 0 || 2 * r > cus || (!all && g.e[best].gp.tiles() < r)) return;
     const int64_t nst = g.v == bk::GemmVariant::GradDL ? B * dl_stages_per_sample(T0) : cdiv(B * T0, 64);
     const int64_t sp = std::min({cus / r, nst / kTailMinStages, kTailMaxSplit});
     if (sp < 2) return;
+    if (all) {
+        for (GradEntry& e : g.e) e.gp.ksplit = sp;
+        return;
+    }
     std::rotate(g.e.begin() + (std::ptrdiff_t)best, g.e.begin() + (std::ptrdiff_t)best + 1, g.e.end());
     GradPlan& gp = g.e.back().gp;
     gp.ksplit = sp;
@@ -730,11 +772,12 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
 // kMaxGemm layers each.
 std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16, int64_t B) {
     std::vector<GradGroup> out;
+    const std::vector<bk::GemmVariant> vars = grad_variants(layers, n, bf16, B);
     for (int var = 0; var < bk::kGemmVariants; ++var) {
         for (int64_t l = 0; l < n; ++l) {
             const bk_layer& L = layers[l];
-            if (L.kind != BK_LINEAR || L.d * L.p == 0 || keeps_grads(L)) continue;
-            const auto v = grad_variant(L, bf16, B);
+            if (!gemm_grad(L)) continue;
+            const auto v = vars[(size_t)l];
             if ((int)v != var) continue;
             if (out.empty() || out.back().v != v || (int64_t)out.back().e.size() == bk::kMaxGemm)
                 out.push_back(GradGroup{v, {}});

@@ -129,10 +129,10 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 //          other variant takes), 128 x 128;
 //  Vec   : 16-byte loads, register transpose, 128 x 128 (fp32, or huge bf16);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
-//  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads (T >= 64);
-//  GradDL: as Grad with LDS DMA and the weights on the accumulators
-//          (B <= kDMaxB; each sample padded to whole stages of
-//          kDLStageRows rows).
+//  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads, LDS DMA,
+//          the weights on g's fragments (B <= kDMaxB);
+//  GradDL: as Grad with the weights on the accumulators (each sample padded
+//          to whole stages of kDLStageRows rows).
 //  Narrow32 / Narrow64: bf16, one side of d x p at most 32 / 64, tiles of
 //          256 along the long side (operands swapped when d < p).
 //  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns.

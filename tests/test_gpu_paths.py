@@ -169,3 +169,39 @@ def test_weighted_sum_runs(bk, B, n, accum):
                                "Pb": P.to(DEV), "accumulate": True}])
         bk.bk_weighted_grads(arr, 1, C.to(DEV), bk.BK_BF16, B)
         assert torch.equal(Gb, want)
+
+
+# The 256 x 256 DMA tiles over the flat rows of the batch, weights on g's
+# fragments: several samples per 32-row stage and per 16-row step, last stages
+# of every kind, K slices of a launch without a whole round, zero weights,
+# batches past the weight table (the 256 x 128 tiles).
+@pytest.mark.parametrize("B,T,d,p", [
+    (1, 1, 256, 256),        # one row
+    (33, 1, 264, 136),       # one row past a stage
+    (3, 16, 128, 72),        # 48 rows: a last stage of one step
+    (5, 37, 512, 264),       # samples across stages, ragged tiles
+    (2, 63, 80, 520),
+    (9, 13, 300, 200),
+    (80, 20, 256, 512),      # 50 stages: K slices
+    (1100, 1, 768, 200),
+    (6, 65, 264, 264),       # T > 64, padding over 1/8
+    (4097, 1, 72, 80),       # past the weight table
+])
+def test_flat_weighted_grad(bk, B, T, d, p):
+    gen = torch.Generator().manual_seed(B + T + d)
+    a, ah = _draw(B, T, d, BF, gen)
+    g, gh = _draw(B, T, p, BF, gen, 1e-2)
+    C = torch.rand(B, generator=gen) + 0.1
+    C[B // 2] = 0.0
+    G = bk.bk_weighted_grad(a, g, C.to(DEV))
+    ref = oracle.weighted_grad(ah, gh, C)
+    assert _frob(G.cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
+    C2 = torch.exp2(torch.randint(-3, 4, (B,), generator=gen).float())       # exact in bf16
+    G2 = bk.bk_weighted_grad(a, g, C2.to(DEV))
+    assert _frob(G2.cpu().numpy(), oracle.weighted_grad(ah, gh, C2)) <= GRAD_GUARD_EXACT
+    # two layers in one launch, one of them adding to its gradient
+    G0 = torch.randn(d, p, generator=gen).to(DEV)
+    Ga, Gw = G0.clone(), torch.empty(d, p, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "G": Ga, "accumulate": True}, {"x": a, "g": g, "G": Gw}])
+    bk.bk_weighted_grads(arr, 2, C.to(DEV), bk.BK_BF16, B)
+    assert torch.equal(Ga, G0 + Gw) and _frob(Gw.cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
