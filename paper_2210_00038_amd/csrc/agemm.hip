@@ -1201,6 +1201,244 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
         }
 }
 
+// ---------------------------------------------------------------------------
+// fp32 kernel, rows of any alignment: 128 x 128 output tile per 256-thread
+// workgroup, two workgroups per CU, waves of 64 x 64.
+//
+// fp32 MFMAs (32x32x2, 64 cycles) take one k value per lane and operand, so
+// the [k][column] rows of a and g are read as they lie in memory: a lane reads
+// two neighbouring columns of one a row and one g row (8 bytes: its values for
+// two 32-column sub-tiles, sub-tile x holding the columns = x mod 2) for four
+// MFMAs, and ends with two neighbouring columns of the output.  Rows go from
+// HBM straight into a ring of four 16-row stages (16 KB each: an a part and a
+// g part), up to three in flight: 16 bytes per lane when the rows allow it
+// (VEC), else 4.  Clip weights multiply g's values (rounded to
+// fp32, as a product C_i g): each wave fetches the weights of a stage's 16 rows
+// by one more DMA instruction, rows 0, 2, .. first, then 1, 3, .., into its own
+// slot of the stage.
+//
+// INST: the rows are one sample's, the tile's sum of squares is a norm partial,
+// and the tile is kept in L.G when set (BK-MixOpt).
+//
+// Bound by the fp32 MFMAs (157 TFLOP/s at 2.4 GHz; the chip holds 2.15 under
+// them).  The 12 layers of three GPT-2-small blocks on 16 x 128 tokens (87
+// GFLOP): 1171 us (74 TFLOP/s) on the register-transposing 128 x 128 kernel, 776
+// with this staging, 762 (114 TFLOP/s) with the reads a group ahead and the DMA
+// spread over the MFMAs.  One workgroup of eight waves per CU (32-row stages)
+// took 794: the MFMAs were busy 75% of the time, the barriers of one workgroup
+// uncovered by another.
+// ---------------------------------------------------------------------------
+constexpr int kFK = 16;                          // k rows per stage
+constexpr int kFRing = 4;                        // stages in the ring
+constexpr int kFOp = kFK * kTile * 4;            // bytes of one operand of one stage
+constexpr int kFW = 256;                         // bytes of a wave's weights slot (64 lanes)
+constexpr int kFWaves = 4;
+constexpr int kFStage = 2 * kFOp + kFWaves * kFW;
+
+template <bool INST, bool VEC>
+__global__ __launch_bounds__(256, 2) void agemm_f32_kernel(const GemmArgs args, int n_remap) {
+    constexpr int NI = kFK / (VEC ? 2 : 1) * (VEC ? 1 : 2) / kFWaves;   // DMA instructions per wave, operand, stage
+    constexpr int LPW = 2 * NI + (INST ? 0 : 1);                        // ... per wave and stage
+    static_assert(LPW * (kFRing - 2) < 64, "vmcnt");
+    __shared__ __attribute__((aligned(16))) char lds[kFRing * kFStage];
+    __shared__ float red[kFWaves];
+
+    const int wg = (int)blockIdx.x < n_remap ? xcd_remap(blockIdx.x, n_remap) : (int)blockIdx.x;
+    const int l = find_desc(args.n, (int64_t)wg, [&](int k) { return args.L[k].wg_begin; });
+    const GemmLayer& L = args.L[l];
+    const int nT = L.T, d = L.d, p = L.p, tn = L.tn;
+    const int tiles = L.tm * tn;
+    const int local = wg - L.wg_begin, sf = L.split_from;
+    // Clipped gradient: tiles below split_from whole, the others in ksplit
+    // slices.  INST: workgroup = (sample, tile, slice).
+    const int sample = INST ? local / (tiles * max(L.ksplit, 1)) : 0;
+    const int in_smp = local - (INST ? sample * tiles * max(L.ksplit, 1) : 0);
+    const int ks = in_smp < sf ? 1 : max(L.ksplit, 1);
+    const int rel = in_smp < sf ? 0 : (in_smp - sf) / ks;            // split tile, from split_from
+    const int tile = in_smp < sf ? in_smp : sf + rel;
+    const int slice = in_smp < sf ? 0 : (in_smp - sf) - rel * ks;
+    const int mt = tile / tn, nt = tile - mt * tn;
+    const int m0 = mt * kTile, n0 = nt * kTile;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const uint32_t nrows = INST ? (uint32_t)nT : (uint32_t)args.B * (uint32_t)nT;
+    const uint32_t rowA = (uint32_t)d * 4u, rowB = (uint32_t)p * 4u;
+    const float* baseA = reinterpret_cast<const float*>(L.a) + (INST ? (size_t)sample * nT * d : 0);
+    const float* baseB = reinterpret_cast<const float*>(L.g) + (INST ? (size_t)sample * nT * p : 0);
+
+    // DMA instruction i of this wave for one operand, q = 4 i + wave: rows 2 q
+    // and 2 q + 1, 16 bytes per lane, or half q of the stage's rows, 4 bytes per
+    // lane.  Columns past the matrix get an out-of-range offset.
+    uint32_t offA[NI], offB[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int q = kFWaves * i + wave;
+        const int row = VEC ? 2 * q + (lane >> 5) : q >> 1;
+        const int col = VEC ? 4 * (lane & 31) : 64 * (q & 1) + lane;
+        offA[i] = m0 + col < d ? (uint32_t)row * rowA + (uint32_t)(m0 + col) * 4u : kOut;
+        offB[i] = n0 + col < p ? (uint32_t)row * rowB + (uint32_t)(n0 + col) * 4u : kOut;
+    }
+    const u32x4_t rsC = raw_rsrc(args.C, INST ? 0u : (uint32_t)args.B * 4u);
+    // DMA instruction k (of LPW) of stage st into its slot; rows past the last
+    // one load zeros.
+    auto issue = [&](uint32_t st, int k) {
+        char* buf = lds + (st % kFRing) * kFStage;
+        if (k < 2 * NI) {
+            const int i = k >> 1;
+            const bool isa = (k & 1) == 0;
+            const u32x4_t rs = rows_raw_rsrc(isa ? baseA : baseB, isa ? rowA : rowB, st * kFK, nrows, kFK);
+            char* dst = buf + (isa ? 0 : kFOp) + (kFWaves * i + wave) * (VEC ? 1024 : 256);
+            if constexpr (VEC) dma16_asm(rs, isa ? offA[i] : offB[i], dst);
+            else dma4_asm(rs, isa ? offA[i] : offB[i], dst);
+        } else {
+            const uint32_t row = st * kFK + 2u * (lane & 7) + ((lane >> 3) & 1);
+            const bool ok = lane < kFK && row < nrows;
+            dma4_asm(rsC, ok ? row / (uint32_t)nT * 4u : kOut, buf + 2 * kFOp + wave * kFW);
+        }
+    };
+
+    f32x16_t acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.f;
+
+    const uint32_t nst_all = (nrows + kFK - 1) / kFK;
+    const uint32_t st_begin = (uint32_t)((uint64_t)slice * nst_all / (uint32_t)ks);
+    const uint32_t st_end = (uint32_t)((uint64_t)(slice + 1) * nst_all / (uint32_t)ks);
+    const int h = lane >> 5;
+    // A stage is two groups of four k steps (16 MFMAs).  The fragments of
+    // a group are read while the group before it is multiplied.  Between the
+    // MFMAs of its first group the wave refills stage st - 1's slot with stage
+    // st + 3 (issued in one go after the barrier, the address arithmetic left
+    // the MFMA pipe idle); in the last group, after its first MFMAs, it waits
+    // for its DMA of stage st + 1 (two later stages may stay in flight) and for
+    // the workgroup (every wave's part has landed, and no wave reads stage st
+    // any more), and reads the next stage's first group.
+    constexpr int GS = 4, NG = kFK / 2 / GS;     // k steps per group, groups per stage
+    struct Group {
+        float2 a[GS];
+        float2 b[GS];
+        float4 w;
+    };
+    Group fr[2];
+    auto read = [&](Group& f, uint32_t st, int q) {
+        const char* buf = lds + (st % kFRing) * kFStage;
+        const float* A = reinterpret_cast<const float*>(buf) + (2 * GS * q + h) * kTile + 64 * wm + 2 * (lane & 31);
+        const float* Bt =
+            reinterpret_cast<const float*>(buf + kFOp) + (2 * GS * q + h) * kTile + 64 * wn + 2 * (lane & 31);
+        if constexpr (!INST) f.w = reinterpret_cast<const float4*>(buf + 2 * kFOp + wave * kFW + 32 * h)[q];
+#pragma unroll
+        for (int j = 0; j < GS; ++j) {
+            f.a[j] = *reinterpret_cast<const float2*>(A + 2 * j * kTile);
+            f.b[j] = *reinterpret_cast<const float2*>(Bt + 2 * j * kTile);
+        }
+    };
+    auto mma = [&](const Group& f, int j) {
+        const float w = j == 0 ? f.w.x : j == 1 ? f.w.y : j == 2 ? f.w.z : f.w.w;
+        const float b0 = INST ? f.b[j].x : f.b[j].x * w, b1 = INST ? f.b[j].y : f.b[j].y * w;
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[j].x, b0, acc[0][0], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[j].x, b1, acc[0][1], 0, 0, 0);
+        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[j].y, b0, acc[1][0], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[j].y, b1, acc[1][1], 0, 0, 0);
+    };
+    constexpr int PPS = (LPW + GS * (NG - 1) - 1) / (GS * (NG - 1));     // DMA instructions per k step
+#pragma unroll
+    for (int s = 0; s < kFRing - 1; ++s)
+#pragma unroll
+        for (int k = 0; k < LPW; ++k) issue(st_begin + s, k);
+    wait_vmcnt<LPW * (kFRing - 2)>();
+    lds_barrier();
+    read(fr[0], st_begin, 0);
+    for (uint32_t st = st_begin; st < st_end; ++st) {
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+            if (q + 1 < NG) read(fr[(q + 1) & 1], st, q + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < GS; ++j) {
+                mma(fr[q & 1], j);
+                if (q + 1 < NG) {
+#pragma unroll
+                    for (int k = PPS * (GS * q + j); k < PPS * (GS * q + j + 1); ++k)
+                        if (k < LPW) issue(st + kFRing - 1, k);
+                } else if (j == GS / 2 - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_vmcnt<LPW * (kFRing - 2)>();
+                    lds_barrier();
+                    read(fr[0], st + 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // Drain the DMA past the end before the workgroup exits.
+    wait_vmcnt<0>();
+
+    // acc[x][y][i] is the tile's entry (row 64 wm + 2 acc_row + x, column
+    // 64 wn + 2 (lane mod 32) + y); rows and columns past d and p are zeros.
+    const int cn = 64 * wn + 2 * (lane & 31);
+    if (ks > 1) {
+        float* P = args.tiles + L.ptile_off +
+                   (((INST ? (size_t)sample * tiles : 0) + rel) * ks + slice) * (kTile * kTile);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                *reinterpret_cast<float2*>(P + (64 * wm + 2 * acc_row(i, lane) + x) * kTile + cn) =
+                    make_float2(acc[x][0][i], acc[x][1][i]);
+        return;
+    }
+    if constexpr (INST) {
+        float s = 0.f;
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s += acc[x][y][i] * acc[x][y][i];
+        const float tot = block_sum_256(s, red);
+        if (tid == 0) args.part[(size_t)L.part_off + (size_t)sample * tiles + tile] = tot;
+    }
+    float* out = INST ? (L.G ? L.G + (size_t)sample * d * p : nullptr) : L.G;
+    const int n = n0 + cn;
+    if (!out || n >= p) return;
+    const bool add = !INST && L.accum != 0;
+    const bool two = p % 2 == 0 && (reinterpret_cast<uintptr_t>(out) & 7u) == 0;     // 8-byte stores
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int r0 = m0 + 64 * wm + x;
+        float* q = out + (size_t)r0 * p + n;
+        float2 o[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = 2 * acc_row(i, lane);
+            o[i] = make_float2(0.f, 0.f);
+            if (add && r0 + r < d) {
+                if (two) o[i] = *reinterpret_cast<const float2*>(q + (size_t)r * p);
+                else o[i] = make_float2(q[(size_t)r * p], n + 1 < p ? q[(size_t)r * p + 1] : 0.f);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = 2 * acc_row(i, lane);
+            if (r0 + r >= d) continue;
+            const float2 v = add ? make_float2(o[i].x + acc[x][0][i], o[i].y + acc[x][1][i])
+                                 : make_float2(acc[x][0][i], acc[x][1][i]);
+            if (two) {
+                *reinterpret_cast<float2*>(q + (size_t)r * p) = v;
+            } else {
+                q[(size_t)r * p] = v.x;
+                if (n + 1 < p) q[(size_t)r * p + 1] = v.y;
+            }
+        }
+    }
+}
+
 // Sum of the K slices of split layers, slice 0 first.  Workgroup -> layer by
 // red_begin; inside a layer, tile group (sample * tiles + tile for the
 // instantiated norm, tile - split_from otherwise) and one kSplitRedWG-element
@@ -1278,6 +1516,9 @@ hipError_t launch_split_reduce(const GemmArgs& args, int n_wg, bool inst_norm, G
     else if (v == GemmVariant::Narrow32) {
         if (inst_norm) hipLaunchKernelGGL((split_reduce_kernel<kNM, 32, true>), grid, block, 0, s, args);
         else hipLaunchKernelGGL((split_reduce_kernel<kNM, 32, false>), grid, block, 0, s, args);
+    } else if (v == GemmVariant::F32 || v == GemmVariant::F32Any) {
+        if (inst_norm) hipLaunchKernelGGL((split_reduce_kernel<kTile, kTile, true>), grid, block, 0, s, args);
+        else hipLaunchKernelGGL((split_reduce_kernel<kTile, kTile, false>), grid, block, 0, s, args);
     } else if (v == GemmVariant::Narrow64) {
         if (inst_norm) hipLaunchKernelGGL((split_reduce_kernel<kNM, 64, true>), grid, block, 0, s, args);
         else hipLaunchKernelGGL((split_reduce_kernel<kNM, 64, false>), grid, block, 0, s, args);
@@ -1317,6 +1558,14 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
     if (v == GemmVariant::Narrow64) {
         if (inst_norm) hipLaunchKernelGGL((anarrow_kernel<true, 64>), grid, block, 0, s, args, n_wg);
         else hipLaunchKernelGGL((anarrow_kernel<false, 64>), grid, block, 0, s, args, n_wg);
+        return hipGetLastError();
+    }
+    if (v == GemmVariant::F32 || v == GemmVariant::F32Any) {
+        const int nr = n_remap > 0 && n_remap < n_wg ? n_remap : n_wg;
+#define BK_F32_GEMM(I, V) hipLaunchKernelGGL((agemm_f32_kernel<I, V>), grid, block, 0, s, args, nr)
+        if (v == GemmVariant::F32) { if (inst_norm) BK_F32_GEMM(true, true); else BK_F32_GEMM(false, true); }
+        else                       { if (inst_norm) BK_F32_GEMM(true, false); else BK_F32_GEMM(false, false); }
+#undef BK_F32_GEMM
         return hipGetLastError();
     }
 #define BK_GEMM(T, I, V) hipLaunchKernelGGL((agemm_kernel<T, I, V>), grid, block, 0, s, args)

@@ -218,8 +218,8 @@ void finish_norm_plan(NormPlan& np, const bk_layer& L, int64_t B) {
         np.tile_elems = bk::kGhostSplitTile;
         np.npart = np.ksplit > 1 ? np.tiles * bk::kGhostSplitParts : np.tiles;
     }
-    if (np.path == Path::Inst && inst_splits(np.var)) {
-        np.ksplit = inst_ksplit(B, np.tiles, L.T);
+    if (np.path == Path::Inst) {
+        if (inst_splits(np.var)) np.ksplit = inst_ksplit(B, np.tiles, L.T);
         if (np.ksplit > 1) np.npart = np.tiles * (np.tile_elems / bk::kSplitRedWG);
     }
     const bool small = np.path == Path::Ghost && np.var >= 4;
@@ -360,11 +360,45 @@ void demote_few_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_d
     }
 }
 
+// fp32 instantiated norms: one workgroup per (sample, tile), a 16-row stage of
+// its rows at a time.  When a call's stages, dealt evenly to kF32InstSlots
+// workgroups, make S each, a layer of 2 S stages or more per tile would run
+// long after the others (the stem of a ResNet: one or two tiles per sample over
+// thousands of rows): its tiles are cut into slices of about S stages, at
+// least kF32InstStages.  As for the column slices, only while the norms'
+// workspace stays within kGhostSplitWs.
+constexpr int64_t kF32InstSlots = 384, kF32InstStages = 16;
+void split_long_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B) {
+    auto f32 = [](const NormPlan& np) {
+        return np.path == Path::Inst && np.nwg > 0 &&
+               (np.var == (int)bk::GemmVariant::F32 || np.var == (int)bk::GemmVariant::F32Any);
+    };
+    int64_t work = 0;
+    for (size_t l = 0; l < plans.size(); ++l)
+        if (f32(plans[l])) work += B * plans[l].tiles * cdiv(layers[l].T, 16);
+    if (work == 0) return;
+    const int64_t S = std::max(kF32InstStages, cdiv(work, kF32InstSlots));
+    std::vector<NormPlan> split = plans;
+    size_t need = 0;
+    bool any = false;
+    for (size_t l = 0; l < plans.size(); ++l) {
+        NormPlan& np = split[l];
+        if (f32(np) && cdiv(layers[l].T, 16) >= 2 * S) {
+            np.ksplit = cdiv(layers[l].T, 16) / S;
+            finish_norm_plan(np, layers[l], B);
+            any = true;
+        }
+        need += norm_ws_bytes(np, B);
+    }
+    if (any && need <= kGhostSplitWs) plans.swap(split);
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     demote_small_full(plans, layers, B);
     demote_few_small(plans, layers, dt, B);
     split_small_ghost(plans, layers, dt, B);
+    if (dt == BK_F32) split_long_f32_inst(plans, layers, B);
 }
 
 // The norm plans of a call's layers (norm_plan each, then launch_wide).
@@ -732,7 +766,7 @@ constexpr int64_t kTailMinStages = 8;    // stages per slice of a split tail til
 constexpr int64_t kTailMaxSplit = 16;    // K slices per tail tile, at most
 
 // The 256 x 256 clipped-gradient kernels (Grad, GradDL) hold one workgroup
-// per CU, so a launch of N tiles of equal work runs in ceil(N / cus) rounds.
+// per CU (two fp32 workgroups share a CU's MFMA rate), so a launch of N tiles of equal work runs in ceil(N / cus) rounds.
 // When the last round is at most half full (r = N mod cus tiles), those r
 // tiles are cut into s = cus / r K slices each (at most kTailMaxSplit, of
 // at least kTailMinStages stages) and moved behind every other tile in
@@ -754,7 +788,8 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     const int64_t r = N % cus;
     const bool all = N == r;             // no whole round
     if (r == 0 || 2 * r > cus || (!all && g.e[best].gp.tiles() < r)) return;
-    const int64_t nst = g.v == bk::GemmVariant::GradDL ? B * dl_stages_per_sample(T0) : cdiv(B * T0, 64);
+    const int64_t nst = g.v == bk::GemmVariant::GradDL ? B * dl_stages_per_sample(T0)
+                        : g.v == bk::GemmVariant::Grad ? cdiv(B * T0, 64) : cdiv(B * T0, 16);
     const int64_t sp = std::min({cus / r, nst / kTailMinStages, kTailMaxSplit});
     if (sp < 2) return;
     if (all) {
@@ -766,6 +801,59 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     gp.ksplit = sp;
     gp.split_from = gp.tiles() - r;
     gp.tail = true;
+}
+
+// K slices of an fp32 launch (128 x 128 tiles, two workgroups per CU: P = 2 cus
+// slots; a layer's tile takes c = ceil(B T / 16) stages).  Layers of different
+// T: tiles of twice the even share of stages per slot or more (the early layers
+// of a ResNet) are cut into slices of about that share (a ResNet-18 of width 32
+// at 160 x 160, 8 samples: 3.4 ms -> 170 us).  Layers of one T with fewer tiles
+// than CUs: every tile in s slices, s the one that gives the shortest
+// ceil(N s / P) / s rounds plus the cost of writing and adding the partial
+// tiles, about kF32SliceCost stages a slice (LoRA of rank 16, 144 tiles of 256
+// stages: 287 -> 191 us in three slices).  With more tiles the last round of
+// cus tiles is split as the 256 x 256 kernels' (plan_tail): two workgroups share
+// a CU's MFMAs, so it is the tiles per CU that count (cutting the last round of
+// P slots instead changed nothing at 1296 tiles and cost 7% at 576).  At most
+// kF32MaxSlices partial tiles (64 MiB) in all.
+constexpr int64_t kF32MinStages = 8, kF32SliceCost = 7, kF32MaxSlices = 1024;
+void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
+    if (g.e.empty()) return;
+    const int64_t P = 2 * cus;
+    auto stages = [&](const GradEntry& e) { return cdiv(B * layers[e.l].T, 16); };
+    int64_t N = 0, work = 0;
+    bool same = true;
+    for (const GradEntry& e : g.e) {
+        N += e.gp.tiles();
+        work += e.gp.tiles() * stages(e);
+        same = same && layers[e.l].T == layers[g.e[0].l].T;
+    }
+    if (work == 0) return;
+    if (!same) {
+        const int64_t S = std::max(kF32MinStages, cdiv(work, P));
+        int64_t slices = 0;
+        for (const GradEntry& e : g.e)
+            if (stages(e) >= 2 * S) slices += e.gp.tiles() * (stages(e) / S);
+        if (slices > kF32MaxSlices) return;
+        for (GradEntry& e : g.e)
+            if (stages(e) >= 2 * S) e.gp.ksplit = stages(e) / S;
+        return;
+    }
+    if (N >= cus) {
+        plan_tail(g, layers, B, cus);
+        return;
+    }
+    const int64_t c = stages(g.e[0]);
+    int64_t s = 1;
+    double best = 1.0;
+    for (int64_t k = 2; k <= kTailMaxSplit && c / k >= kF32MinStages && N * k <= kF32MaxSlices; ++k) {
+        const double t = (double)cdiv(N * k, P) / (double)k + (double)(kF32SliceCost * N * k) / (double)(P * c);
+        if (t < 0.95 * best) {
+            best = t;
+            s = k;
+        }
+    }
+    for (GradEntry& e : g.e) e.gp.ksplit = s;
 }
 
 // The grouped launches of bk_weighted_grads: by kernel variant, at most
@@ -785,11 +873,13 @@ std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16,
         }
     }
     int64_t cus = 0;
-    for (GradGroup& g : out)
-        if (g.v == bk::GemmVariant::GradDL || g.v == bk::GemmVariant::Grad) {
-            if (cus == 0) cus = device_cus();
-            plan_tail(g, layers, B, cus);
-        }
+    for (GradGroup& g : out) {
+        const bool f32 = g.v == bk::GemmVariant::F32 || g.v == bk::GemmVariant::F32Any;
+        if (g.v != bk::GemmVariant::GradDL && g.v != bk::GemmVariant::Grad && !f32) continue;
+        if (cus == 0) cus = device_cus();
+        if (f32) plan_f32(g, layers, B, cus);
+        else plan_tail(g, layers, B, cus);
+    }
     return out;
 }
 
@@ -872,7 +962,7 @@ bk_status weighted_grads(const char* fn, const bk_layer* layers, int64_t n, cons
             g.accum = (L.flags & BK_LAYER_ACCUMULATE) ? 1 : 0;
             g.ptile_off = ptile;
             g.red_begin = (int32_t)red;
-            if (gp.tail) remap = wg + gp.split_from;   // the last layer; its slices run last
+            if (gp.tail) remap = wg + gp.split_from;   // the slices from here on run last, in order
             wg += gp.wgs();
             if (gp.ksplit > 1) {
                 ptile += gp.split_tiles() * gp.ksplit * gp.tile_elems;
@@ -1122,11 +1212,12 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
         case BK_OP_INST_NORM: {  // upper bound over the kernels (alignment is not known here)
             const size_t small = align_up((size_t)(B * cdiv(d, bk::kTile) * cdiv(p, bk::kTile)) * sizeof(float));
             L.kind = BK_LINEAR;
-            NormPlan np{};
-            np.path = Path::Inst;
-            set_norm_variant(np, L, dt, B);  // NULL pointers count as aligned
-            finish_norm_plan(np, L, B);
-            return std::max(small, norm_ws_bytes(np, B));
+            std::vector<NormPlan> one(1);
+            one[0].path = Path::Inst;
+            set_norm_variant(one[0], L, dt, B);  // NULL pointers count as aligned
+            finish_norm_plan(one[0], L, B);
+            launch_wide(one, &L, dt, B);
+            return std::max(small, norm_ws_bytes(one[0], B));
         }
         case BK_OP_WEIGHTED_GRAD:   // 16-byte aligned rows assumed (an upper bound)
             L.kind = BK_LINEAR;

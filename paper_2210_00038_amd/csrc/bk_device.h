@@ -176,6 +176,13 @@ __device__ __forceinline__ void dma16_asm(const u32x4_t& rs, uint32_t off, char*
                  :: "v"(off), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(m0v)) : "memory", "m0");
 }
 
+// The same with 4 bytes per lane (lane l's at lds_dst + 4 l).
+__device__ __forceinline__ void dma4_asm(const u32x4_t& rs, uint32_t off, char* lds_dst) {
+    const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_dst;
+    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dword %0, %1, 0 offen lds"
+                 :: "v"(off), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(m0v)) : "memory", "m0");
+}
+
 // ---------------------------------------------------------------------------
 // Reductions in a fixed order (deterministic).
 // ---------------------------------------------------------------------------

@@ -125,9 +125,10 @@ struct NoiseArgs {
 constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by one workgroup
 
 // Kernel variant of the a^T g GEMMs for one layer:
-//  Scalar: element loads (rows not 16-byte multiples / unaligned, that no
-//          other variant takes), 128 x 128;
-//  Vec   : 16-byte loads, register transpose, 128 x 128 (fp32, or huge bf16);
+//  Scalar: element loads, 128 x 128 (unaligned bf16 rows of fewer than 8
+//          columns, rows past 2^26 bytes);
+//  Vec   : 16-byte loads, register transpose, 128 x 128 (rows past 2^23 bytes
+//          in bf16, 2^26 in fp32);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
 //  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads, LDS DMA,
 //          the weights on g's fragments (B <= kDMaxB);
@@ -135,9 +136,12 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 //          to whole stages of kDLStageRows rows).
 //  Narrow32 / Narrow64: bf16, one side of d x p at most 32 / 64, tiles of
 //          256 along the long side (operands swapped when d < p).
-//  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns.
-enum class GemmVariant { Scalar = 0, Vec = 1, Wide = 2, Grad = 3, GradDL = 4, Narrow32 = 5, Narrow64 = 6, WideAny = 7 };
-constexpr int kGemmVariants = 8;
+//  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns;
+//  F32 / F32Any: fp32, LDS DMA, 128 x 128; 16-byte rows / rows of any alignment.
+enum class GemmVariant {
+    Scalar = 0, Vec = 1, Wide = 2, Grad = 3, GradDL = 4, Narrow32 = 5, Narrow64 = 6, WideAny = 7, F32 = 8, F32Any = 9
+};
+constexpr int kGemmVariants = 10;
 constexpr int kDMaxB = 4096;
 constexpr int kDLStageRows = 32;   // k rows per stage of the GradDL kernel
 constexpr int kDLBuffers = 4;      // its LDS stage buffers (the ping-pong schedule takes four)

@@ -30,6 +30,8 @@ GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p) {
 GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, bool aligned) {
     const int64_t es = bf16 ? 2 : 4;
     const bool vec = aligned && (d * es) % 16 == 0 && (p * es) % 16 == 0;
+    if (!bf16 && 4 * 32 * std::max(d, p) < ((int64_t)1 << 31))   // a stage of 32 rows takes 32-bit offsets
+        return vec ? GemmVariant::F32 : GemmVariant::F32Any;
     // bf16 rows of any alignment, 8 columns or more on both sides.
     if (!vec) return bf16 && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
     // The wide and narrow kernels address one K stage of rows at a time with

@@ -205,3 +205,45 @@ def test_flat_weighted_grad(bk, B, T, d, p):
     arr = bk.make_layers([{"x": a, "g": g, "G": Ga, "accumulate": True}, {"x": a, "g": g, "G": Gw}])
     bk.bk_weighted_grads(arr, 2, C.to(DEV), bk.BK_BF16, B)
     assert torch.equal(Ga, G0 + Gw) and _frob(Gw.cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
+
+
+# The fp32 GEMM: 128 x 128 tiles, 16-row stages, rows of 16-byte multiples and
+# of any length, K slices, accumulation, per-sample gradients.
+@pytest.mark.parametrize("B,T,d,p,off", [
+    (1, 1, 4, 4, 0),           # one row, one piece
+    (3, 5, 128, 132, 0),       # 15 rows; one piece past a tile
+    (2, 8, 127, 129, 0),       # 16 rows of odd length
+    (17, 1, 300, 10, 0),       # one row past a stage, a sample a row
+    (4, 64, 256, 384, 0),      # whole tiles, two K slices
+    (40, 33, 132, 260, 0),     # many slices, ragged
+    (6, 50, 64, 200, 1),       # misaligned base
+    (5, 100, 1, 77, 0),        # one column
+    (2, 1030, 136, 24, 0),     # long samples: per-sample gradients in K slices too
+])
+def test_f32_gemm(bk, B, T, d, p, off):
+    gen = torch.Generator().manual_seed(B + T + d + p)
+    a, ah = _draw(B, T, d, F32, gen, 1.0, off)
+    g, gh = _draw(B, T, p, F32, gen, 1e-2, off)
+    C = torch.rand(B, generator=gen) + 0.1
+    C[B // 2] = 0.0
+    G = bk.bk_weighted_grad(a, g, C.to(DEV))
+    ref = oracle.weighted_grad(ah, gh, C)
+    # random products: sqrt(rows) roundings of the running sum, 2^-24 each
+    bound = 4 * np.sqrt(B * T) * 2.0 ** -24 + 2.0 ** -23
+    assert _frob(G.cpu().numpy(), ref) <= min(bound, GRAD_GATE["f32"])
+    G0 = torch.randn(d, p, generator=gen).to(DEV)
+    Ga = G0.clone()
+    arr = bk.make_layers([{"x": a, "g": g, "G": Ga, "accumulate": True}])
+    bk.bk_weighted_grads(arr, 1, C.to(DEV), bk.BK_F32, B)
+    assert torch.equal(Ga, G0 + G)
+    norm, P = bk.bk_per_sample_grads(a, g)
+    assert torch.equal(norm, bk.bk_inst_norm(a, g))
+    assert _rel(norm.cpu().numpy(), oracle.linear_norm_sq(ah, gh)) <= NORM_GATE["f32"]
+    assert _frob(P.cpu().numpy(), oracle.per_sample_grads(ah, gh)) <= bound
+    # next to a layer of many more rows, which takes slices of its own
+    x, xh = _draw(B, 40 * T, 24, F32, gen)
+    Gs = [torch.empty(d, p, device=DEV), torch.empty(24, 24, device=DEV)]
+    arr = bk.make_layers([{"x": a, "g": g, "G": Gs[0]}, {"x": x, "g": x, "G": Gs[1]}])
+    bk.bk_weighted_grads(arr, 2, C.to(DEV), bk.BK_F32, B)
+    assert _frob(Gs[0].cpu().numpy(), ref) <= min(bound, GRAD_GATE["f32"])
+    assert _frob(Gs[1].cpu().numpy(), oracle.weighted_grad(xh, xh, C)) <= GRAD_GATE["f32"]
