@@ -227,9 +227,10 @@ void finish_norm_plan(NormPlan& np, const bk_layer& L, int64_t B) {
     const bool affine = L.kind == BK_NORM_AFFINE || (L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS));
     // A ghost layer on the 16-byte path with one 128-row block per sample
     // sums its bias terms while its g passes through LDS for the Gram.
-    // So does the few-token kernel.
-    np.fused_bias = np.path == Path::Ghost && ((np.var == 1 && np.ksplit == 1) || small) && L.T > 0 &&
-                    L.T <= bk::kSuper && L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS) && L.p > 0;
+    // So do the few-token and the whole-sample kernel.
+    np.fused_bias = np.path == Path::Ghost && L.T > 0 &&
+                    ((np.var == 1 && np.ksplit == 1 && L.T <= bk::kSuper) || small || np.var == 2) &&
+                    L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS) && L.p > 0;
     np.aff_chunks = affine && !np.fused_bias ? cdiv(L.p, bk::kAffineCols) : 0;
 }
 

@@ -35,7 +35,8 @@ struct GhostLayer {
     int32_t ka;
     int32_t red_begin;  // first workgroup of the split's reduction
     int64_t tile_off;
-    // Linear layer with a bias, 16-byte rows and T <= 128: the per-sample
+    // Linear layer with a bias whose workgroups see whole samples (16-byte
+    // rows and T <= 128, few tokens, the whole-sample kernel): the per-sample
     // bias sums [B,p] go here and their squared norm joins the partials; else
     // nullptr.
     float* Pb;

@@ -54,6 +54,50 @@ __device__ __forceinline__ WaveTiles wave_tiles(int wave, bool diag) {
     return t;
 }
 
+// Column sums of rows held in LDS, a wave at a time: lane 8 j + r adds 16-byte
+// column j of rows r, r + 8, .. into c[EPV] (add16), then col_reduce8 adds the
+// eight lanes of a column in a fixed order and leaves each lane one element:
+// element lane mod 8 of column j for EPV = 8 (bf16), (lane mod 8) / 2 for EPV =
+// 4.  Three exchange steps on the vector ALU (DPP), each lane sending the half
+// of its values that its partner keeps (shuffles of every value through LDS
+// cost the T <= 256 kernel 40% of its time).
+template <typename T>
+__device__ __forceinline__ void add16(const uint4& v, float c[Elem<T>::per16]) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2) {
+            c[2 * e] += __uint_as_float(w[e] << 16);
+            c[2 * e + 1] += __uint_as_float(w[e] & 0xFFFF0000u);
+        } else {
+            c[e] += __uint_as_float(w[e]);
+        }
+    }
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_get(float a) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL, int N>
+__device__ __forceinline__ void dpp_halve(float* c, bool hi) {
+    if constexpr (N == 1) {
+        c[0] += dpp_get<CTRL>(c[0]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < N / 2; ++e) {
+            const float keep = hi ? c[N / 2 + e] : c[e], send = hi ? c[e] : c[N / 2 + e];
+            c[e] = keep + dpp_get<CTRL>(send);
+        }
+    }
+}
+template <int EPV>
+__device__ __forceinline__ float col_reduce8(float* c, int lane) {
+    dpp_halve<0x141, EPV>(c, (lane & 4) != 0);                   // row_half_mirror: lane i with 7 - i
+    dpp_halve<0x4E, EPV / 2>(c, (lane & 2) != 0);                // quad_perm [2,3,0,1]
+    dpp_halve<0xB1, EPV / 4>(c, (lane & 1) != 0);                // quad_perm [1,0,3,2]
+    return c[0];
+}
+
 // The K elements (fewer than 16 bytes) of a short row, zeros after them; at
 // column k > 0 there is nothing.
 template <typename T>
@@ -186,10 +230,8 @@ constexpr int kRingBytes = 64 * 1024;        // LDS ring of gram_dl
 // Column sums (DIAG with a single 128-row block, i.e. T <= 128): with cs set,
 // each chunk's columns are also summed over the block's rows from LDS, cs[k] =
 // sum_t X[t, k] is written and bsq accumulates cs[k]^2 (threads that finish
-// columns).  Thread t sums 16-byte column t % C16 over every (256 / C16)-th
-// row; lanes of a wave holding the same column are added by shuffles, the
-// four waves through cbuf (two 4 x 128-float halves, by chunk parity), in a
-// fixed order.
+// columns).  Wave w sums rows 32 q + 8 w + 0 .. 7, the four waves are added
+// through cbuf (two 4 x 128-float halves, by chunk parity), in a fixed order.
 template <typename T, bool DIAG, int CW>
 __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K, int rowR, int rowC,
                                         int ch0, int ch1, const WaveTiles& wt, f32x16_t acc[4], char* __restrict__ lds,
@@ -274,40 +316,20 @@ __device__ __forceinline__ void gram_dl(const T* __restrict__ X, int rows, int K
 
     // Column sums of chunk ch into cbuf, and their completion (after the
     // next barrier) into cs / bsq.
-    constexpr int RPP = 256 / C16;            // rows apart of one thread's reads
+    static_assert(!DIAG || C16 == 8, "column sums");
     auto colsum = [&](int ch) {
         const char* sR = lds + ((ch % NCH) * SPC) * SLOT;
-        const int j = tid % C16;
         float c[EPV];
 #pragma unroll
         for (int e = 0; e < EPV; ++e) c[e] = 0.f;
 #pragma unroll
-        for (int q = 0; q < kSuper / RPP; ++q) {
-            const int row = tid / C16 + RPP * q;
-            const uint4 v = *reinterpret_cast<const uint4*>(sR + row * CW + swz(row, j) * 16);
-            if constexpr (sizeof(T) == 2) {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    c[2 * e] += __uint_as_float(w[e] << 16);
-                    c[2 * e + 1] += __uint_as_float(w[e] & 0xFFFF0000u);
-                }
-            } else {
-                c[0] += __uint_as_float(v.x);
-                c[1] += __uint_as_float(v.y);
-                c[2] += __uint_as_float(v.z);
-                c[3] += __uint_as_float(v.w);
-            }
+        for (int q = 0; q < kSuper / 32; ++q) {
+            const int row = 32 * q + 8 * wave + (lane & 7);
+            add16<T>(*reinterpret_cast<const uint4*>(sR + row * CW + swz(row, lane >> 3) * 16), c);
         }
-        // lanes j, j + C16, ... of the wave hold the same columns
-#pragma unroll
-        for (int off = C16; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) c[e] += __shfl_xor(c[e], off, 64);
-        if (lane < C16) {
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) cbuf[(ch & 1) * 512 + wave * 128 + j * EPV + e] = c[e];
-        }
+        const float v = col_reduce8<EPV>(c, lane);
+        if (EPV == 8) cbuf[(ch & 1) * 512 + wave * 128 + lane] = v;
+        else if (!(lane & 1)) cbuf[(ch & 1) * 512 + wave * 128 + (lane >> 1)] = v;
     };
     auto colsum_done = [&](int ch) {
         if (tid < EPC) {
@@ -596,6 +618,42 @@ struct HalfTiles {
     }
 };
 
+// Column sums of g's chunks over a whole sample of T <= 256 rows (the bias
+// gradient), formed while the chunks sit in LDS for the Gram: wave w adds rows
+// 64 q + 8 w + 0 .. 7, the eight waves are added through cbuf (two halves, by
+// chunk parity) after the next barrier.  Rows past T are zeros.  The sums go to
+// cs and their squares to bsq (threads that finish columns).  On six ViT-base
+// blocks (T = 197, 64 samples) the norms take 392 us with them and 328 without,
+// against 170 us for a pass of their own over g (shuffles of all eight values
+// through LDS: 468 us).
+struct BiasSums {
+    float* cs;          // [p], or nullptr: no bias
+    float* cbuf;        // [2][8 waves][64]
+    float bsq;
+    __device__ __forceinline__ void add(const char* __restrict__ slot, int ch) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        float c[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c[e] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = 64 * q + 8 * wave + (lane & 7);
+            add16<bf16_t>(*reinterpret_cast<const uint4*>(slot + row * kFullCW + full_swz(row, lane >> 3) * 16), c);
+        }
+        cbuf[(ch & 1) * 512 + wave * 64 + lane] = col_reduce8<8>(c, lane);
+    }
+    __device__ __forceinline__ void done(int ch, int p) {
+        const int tid = threadIdx.x, k = ch * 64 + tid;
+        if (tid >= 64 || k >= p) return;
+        const float* q = cbuf + (ch & 1) * 512 + tid;
+        float v = q[0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += q[64 * w];
+        cs[k] = v;
+        bsq += v * v;
+    }
+};
+
 // One wave's share of a work item: stream a's then g's chunks through the
 // ring, accumulating this wave's sub-tiles (Tiles) of both Grams, and return
 // its weighted sum of Gram(a) o Gram(g).  Chunk v: wait for this wave's loads
@@ -603,7 +661,7 @@ struct HalfTiles {
 // it have landed and every wave is done with chunk v - 1), refill chunk
 // v - 1's slot, multiply.
 template <typename Tiles, int LPW, int NSLOT, int SLOTB>
-__device__ __forceinline__ float stream_wave(const FullStream<LPW>& fs, char* ring, int wave) {
+__device__ __forceinline__ float stream_wave(const FullStream<LPW>& fs, char* ring, int wave, BiasSums& bias) {
     constexpr int N = Tiles::N;
     f32x16_t accA[N > 0 ? N : 1], accG[N > 0 ? N : 1];
 #pragma unroll
@@ -619,13 +677,20 @@ __device__ __forceinline__ float stream_wave(const FullStream<LPW>& fs, char* ri
         fs.template issue<NSLOT, SLOTB>(v + NSLOT - 1, ring, wave);
         Tiles::compute(ring + (v % NSLOT) * SLOTB, accA);
     }
+    const bool sums = bias.cs != nullptr;
     for (int v = fs.nca; v < nv; ++v) {
         wait_vmcnt<LPW * (NSLOT - 2)>();
         lds_barrier();
+        if (sums && v > fs.nca) bias.done(v - 1 - fs.nca, fs.Kg);
         fs.template issue<NSLOT, SLOTB>(v + NSLOT - 1, ring, wave);
+        if (sums) bias.add(ring + (v % NSLOT) * SLOTB, v - fs.nca);
         Tiles::compute(ring + (v % NSLOT) * SLOTB, accG);
     }
     wait_vmcnt<0>();
+    if (sums) {
+        lds_barrier();
+        bias.done(nv - 1 - fs.nca, fs.Kg);
+    }
     return Tiles::dot(accA, accG);
 }
 
@@ -690,36 +755,38 @@ __device__ __forceinline__ float stream_wave_pp(const FullStream<LPW>& fs, char*
 }
 
 template <typename Tiles, int LPW, int NSLOT, int SLOTB, bool PP>
-__device__ __forceinline__ float stream_any(const FullStream<LPW>& fs, char* ring, int wave) {
+__device__ __forceinline__ float stream_any(const FullStream<LPW>& fs, char* ring, int wave,
+                                            BiasSums& bias) {
     if constexpr (PP) return stream_wave_pp<Tiles, LPW, NSLOT, SLOTB>(fs, ring, wave);
-    else return stream_wave<Tiles, LPW, NSLOT, SLOTB>(fs, ring, wave);
+    else return stream_wave<Tiles, LPW, NSLOT, SLOTB>(fs, ring, wave, bias);
 }
 
 template <int NSUB, int LPW, int NSLOT, int SLOTB, bool PP = false>
-__device__ __forceinline__ float diag_item(const FullStream<LPW>& fs, char* ring, int wave) {
+__device__ __forceinline__ float diag_item(const FullStream<LPW>& fs, char* ring, int wave,
+                                           BiasSums& bias) {
     switch (wave) {
-        case 0: return stream_any<DiagTiles<NSUB, 0>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 1: return stream_any<DiagTiles<NSUB, 1>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 2: return stream_any<DiagTiles<NSUB, 2>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 3: return stream_any<DiagTiles<NSUB, 3>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 4: return stream_any<DiagTiles<NSUB, 4>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 5: return stream_any<DiagTiles<NSUB, 5>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 6: return stream_any<DiagTiles<NSUB, 6>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        default: return stream_any<DiagTiles<NSUB, 7>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
+        case 0: return stream_any<DiagTiles<NSUB, 0>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 1: return stream_any<DiagTiles<NSUB, 1>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 2: return stream_any<DiagTiles<NSUB, 2>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 3: return stream_any<DiagTiles<NSUB, 3>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 4: return stream_any<DiagTiles<NSUB, 4>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 5: return stream_any<DiagTiles<NSUB, 5>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 6: return stream_any<DiagTiles<NSUB, 6>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        default: return stream_any<DiagTiles<NSUB, 7>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
     }
 }
 
 template <int LPW, int NSLOT, int SLOTB, bool PP = false>
-__device__ __forceinline__ float half_item(const FullStream<LPW>& fs, char* ring, int wave) {
+__device__ __forceinline__ float half_item(const FullStream<LPW>& fs, char* ring, int wave, BiasSums& bias) {
     switch (wave) {
-        case 0: return stream_any<HalfTiles<0>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 1: return stream_any<HalfTiles<1>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 2: return stream_any<HalfTiles<2>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 3: return stream_any<HalfTiles<3>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 4: return stream_any<HalfTiles<4>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 5: return stream_any<HalfTiles<5>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        case 6: return stream_any<HalfTiles<6>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
-        default: return stream_any<HalfTiles<7>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave);
+        case 0: return stream_any<HalfTiles<0>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 1: return stream_any<HalfTiles<1>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 2: return stream_any<HalfTiles<2>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 3: return stream_any<HalfTiles<3>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 4: return stream_any<HalfTiles<4>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 5: return stream_any<HalfTiles<5>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        case 6: return stream_any<HalfTiles<6>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
+        default: return stream_any<HalfTiles<7>, LPW, NSLOT, SLOTB, PP>(fs, ring, wave, bias);
     }
 }
 
@@ -749,6 +816,7 @@ constexpr bool kLongPP = BK_GHOST_LONG_PP != 0;  // ping-pong stream (stream_wav
 __global__ __launch_bounds__(kFullThreads) void ghost_full_kernel(const GhostArgs args) {
     __shared__ __attribute__((aligned(16))) char ring[kFullSlots * kFullSlot];
     __shared__ float red[kFullThreads / 64];
+    __shared__ float cbuf[2 * 8 * 64];
     // One workgroup per (layer, sample); nothing is shared between them, so
     // the hardware's round-robin deal over the XCDs stays (the host orders the
     // layers largest first).
@@ -759,14 +827,15 @@ __global__ __launch_bounds__(kFullThreads) void ghost_full_kernel(const GhostArg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     FullStream<4> fs;
     fs.init(L, sample, 0, 256, wave, lane);
+    BiasSums bias{L.Pb ? L.Pb + (size_t)sample * L.p : nullptr, cbuf, 0.f};
     float part;
     switch (L.nsb) {            // 32-row blocks, 5 .. 8 (the host's range for this kernel)
-        case 5: part = diag_item<5, 4, kFullSlots, kFullSlot>(fs, ring, wave); break;
-        case 6: part = diag_item<6, 4, kFullSlots, kFullSlot>(fs, ring, wave); break;
-        case 7: part = diag_item<7, 4, kFullSlots, kFullSlot>(fs, ring, wave); break;
-        default: part = diag_item<8, 4, kFullSlots, kFullSlot>(fs, ring, wave); break;
+        case 5: part = diag_item<5, 4, kFullSlots, kFullSlot>(fs, ring, wave, bias); break;
+        case 6: part = diag_item<6, 4, kFullSlots, kFullSlot>(fs, ring, wave, bias); break;
+        case 7: part = diag_item<7, 4, kFullSlots, kFullSlot>(fs, ring, wave, bias); break;
+        default: part = diag_item<8, 4, kFullSlots, kFullSlot>(fs, ring, wave, bias); break;
     }
-    write_part_512(part, red, args.part + (size_t)L.part_off + (size_t)sample);
+    write_part_512(part + bias.bsq, red, args.part + (size_t)L.part_off + (size_t)sample);
 }
 
 __global__ __launch_bounds__(kFullThreads) void ghost_long_kernel(const GhostArgs args) {
@@ -779,12 +848,13 @@ __global__ __launch_bounds__(kFullThreads) void ghost_long_kernel(const GhostArg
     const GhostLayer& L = args.L[l];
     const int local = wg - L.wg_begin, nsb = L.nsb, items = L.npairs;   // items = nsb^2
     const int sample = local / items, q = local - sample * items;
+    BiasSums none{nullptr, nullptr, 0.f};            // their bias sums run in a pass of their own
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     float part;
     if (q < nsb) {                                   // diagonal: super block q against itself
         FullStream<4> fs;
         fs.init(L, sample, 256 * q, 0, wave, lane);
-        part = diag_item<8, 4, kLongSlots, kLongSlot, kLongPP>(fs, ring, wave);
+        part = diag_item<8, 4, kLongSlots, kLongSlot, kLongPP>(fs, ring, wave, none);
     } else {                                         // pair R < C, half h of C
         int m = (q - nsb) >> 1;
         const int h = (q - nsb) & 1;
@@ -793,7 +863,7 @@ __global__ __launch_bounds__(kFullThreads) void ghost_long_kernel(const GhostArg
         const int C = R + 1 + m;
         FullStream<6> fs;
         fs.init(L, sample, 256 * R, 256 * C + 128 * h, wave, lane);
-        part = half_item<6, kLongSlots, kLongSlot, kLongPP>(fs, ring, wave);
+        part = half_item<6, kLongSlots, kLongSlot, kLongPP>(fs, ring, wave, none);
     }
     write_part_512(part, red, args.part + (size_t)L.part_off + (size_t)sample * items + q);
 }
@@ -919,9 +989,9 @@ __global__ __launch_bounds__(256, 2) void ghost_norm_kernel(const GhostArgs args
 // 1024 samples 158 -> 18 us; 36 encoder layers at T = 37, 64 samples (600 MB)
 // 172 -> 106 us (5.7 TB/s); one 64 x 64 float32 layer at T = 16 12 -> 7 us.
 //
-// Bias sums (Pb): one sample per workgroup: row groups of 8 NSUB threads per
-// 16-byte column, added by shuffles and through LDS; several samples: each
-// thread adds the T rows of its (sample, column).  Fixed orders throughout.
+// Bias sums (Pb): one sample per workgroup: a wave adds all rows of eight
+// 16-byte columns of the chunk; several samples: each thread adds the T rows of
+// its (sample, column).  Fixed orders throughout.
 // ---------------------------------------------------------------------------
 template <typename T, int NSUB>
 __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(const GhostArgs args) {
@@ -935,7 +1005,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
     constexpr int KS = CPR / 2 / 4;               // MFMA k steps (32 bytes) per wave and chunk
     static_assert(NP == 4, "16 KB chunks");
     __shared__ __attribute__((aligned(16))) uint4 buf[32 * NSUB * ROWU4];
-    __shared__ float cbuf[4 * EPC];
+    __shared__ float cbuf[32];                    // column sums of the products
     __shared__ float bs[32];                      // squared bias sums of the workgroup's samples
     __shared__ float red[4];
 
@@ -971,18 +1041,6 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
             }
         }
     };
-    auto unpack = [&](const uint4& v, float c[EPV]) {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if constexpr (sizeof(T) == 2) {
-                c[2 * e] += __uint_as_float(w[e] << 16);
-                c[2 * e + 1] += __uint_as_float(w[e] & 0xFFFF0000u);
-            } else {
-                c[e] += __uint_as_float(w[e]);
-            }
-        }
-    };
     float bsq[4] = {0.f, 0.f, 0.f, 0.f};          // this thread's squared bias sums, of up to 4 samples
     // Several samples: thread (c16, rq) sums samples rq, rq + RPP, ...
     auto bias_direct = [&](int ch) {
@@ -994,7 +1052,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
             float c[EPV];
 #pragma unroll
             for (int e = 0; e < EPV; ++e) c[e] = 0.f;
-            for (int t = 0; t < nT; ++t) unpack(buf[(s * nT + t) * ROWU4 + c16], c);
+            for (int t = 0; t < nT; ++t) add16<T>(buf[(s * nT + t) * ROWU4 + c16], c);
 #pragma unroll
             for (int e = 0; e < EPV; ++e) bsq[m] += c[e] * c[e];      // columns past p are zeros
             float* q = Pb + (size_t)s * p + k;
@@ -1010,26 +1068,17 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
             }
         }
     };
-    // One sample: row groups, then (bias_done, after a barrier) the waves.
-    auto bias_groups = [&]() {
+    // One sample: a wave adds all rows of eight 16-byte columns.
+    auto bias_one = [&](int ch) {
+        if (8 * wave >= CPR) return;              // NSUB == 2: waves 0 and 1
         float c[EPV];
 #pragma unroll
         for (int e = 0; e < EPV; ++e) c[e] = 0.f;
 #pragma unroll
-        for (int j = 0; j < NP; ++j) unpack(buf[(rq + RPP * j) * ROWU4 + c16], c);
-#pragma unroll
-        for (int off = CPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) c[e] += __shfl_xor(c[e], off, 64);
-        if (lane < CPR) {
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) cbuf[wave * EPC + lane * EPV + e] = c[e];
-        }
-    };
-    auto bias_done = [&](int ch) {
-        const int k = ch * EPC + tid;
-        if (tid < EPC && k < p) {
-            const float v = ((cbuf[tid] + cbuf[EPC + tid]) + cbuf[2 * EPC + tid]) + cbuf[3 * EPC + tid];
+        for (int q = 0; q < 4 * NSUB; ++q) add16<T>(buf[(8 * q + (lane & 7)) * ROWU4 + 8 * wave + (lane >> 3)], c);
+        const float v = col_reduce8<EPV>(c, lane);
+        const int k = ch * EPC + 8 * wave * EPV + (EPV == 8 ? lane : lane >> 1);
+        if (k < p && (EPV == 8 || !(lane & 1))) {
             Pb[k] = v;
             bsq[0] += v * v;
         }
@@ -1038,7 +1087,6 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
         const bool isa = v < nca;
         const int K = isa ? d : p, ch = isa ? v : v - nca;
         lds_barrier();
-        if (!isa && ch > 0 && Pb && S == 1) bias_done(ch - 1);
         if (K >= EPV && (ch + 1) * EPC > K) {     // the rows' last chunk (uniform)
 #pragma unroll
             for (int j = 0; j < NP; ++j) pr[j] = shift_tail<T>(pr[j], ch * EPC + c16 * EPV, K);
@@ -1059,7 +1107,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
             }
         }
         if (!isa && Pb) {
-            if (S == 1) bias_groups();
+            if (S == 1) bias_one(ch);
             else bias_direct(ch);
         }
     };
@@ -1094,7 +1142,6 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
         if (v < nv) chunk(p0, v, acc[1]);
     }
     lds_barrier();
-    if (Pb && S == 1 && nv > nca) bias_done(nv - nca - 1);
 
     // Add the four waves' shares and multiply the Grams; with several samples
     // (NSUB == 1) the products go to prod[row][col].

@@ -247,3 +247,24 @@ def test_f32_gemm(bk, B, T, d, p, off):
     bk.bk_weighted_grads(arr, 2, C.to(DEV), bk.BK_F32, B)
     assert _frob(Gs[0].cpu().numpy(), ref) <= min(bound, GRAD_GATE["f32"])
     assert _frob(Gs[1].cpu().numpy(), oracle.weighted_grad(xh, xh, C)) <= GRAD_GATE["f32"]
+
+
+# 128 < T <= 256 in a launch of at least 512 (layer, sample) workgroups: the
+# whole-sample kernel forms the bias sums too (chunks of 64 columns, rows past T
+# zero, one chunk and several).
+@pytest.mark.parametrize("B,T,d,p", [(3, 129, 264, 200), (2, 197, 512, 264), (2, 256, 1280, 136)])
+def test_bias_in_whole_sample_ghost(bk, B, T, d, p):
+    gen = torch.Generator().manual_seed(B + T + p)
+    a, ah = _draw(B, T, d, BF, gen)
+    g, gh = _draw(B, T, p, BF, gen, 1e-2)
+    assert oracle.use_ghost(T, d, p)
+    k = -(-512 // B)
+    Pb, norm = torch.full((2, B, p), float("nan"), device=DEV), torch.empty(k + 1, B, device=DEV)
+    specs = [{"x": a, "g": g, "bias": i < 2, "Pb": Pb[i] if i < 2 else None} for i in range(k + 1)]
+    bk.bk_layer_norms(bk.make_layers(specs), k + 1, bk.BK_BF16, B, norm)
+    ref, sb = oracle.linear_norm_sq(ah, gh), oracle.bias_sums(gh)
+    got = norm.cpu().numpy()
+    for i in range(2):
+        assert _frob(Pb[i].cpu().numpy(), sb) <= 1e-6
+        assert _rel(got[i], ref + (sb ** 2).sum(1)) <= NORM_GUARD
+    assert _rel(got[2], ref) <= NORM_GUARD and torch.equal(norm[2], norm[k])
