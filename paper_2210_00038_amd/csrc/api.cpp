@@ -473,8 +473,19 @@ size_t layer_norms_ws(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t B)
     return tot;
 }
 
+// The clip factors that follow the norms (bk_private_grad).
+struct ClipOut {
+    float* C;
+    float* total;
+    int mode;
+    float R, gamma;
+};
+
+// With `clip`, the launch that finishes the norms of up to kMaxReduce layers
+// also writes the clip factors; *clipped says whether it did.
 bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtype dt, int64_t B,
-                      float* norm_sq, void* ws, size_t ws_bytes, hipStream_t s) {
+                      float* norm_sq, void* ws, size_t ws_bytes, hipStream_t s, const ClipOut* clip = nullptr,
+                      bool* clipped = nullptr) {
     if (n < 0) return fail(BK_ERR_INVALID_VALUE, "%s: negative layer count", fn);
     if (n > 0 && !layers) return fail(BK_ERR_INVALID_VALUE, "%s: NULL layer array", fn);
     bk_status st = check_dtype(fn, dt);
@@ -663,6 +674,14 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
         r.n = (int32_t)cnt;
         r.B = (int32_t)B;
         r.part = part;
+        if (clip && cnt == n) {
+            r.C = clip->C;
+            r.total = clip->total;
+            r.mode = clip->mode;
+            r.R = clip->R;
+            r.gamma = clip->gamma;
+            *clipped = true;
+        }
         for (int64_t k = 0; k < cnt; ++k) {
             const Item& it = items[(size_t)(l0 + k)];
             r.L[k].out = norm_sq + (l0 + k) * B;
@@ -1502,9 +1521,13 @@ bk_status bk_private_grad(const bk_layer* layers, int64_t n, bk_dtype dt, int64_
     if (ws_bytes < need || (need > 0 && !ws))
         return fail(BK_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", fn, ws_bytes, need);
 
-    if ((st = layer_norms(fn, layers, n, dt, B, norm_sq, ws, ws_bytes, s)) != BK_OK) return st;
-    hipError_t e = bk::launch_clip(norm_sq, n, B, (int)mode, R, gamma, C, total_sq, s);
-    if (e != hipSuccess) return hip_fail(e, "clip launch");
+    const ClipOut clip{C, total_sq, (int)mode, R, gamma};
+    bool clipped = false;
+    if ((st = layer_norms(fn, layers, n, dt, B, norm_sq, ws, ws_bytes, s, &clip, &clipped)) != BK_OK) return st;
+    if (!clipped) {
+        hipError_t e = bk::launch_clip(norm_sq, n, B, (int)mode, R, gamma, C, total_sq, s);
+        if (e != hipSuccess) return hip_fail(e, "clip launch");
+    }
     if ((st = weighted_grads(fn, layers, n, C, dt, B, ws, ws_bytes, s)) != BK_OK) return st;
     if (noise_std == 0.f) return BK_OK;
     std::vector<float*> G;

@@ -101,9 +101,15 @@ struct ReduceLayer {
     int32_t npart2;
 };
 constexpr int kMaxReduce = 200;
+// With C set the launch holds every layer of the call and also finishes
+// Algorithm 1's aggregation: the sum over layers and the clip factors.
 struct ReduceArgs {
     int32_t n, B;
     const float* part;
+    float* C;           // [B] clip factors, or nullptr: norms only
+    float* total;       // [B] squared norms over all layers, or nullptr
+    int32_t mode;
+    float R, gamma;
     ReduceLayer L[kMaxReduce];
 };
 

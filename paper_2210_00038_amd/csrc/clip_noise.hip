@@ -7,14 +7,10 @@
 namespace bk {
 namespace {
 
-// norm_sq[l][i] = sum of the partials of (layer l, sample i), in index order.
-__global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs args) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)args.n * args.B) return;
-    const int l = (int)(idx / args.B), i = (int)(idx - (int64_t)l * args.B);
-    const ReduceLayer& L = args.L[l];
-    // Partials in ascending order (the weight run, then the bias / affine
-    // run); sixteen loads are issued ahead of their adds.
+// Sum of the partials of (layer L, sample i) in ascending order (the weight
+// run, then the bias / affine run); sixteen loads are issued ahead of their
+// adds.
+__device__ __forceinline__ float reduce_partials(const ReduceArgs& args, const ReduceLayer& L, int i) {
     double s = 0.0;
     auto run = [&](const float* p, int np) {
         int k = 0;
@@ -29,10 +25,52 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs args) {
     };
     run(args.part + L.part_off + (int64_t)i * L.npart, L.npart);
     run(args.part + L.part_off2 + (int64_t)i * L.npart2, L.npart2);
-    L.out[i] = (float)s;
+    return (float)s;
 }
 
-// Algorithm 1, aggregation and clip factor (clip functions of eq. "DP optimizers").
+// Algorithm 1's clip factor of a sample with squared norm s (clip functions of
+// eq. "DP optimizers").
+__device__ __forceinline__ float clip_factor(double s, int mode, float R, float gamma) {
+    const double nrm = sqrt(s);
+    if (mode == 0) return (float)((nrm <= (double)R) ? 1.0 : (double)R / nrm);   // Abadi: min(R / ||g||, 1)
+    const double den = nrm + (double)gamma;                                     // automatic: 1 / (||g|| + gamma)
+    return (float)((den == 0.0) ? 0.0 : 1.0 / den);
+}
+
+// norm_sq[l][i] = sum of the partials of (layer l, sample i).
+__global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs args) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (int64_t)args.n * args.B) return;
+    const int l = (int)(idx / args.B), i = (int)(idx - (int64_t)l * args.B);
+    args.L[l].out[i] = reduce_partials(args, args.L[l], i);
+}
+
+// The same and the clip factors in one launch, for calls of up to kMaxReduce
+// layers: a workgroup takes as many whole samples as fit 256 (layer, sample)
+// pairs, one thread each, and then adds each sample's norms (ascending layers,
+// as clip_kernel).  Both are launch latency: the two kernels took 4.3 us (one
+// layer, 4 samples) to 11.7 us (21 layers, split ones among them), this one
+// 2.2 to 5.3.
+constexpr int kPairs = 256;
+static_assert(kMaxReduce <= kPairs, "one thread per (layer, sample)");
+__global__ __launch_bounds__(kPairs) void reduce_clip_kernel(const ReduceArgs args, int per_wg) {
+    __shared__ float norm[kPairs];
+    const int i0 = blockIdx.x * per_wg, l = threadIdx.x / per_wg, j = threadIdx.x - l * per_wg;
+    if (l < args.n && i0 + j < args.B) {
+        const float s = reduce_partials(args, args.L[l], i0 + j);
+        args.L[l].out[i0 + j] = s;
+        norm[threadIdx.x] = s;
+    }
+    __syncthreads();
+    const int i = i0 + threadIdx.x;
+    if ((int)threadIdx.x >= per_wg || i >= args.B) return;
+    double s = 0.0;
+    for (int k = 0; k < args.n; ++k) s += (double)norm[k * per_wg + threadIdx.x];
+    args.C[i] = clip_factor(s, args.mode, args.R, args.gamma);
+    if (args.total) args.total[i] = (float)s;
+}
+
+// Algorithm 1, aggregation and clip factor.
 __global__ __launch_bounds__(256) void clip_kernel(const float* __restrict__ norm_sq, int64_t L,
                                                    int64_t B, int mode, float R, float gamma,
                                                    float* __restrict__ C, float* __restrict__ total) {
@@ -49,15 +87,7 @@ __global__ __launch_bounds__(256) void clip_kernel(const float* __restrict__ nor
         for (int u = 0; u < 16; ++u) s += (double)v[u];
     }
     for (; l < L; ++l) s += (double)norm_sq[l * B + i];
-    const double nrm = sqrt(s);
-    double c;
-    if (mode == 0) {                       // Abadi: min(R / ||g||, 1)
-        c = (nrm <= (double)R) ? 1.0 : (double)R / nrm;
-    } else {                               // automatic: 1 / (||g|| + gamma)
-        const double den = nrm + (double)gamma;
-        c = (den == 0.0) ? 0.0 : 1.0 / den;
-    }
-    C[i] = (float)c;
+    C[i] = clip_factor(s, mode, R, gamma);
     if (total) total[i] = (float)s;
 }
 
@@ -122,6 +152,11 @@ __global__ __launch_bounds__(256) void philox_raw_kernel(uint64_t seed, uint32_t
 
 hipError_t launch_reduce(const ReduceArgs& args, int n_threads, hipStream_t s) {
     if (n_threads <= 0) return hipSuccess;
+    if (args.C) {
+        const int per_wg = kPairs / args.n;
+        hipLaunchKernelGGL(reduce_clip_kernel, dim3((args.B + per_wg - 1) / per_wg), dim3(kPairs), 0, s, args, per_wg);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(reduce_kernel, dim3((n_threads + 255) / 256), dim3(256), 0, s, args);
     return hipGetLastError();
 }
