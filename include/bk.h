@@ -313,13 +313,15 @@ bk_status bk_philox_raw(uint64_t seed, uint32_t tensor_id, uint32_t step, uint64
 /* ---------------------------------------------------------------------------
  * Grouped forms: the same computations for n layers in as few launches as
  * possible.  Results are bit-identical to calling the per-layer form on each
- * layer, with two exceptions, both to fp32 rounding: bf16 ghost-norm layers
+ * layer, with three exceptions, all to fp32 rounding: bf16 ghost-norm layers
  * with 128 < T <= 256 (and 16-byte rows) take a whole-sample kernel when the
  * launch gives it at least 512 workgroups (one per layer and sample), and a
  * kernel over pairs of 128-row blocks otherwise; and when all layers of that
  * pair kernel in a call (also 64 < T <= 128, fp32, unaligned rows, and long
- * rows of few tokens) give fewer than 128 workgroups, their rows are cut into
- * column slices.  Every result is
+ * rows of few tokens) give fewer than 64 workgroups, their rows are cut into
+ * column slices; instantiated norms take larger tiles, and long fp32 ones K
+ * slices, by what the call's instantiated layers give together (the clipped
+ * gradients' K slices likewise).  Every result is
  * deterministic.  The bk_layer array is read on the host during the call only.
  * ------------------------------------------------------------------------- */
 

@@ -156,16 +156,7 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
         np.npart = 0;
         np.var = 0;
     } else if (np.path == Path::Inst) {
-        auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, L.T, aligned16(L.x) && aligned16(L.g));
-        // 256 x 256 tiles on the LDS-DMA kernel (one workgroup per sample and
-        // tile) when the layer gives at least 128 of them: the wide kernel's
-        // 256 x 128 tiles at two workgroups per CU fill the chip no better,
-        // and below that it can split K.  Each sample is padded to 16-row
-        // steps by at most 1/8, and B T rows stay below 2^31.
-        if (v == bk::GemmVariant::Wide && L.T >= 64 && dl_padding_ok(L.T) && B * L.T < ((int64_t)1 << 31)) {
-            const bk::GemmGeom dl = bk::gemm_geom(bk::GemmVariant::GradDL, L.d, L.p);
-            if (B * dl.tm * dl.tn >= 128) v = bk::GemmVariant::GradDL;
-        }
+        const auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, L.T, aligned16(L.x) && aligned16(L.g));
         const bk::GemmGeom geo = bk::gemm_geom(v, L.d, L.p);
         np.var = (int)v;
         np.tiles = geo.tm * geo.tn;
@@ -394,8 +385,42 @@ void split_long_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers, i
     if (any && need <= kGhostSplitWs) plans.swap(split);
 }
 
+// bf16 instantiated norms on the 256 x 256 tiles of the LDS-DMA kernel (one
+// workgroup per sample and tile), when the call's layers that it can take give
+// at least kInstDLMinWG of them: below that the wide kernel, whose 256 x 128
+// tiles at two workgroups per CU fill the chip no better, can split K.  It
+// takes layers of T >= 64 whose samples pad to 16-row steps by at most 1/8, and
+// B T < 2^31.  (Counted per layer, a 768 x 768 layer of 8 samples, 72 tiles,
+// kept a launch of its own beside 792 tiles: 49 us, now inside their rounds.)
+constexpr int64_t kInstDLMinWG = 128;
+void promote_inst_dl(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B) {
+    auto takes = [&](size_t l) {
+        const bk_layer& L = layers[l];
+        return plans[l].path == Path::Inst && plans[l].var == (int)bk::GemmVariant::Wide && L.T >= 64 &&
+               dl_padding_ok(L.T) && B * L.T < ((int64_t)1 << 31);
+    };
+    int64_t wg = 0;
+    for (size_t l = 0; l < plans.size(); ++l)
+        if (takes(l)) {
+            const bk::GemmGeom geo = bk::gemm_geom(bk::GemmVariant::GradDL, layers[l].d, layers[l].p);
+            wg += B * geo.tm * geo.tn;
+        }
+    if (wg < kInstDLMinWG) return;
+    for (size_t l = 0; l < plans.size(); ++l)
+        if (takes(l)) {
+            NormPlan& np = plans[l];
+            const bk::GemmGeom geo = bk::gemm_geom(bk::GemmVariant::GradDL, layers[l].d, layers[l].p);
+            np.var = (int)bk::GemmVariant::GradDL;
+            np.tiles = np.npart = geo.tm * geo.tn;
+            np.tile_elems = geo.tile_elems;
+            np.ksplit = 1;
+            finish_norm_plan(np, layers[l], B);
+        }
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    promote_inst_dl(plans, layers, B);
     demote_small_full(plans, layers, B);
     demote_few_small(plans, layers, dt, B);
     split_small_ghost(plans, layers, dt, B);
