@@ -811,15 +811,18 @@ constexpr int64_t kTailMinStages = 8;    // stages per slice of a split tail til
 constexpr int64_t kTailMaxSplit = 16;    // K slices per tail tile, at most
 
 // The 256 x 256 clipped-gradient kernels (Grad, GradDL) hold one workgroup
-// per CU (two fp32 workgroups share a CU's MFMA rate), so a launch of N tiles of equal work runs in ceil(N / cus) rounds.
-// When the last round is at most half full (r = N mod cus tiles), those r
+// per CU (two fp32 workgroups share a CU's MFMA rate), so a launch of N tiles
+// of equal work runs in ceil(N / cus) rounds.  When the last round is at most half full (r = N mod cus tiles), those r
 // tiles are cut into s = cus / r K slices each (at most kTailMaxSplit, of
 // at least kTailMinStages stages) and moved behind every other tile in
 // launch order: the slices are dispatched last and fill the CUs together
 // once the full rounds are done.  They are taken from the layer with the
 // most tiles, which goes last.  A launch of no whole round (N tiles, at most
-// half the CUs) splits every layer's tiles the same way (a classifier stack of
-// 36 tiles with 4096 samples of one token: seven slices each).
+// half the CUs) splits the tiles of all its layers the same way where that is
+// shorter (a classifier stack of 36 tiles with 4096 samples of one token: seven
+// slices each; 128 tiles of 528 rows in two slices had cost 78 -> 98 us).
+constexpr int64_t kDLTimeRows = 32;
+constexpr double kSliceLaunch = 6.0, kSlicePartial = 0.12, kSliceGain = 0.85;
 void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     if (g.e.empty()) return;
     const int64_t T0 = layers[g.e[0].l].T;
@@ -837,7 +840,13 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
                         : g.v == bk::GemmVariant::Grad ? cdiv(B * T0, 64) : cdiv(B * T0, 16);
     const int64_t sp = std::min({cus / r, nst / kTailMinStages, kTailMaxSplit});
     if (sp < 2) return;
-    if (all) {
+    if (all && g.e.size() > 1) {
+        // In stages (about 1 us of 32 rows each): a slice's partial tile
+        // written and read back, and the second launch, against the stages
+        // that run at once.
+        const double stages = (double)cdiv(B * T0, kDLTimeRows);
+        const double cost = kSliceLaunch + (double)(N * sp) * kSlicePartial;
+        if (stages / (double)sp + cost > kSliceGain * stages) return;
         for (GradEntry& e : g.e) e.gp.ksplit = sp;
         return;
     }
