@@ -95,7 +95,8 @@ struct NormPlan {
     int var;            // kernel variant: ghost 0 = scalar, 1 = 16-byte loads,
                         // 2 = whole-sample kernel (bf16, 128 < T <= 256),
                         // 3 = 256-row super blocks (bf16, T > 256),
-                        // 4, 5 = few tokens (T <= 32, T <= 64; any alignment);
+                        // 4, 5 = few tokens (T <= 32, T <= 64; any alignment),
+                        // 6, 7 = fp32, T <= 96, T <= 128 (any alignment);
                         // instantiation: bk::GemmVariant
     int64_t tiles = 0;  // instantiation: output tiles per sample; ghost: super-block pairs
     int64_t ksplit = 1; // instantiation: K slices per tile (wide and narrow kernels);
@@ -182,9 +183,12 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
             np.var = L.T <= 2 * bk::kSuper ? 2 : 3;
             np.npart = np.var == 2 ? 1 : nsb * nsb;
         }
-        // Few tokens: whole samples packed into 32- or 64-row blocks.
-        if (np.path == Path::Ghost && L.T > 0 && L.T <= bk::kGhostSmallT) {
-            np.var = L.T <= 32 ? 4 : 5;
+        // Few tokens: whole samples packed into 32- or 64-row blocks; fp32 up
+        // to one super block: its MFMAs shared by all waves.
+        const bool mid = dt == BK_F32 && L.T <= bk::kSuper && std::min(L.d, L.p) >= 4 &&
+                         L.T * K * (int64_t)es < ((int64_t)1 << 31);
+        if (np.path == Path::Ghost && L.T > 0 && (L.T <= bk::kGhostSmallT || mid)) {
+            np.var = L.T <= 32 ? 4 : L.T <= 64 ? 5 : L.T <= 96 ? 6 : 7;
             np.npart = 1;
         }
         // An embedding with rows of g in 16-byte multiples: the id join
@@ -638,7 +642,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
     // a group larger than one launch's descriptor table is cut into launches
     // of near-equal layer counts (no small last launch).
     for (int kind = 0; kind < 3; ++kind)
-        for (int var = 0; var < (kind == 2 ? bk::kGemmVariants : 6); ++var) {
+        for (int var = 0; var < (kind == 2 ? bk::kGemmVariants : 8); ++var) {
             const Path want = kind == 0 ? Path::Ghost : kind == 1 ? Path::Embed : Path::Inst;
             std::vector<const Item*> all;
             for (const Item& it : items)

@@ -46,8 +46,9 @@ struct GhostArgs {
     int32_t n, B;
     int32_t remap;      // 1: workgroup order remapped per XCD (xcd_remap)
     int32_t n_red;      // workgroups of the column splits' reduction (0: no layer split)
-    int32_t small;      // few tokens: 32-row blocks (1: T <= 32, GhostLayer::nsb samples per
-                        // workgroup, 2: T <= 64) with one partial per sample; 0: super-block pairs
+    int32_t small;      // whole samples, one partial each: 32-row blocks of few tokens (1: T <= 32,
+                        // GhostLayer::nsb samples per workgroup, 2: T <= 64), fp32 3: T <= 96, 4: T <= 128;
+                        // 0: super-block pairs
     float* part;        // partial sums, [layer][sample][pair]
     float* tiles;       // partial Grams of the column splits
     GhostLayer L[kMaxGhost];

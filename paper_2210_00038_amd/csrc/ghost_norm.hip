@@ -1213,6 +1213,196 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
     }
 }
 
+// ---------------------------------------------------------------------------
+// fp32 ghost norms of 64 < T <= 128, rows of any alignment and at least 16
+// bytes: one 512-thread workgroup per (layer, sample), bound by the fp32 MFMAs
+// (64 cycles each).
+//
+// The pair kernel gives a diagonal block's sub-tiles to three of its four waves
+// (12 computed of 10 needed), which leaves a SIMD idle.  Here the NT upper-
+// triangle 32 x 32 sub-tiles (6 for NSUB = 3, T <= 96, else 10) are cut into two
+// halves and the columns into the eight 32-byte k steps of a chunk: wave w takes
+// half w / 4 over k steps w mod 4 and w mod 4 + 4, so every wave has the same
+// work.  Chunks of 256 bytes per row pass through two LDS buffers: while chunk
+// v is multiplied, chunk v + 1 is stored and chunk v + 2 is on its way to
+// registers, through buffer loads, whose addresses take one addition each (64-
+// bit addresses left the MFMAs idle for a third of the time).
+// The waves' shares are added through LDS at the end.  Bias sums as in the
+// other kernels.  The 12 layers of three GPT-2-small blocks, 16 x 128 tokens
+// (192 workgroups): 286 -> 189 us; 16 layers 264 wide, 9 x 65 tokens: 78 -> 45 us.
+// ---------------------------------------------------------------------------
+template <int NSUB, int HALF>
+struct HalfTriangle {
+    static constexpr int NT = NSUB * (NSUB + 1) / 2, N = NT / 2;
+    static constexpr int row(int q) { return FullTiles<NSUB>::row(HALF * N + q); }
+    static constexpr int col(int q) { return FullTiles<NSUB>::col(HALF * N + q); }
+};
+
+template <int NSUB, int HALF, int Q>
+__device__ __forceinline__ void half_triangle_mma(f32x16_t* acc, const uint4* fr) {
+    using HT = HalfTriangle<NSUB, HALF>;
+    if constexpr (Q < HT::N) {
+        constexpr int I = HT::row(Q), J = HT::col(Q);
+        Mfma<float>::step(acc[Q], fr[I], fr[J]);
+        half_triangle_mma<NSUB, HALF, Q + 1>(acc, fr);
+    }
+}
+
+constexpr int kMidRowU4 = 17;                     // 16 columns of 16 bytes, padded
+
+// The share of one half of the sub-tiles (waves 4 HALF .. 4 HALF + 3): every
+// wave of the workgroup passes the same barriers.
+template <int NSUB, int HALF>
+__device__ __forceinline__ void ghost_mid_half(const GhostArgs& args, uint4 (*buf)[32 * NSUB * kMidRowU4], float* cbuf,
+                                               float* red) {
+    constexpr int CPR = 16, EPC = 64;             // 16-byte columns, elements per row and chunk
+    constexpr int ROWU4 = kMidRowU4;
+    constexpr int NP = NSUB;                      // loads per thread and chunk
+    constexpr int N = NSUB * (NSUB + 1) / 4;      // sub-tiles per wave
+
+    const int wg = blockIdx.x;
+    const int l = find_desc(args.n, (int64_t)wg, [&](int k) { return args.L[k].wg_begin; });
+    const GhostLayer& L = args.L[l];
+    const int nT = L.T, d = L.d, p = L.p, sample = wg - L.wg_begin;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int c16 = tid % CPR, rq = tid / CPR;    // this thread's pieces: rows rq + 32 j
+    const int nca = (d + EPC - 1) / EPC, nv = nca + (p + EPC - 1) / EPC;
+    const float* A = reinterpret_cast<const float*>(L.x) + (size_t)sample * nT * d;
+    const float* G = reinterpret_cast<const float*>(L.g) + (size_t)sample * nT * p;
+    float* Pb = L.Pb ? L.Pb + (size_t)sample * p : nullptr;
+
+    // The host guarantees rows of at least 16 bytes and T rows within 32-bit
+    // offsets; rows past T get an out-of-range offset (zeros).
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, (uint32_t)nT * (uint32_t)d * 4u);
+    const __amdgpu_buffer_rsrc_t rg = make_rsrc(G, (uint32_t)nT * (uint32_t)p * 4u);
+    uint32_t oa[NP], og[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const uint32_t row = (uint32_t)(rq + 32 * j);
+        oa[j] = row < (uint32_t)nT ? row * (uint32_t)d * 4u : kGhostOut;
+        og[j] = row < (uint32_t)nT ? row * (uint32_t)p * 4u : kGhostOut;
+    }
+    uint4 pr[NP];
+    auto fetch = [&](int v) {
+        if (v < nca) {
+            const uint32_t kc = 4u * (uint32_t)tail_col<float>(v * EPC + 4 * c16, d);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) pr[j] = buffer_load16(ra, oa[j] == kGhostOut ? kGhostOut : oa[j] + kc);
+        } else {
+            const uint32_t kc = 4u * (uint32_t)tail_col<float>((v - nca) * EPC + 4 * c16, p);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) pr[j] = buffer_load16(rg, og[j] == kGhostOut ? kGhostOut : og[j] + kc);
+        }
+    };
+    // Chunk v from its registers into its buffer.
+    auto store = [&](int v) {
+        const bool isa = v < nca;
+        const int K = isa ? d : p, k = (isa ? v : v - nca) * EPC + 4 * c16;
+        if ((isa ? v + 1 : v - nca + 1) * EPC > K) {      // the rows' last chunk (uniform)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) pr[j] = shift_tail<float>(pr[j], k, K);
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j) buf[v & 1][(rq + 32 * j) * ROWU4 + c16] = pr[j];
+    };
+    // Bias sums of g's chunk in buffer b: wave w adds rows 32 (w / 2) + 0 .. 31
+    // of columns 8 (w mod 2) + 0 .. 7, the four row groups are added after the
+    // next barrier.
+    float bsq = 0.f;
+    auto bias_add = [&](int b) {
+        if (wave / 2 >= NSUB) return;
+        float c[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            add16<float>(buf[b][(32 * (wave >> 1) + 8 * q + (lane & 7)) * ROWU4 + 8 * (wave & 1) + (lane >> 3)], c);
+        const float v = col_reduce8<4>(c, lane);
+        if (!(lane & 1)) cbuf[(wave >> 1) * EPC + 32 * (wave & 1) + (lane >> 1)] = v;
+    };
+    auto bias_done = [&](int ch) {
+        const int k = ch * EPC + tid;
+        if (tid >= EPC || k >= p) return;
+        float v = cbuf[tid];
+#pragma unroll
+        for (int q = 1; q < NSUB; ++q) v += cbuf[q * EPC + tid];
+        Pb[k] = v;
+        bsq += v * v;
+    };
+    f32x16_t acc[2][N];
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[o][t][i] = 0.f;
+    auto chunk = [&](int v, f32x16_t* ac) {
+        lds_barrier();       // chunk v is stored, and nobody reads chunk v - 1 any more
+        if (v > nca && Pb) bias_done(v - 1 - nca);
+        if (v + 1 < nv) store(v + 1);
+        if (v + 2 < nv) fetch(v + 2);
+        const uint4* b = buf[v & 1];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int col = 2 * ((wave & 3) + 4 * s) + h;
+            uint4 fr[NSUB];
+#pragma unroll
+            for (int x = 0; x < NSUB; ++x) fr[x] = b[(32 * x + r) * ROWU4 + col];
+            half_triangle_mma<NSUB, HALF, 0>(ac, fr);
+        }
+        if (v >= nca && Pb) {
+            lds_barrier();   // cbuf of the chunk before has been read
+            bias_add(v & 1);
+        }
+    };
+    if (nv > 0) {
+        fetch(0);
+        store(0);
+    }
+    if (nv > 1) fetch(1);
+    for (int v = 0; v < nca; ++v) chunk(v, acc[0]);
+    for (int v = nca; v < nv; ++v) chunk(v, acc[1]);
+    lds_barrier();
+    if (Pb && nv > nca) bias_done(nv - 1 - nca);
+
+    // Add the four waves' shares of each sub-tile (both halves at once) and
+    // multiply the Grams; off-diagonal sub-tiles count twice.
+    float* shr = reinterpret_cast<float*>(buf);   // [8 waves][16][64]
+    float part = bsq;
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        float4 x[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) shr[(wave * 16 + i) * 64 + lane] = acc[o][t][i];
+            __syncthreads();
+            const float* q = shr + HALF * 4096 + 4 * (tid & 255);
+            x[o] = *reinterpret_cast<const float4*>(q);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const float4 y = *reinterpret_cast<const float4*>(q + 1024 * w);
+                x[o].x += y.x;
+                x[o].y += y.y;
+                x[o].z += y.z;
+                x[o].w += y.w;
+            }
+        }
+        part += (HalfTriangle<NSUB, HALF>::row(t) == HalfTriangle<NSUB, HALF>::col(t) ? 1.f : 2.f) * ((x[0].x * x[1].x + x[0].y * x[1].y) + (x[0].z * x[1].z + x[0].w * x[1].w));
+    }
+    write_part_512(part, red, args.part + (size_t)L.part_off + sample);
+}
+
+template <int NSUB>
+__global__ __launch_bounds__(512, 1) void ghost_mid_f32_kernel(const GhostArgs args) {
+    __shared__ __attribute__((aligned(16))) uint4 buf[2][32 * NSUB * kMidRowU4];
+    __shared__ float cbuf[4 * 64];
+    __shared__ float red[8];
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4) ghost_mid_half<NSUB, 0>(args, buf, cbuf, red);
+    else ghost_mid_half<NSUB, 1>(args, buf, cbuf, red);
+}
+
 // Finishes the column splits: one workgroup per (layer, sample, pair, 32 x 32
 // sub-tile slot) adds the slot's slices of Gram(a) and of Gram(g), each in
 // slice order, and writes the weighted sum of their elementwise product as one
@@ -1280,7 +1470,9 @@ hipError_t launch_ghost(const GhostArgs& args, int n_wg, bool bf16, bool embed, 
             else hipLaunchKernelGGL((ghost_small_kernel<bf16_t, 2>), grid, block, 0, s, args);
         } else {
             if (args.small == 1) hipLaunchKernelGGL((ghost_small_kernel<float, 1>), grid, block, 0, s, args);
-            else hipLaunchKernelGGL((ghost_small_kernel<float, 2>), grid, block, 0, s, args);
+            else if (args.small == 2) hipLaunchKernelGGL((ghost_small_kernel<float, 2>), grid, block, 0, s, args);
+            else if (args.small == 3) hipLaunchKernelGGL(ghost_mid_f32_kernel<3>, grid, dim3(512), 0, s, args);
+            else hipLaunchKernelGGL(ghost_mid_f32_kernel<4>, grid, dim3(512), 0, s, args);
         }
         return hipGetLastError();
     }

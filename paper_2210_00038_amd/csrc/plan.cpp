@@ -32,12 +32,13 @@ GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, bool ali
     const bool vec = aligned && (d * es) % 16 == 0 && (p * es) % 16 == 0;
     if (!bf16 && 4 * 32 * std::max(d, p) < ((int64_t)1 << 31))   // a stage of 32 rows takes 32-bit offsets
         return vec ? GemmVariant::F32 : GemmVariant::F32Any;
-    // bf16 rows of any alignment, 8 columns or more on both sides.
-    if (!vec) return bf16 && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
     // The wide and narrow kernels address one K stage of rows at a time with
-    // 32-bit buffer offsets (rows_rsrc): a stage must fit in 2^31 bytes.
+    // 32-bit offsets (rows_rsrc): a stage must fit in 2^31 bytes.
     (void)rows;
-    if (bf16 && 4 * kWideK * std::max(d, p) * es < ((int64_t)1 << 31)) {
+    const bool stage = bf16 && 4 * kWideK * std::max(d, p) * es < ((int64_t)1 << 31);
+    // bf16 rows of any alignment, 8 columns or more on both sides.
+    if (!vec) return stage && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
+    if (stage) {
         const int64_t lo = std::min(d, p), hi = std::max(d, p);
         if (lo <= 64 && hi >= 128) return lo <= 32 ? GemmVariant::Narrow32 : GemmVariant::Narrow64;
         return GemmVariant::Wide;

@@ -268,3 +268,28 @@ def test_bias_in_whole_sample_ghost(bk, B, T, d, p):
         assert _frob(Pb[i].cpu().numpy(), sb) <= 1e-6
         assert _rel(got[i], ref + (sb ** 2).sum(1)) <= NORM_GUARD
     assert _rel(got[2], ref) <= NORM_GUARD and torch.equal(norm[2], norm[k])
+
+
+# fp32 samples of 64 < T <= 128: three or four 32-row blocks, one chunk of 64
+# columns and several, ragged and short rows, a bias in the same pass.
+@pytest.mark.parametrize("B,T,d,p,off", [
+    (3, 65, 264, 130, 0), (2, 96, 64, 203, 0), (2, 97, 1000, 63, 0), (4, 128, 516, 1030, 0), (2, 100, 3, 700, 0),
+    (3, 128, 256, 192, 1)])
+def test_f32_ghost_whole_sample(bk, B, T, d, p, off):
+    gen = torch.Generator().manual_seed(B + T + d)
+    a, ah = _draw(B, T, d, F32, gen, 1.0, off)
+    g, gh = _draw(B, T, p, F32, gen, 1e-2, off)
+    a[B - 1].zero_()
+    ah[B - 1] = 0
+    ref = oracle.linear_norm_sq(ah, gh)
+    out = bk.bk_ghost_norm(a, g)
+    assert torch.equal(out, bk.bk_ghost_norm(a, g)) and out[B - 1].item() == 0.0
+    assert _rel(out.cpu().numpy()[:B - 1], ref[:B - 1]) <= NORM_GATE["f32"]
+    if not oracle.use_ghost(T, d, p):
+        return
+    Pb, norm = torch.full((B, p), float("nan"), device=DEV), torch.empty(2, B, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "bias": True, "Pb": Pb}, {"x": a, "g": g}])
+    bk.bk_layer_norms(arr, 2, bk.BK_F32, B, norm)
+    sb = oracle.bias_sums(gh)
+    assert _frob(Pb.cpu().numpy(), sb) <= 1e-6 and torch.equal(norm[1], out)
+    assert _rel(norm[0].cpu().numpy(), ref + (sb ** 2).sum(1)) <= NORM_GATE["f32"]
