@@ -63,6 +63,22 @@ template <> struct Mfma<float> {
     }
 };
 
+// Hold the wave until its issued MFMAs have written `acc`.  The hardware does
+// not interlock an MFMA's result against other vector instructions: 12 (bf16)
+// or 18 (float32) wait states have to lie between them.  The compiler counts
+// these along one path only where paths from the MFMA to the read meet again,
+// so a read soon after such a join can come too early (copies of elements
+// 11 .. 15 of a lane's 16 were, and the norms varied from run to run).  To be
+// called after the last MFMA, before any branch that leads to a read.
+template <int N>
+__device__ __forceinline__ void mfma_settle(f32x16_t* acc) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) asm volatile("" : "+v"(acc[t]));
+    asm volatile("s_nop 15\n\ts_nop 3");
+#pragma unroll
+    for (int t = 0; t < N; ++t) asm volatile("" : "+v"(acc[t]));
+}
+
 // Row (within the 32x32 tile) of accumulator element i of lane `lane`; the
 // column is lane % 32.  (Output layout of the 32x32 MFMA family.)
 __device__ __forceinline__ int acc_row(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }

@@ -686,6 +686,7 @@ __device__ __forceinline__ float stream_wave(const FullStream<LPW>& fs, char* ri
         if (sums) bias.add(ring + (v % NSLOT) * SLOTB, v - fs.nca);
         Tiles::compute(ring + (v % NSLOT) * SLOTB, accG);
     }
+    mfma_settle<N>(accG);
     wait_vmcnt<0>();
     if (sums) {
         lds_barrier();
@@ -1106,6 +1107,7 @@ __global__ __launch_bounds__(256, NSUB == 1 ? 3 : 2) void ghost_small_kernel(con
                 Mfma<T>::step(acc[2], x1, x1);
             }
         }
+        mfma_settle<NT>(acc);
         if (!isa && Pb) {
             if (S == 1) bias_one(ch);
             else bias_direct(ch);

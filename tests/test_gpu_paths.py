@@ -149,6 +149,24 @@ def test_ghost_few_tokens(bk, B, T, d, p, off, dtype):
     assert _rel(got[1][:n], ref[:n]) <= _norm_bound(dtype)
 
 
+# Every way the few-token kernel's loop over chunks can end (a's and g's of one
+# chunk, an even and an odd number) and the whole-sample kernel's, without a
+# bias: right, and the same bits from every run.
+@pytest.mark.parametrize("dtype,T,na,ng", [
+    (dt, T, na, ng) for dt, T in ((BF, 1), (F32, 1), (BF, 37), (F32, 37), (BF, 150), (BF, 256))
+    for na, ng in ((1, 1), (2, 1), (1, 2), (2, 2), (3, 1), (2, 3))])
+def test_ghost_chunk_counts(bk, dtype, T, na, ng):
+    chunk = 64 if T > 64 else (256 if T <= 32 else 128) // (1 if dtype == BF else 2)
+    B, d, p = (1151, chunk * na - 3, chunk * ng - 5) if T == 1 else (70, chunk * na, chunk * ng - 8)
+    gen = torch.Generator().manual_seed(T + 10 * na + ng)
+    a, ah = _draw(B, T, d, dtype, gen)
+    g, gh = _draw(B, T, p, dtype, gen, 1e-2)
+    out = bk.bk_ghost_norm(a, g)
+    assert _rel(out.cpu().numpy(), oracle.linear_norm_sq(ah, gh)) <= _norm_bound(dtype)
+    for _ in range(50):
+        assert torch.equal(out, bk.bk_ghost_norm(a, g))
+
+
 # Short vectors over at least 16 samples: 16 interleaved runs of samples per
 # element (64 elements a workgroup); longer vectors or fewer samples: one run.
 @pytest.mark.parametrize("B,n,accum", [
