@@ -216,12 +216,14 @@ def cpu_baseline(w: wl.Workload, budget_s: float = 12.0, single_budget_s: float 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SOURCES = {"agrad_dl_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
-                  "agrad_bf16_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
+                  "agemm_f32_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "agemm_bf16_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "anarrow_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "ghost_norm_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
                   "ghost_full_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
                   "ghost_long_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
+                  "ghost_small_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
+                  "ghost_mid_f32_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
                   "split_reduce_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "embed_join_kernel": "paper_2210_00038_amd/csrc/embed_join.hip",
                   "conv_prep_kernel": "paper_2210_00038_amd/csrc/conv_prep.hip",
@@ -238,14 +240,19 @@ def norm_kernel(L, dtype: str = "bf16", time_rule: bool = False, B: int = 1) -> 
         # 8 | p: the id join; else the masked Gram
         return "embed_join_kernel" if L.T <= 16384 and L.p % 8 == 0 else "ghost_norm_kernel"
     if is_ghost(L, time_rule):
-        if dtype != "bf16" or L.T <= 128:
+        if L.T <= 64:
+            return "ghost_small_kernel"
+        if dtype != "bf16":
+            return "ghost_mid_f32_kernel" if L.T <= 128 else "ghost_norm_kernel"
+        if L.T <= 128:
             return "ghost_norm_kernel"
         return "ghost_full_kernel" if L.T <= 256 else "ghost_long_kernel"
     if dtype != "bf16":
-        return "agemm_kernel"
+        return "agemm_f32_kernel"
     if _narrow(L):
         return "anarrow_kernel"
-    # whole 256 x 256 tiles on the DMA kernel when the layer gives at least 128 of them
+    # 256 x 256 tiles on the DMA kernel when the call's layers give at least 128 of
+    # them; counted here for this layer alone
     tiles = -(-L.d // 256) * -(-L.p // 256)
     if L.T >= 64 and 8 * (-(-L.T // 16) * 16) <= 9 * L.T and B * tiles >= 128:
         return "agrad_dl_kernel"
@@ -257,13 +264,10 @@ def grad_kernel(L, dtype: str = "bf16") -> str:
     if L.kind == "embed":
         return "embed_rows_kernel"
     if dtype != "bf16":
-        return "agemm_kernel"
-    if L.T < 64:
-        return "agemm_bf16_kernel"
+        return "agemm_f32_kernel"
     if _narrow(L):
-        return "anarrow_kernel"
-    # the DMA kernel pads each sample to 16-row steps; it takes T when that adds at most 1/8
-    return "agrad_dl_kernel" if 8 * (-(-L.T // 16) * 16) <= 9 * L.T else "agrad_bf16_kernel"
+        return "agemm_bf16_kernel" if L.T < 64 else "anarrow_kernel"
+    return "agrad_dl_kernel"
 
 
 def dominant_kernel(w: wl.Workload, phase: str, time_rule: bool = False) -> str:
