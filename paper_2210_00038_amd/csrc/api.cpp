@@ -157,7 +157,7 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
         np.npart = 0;
         np.var = 0;
     } else if (np.path == Path::Inst) {
-        const auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, L.T, aligned16(L.x) && aligned16(L.g));
+        const auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, 0, aligned16(L.x) && aligned16(L.g));
         const bk::GemmGeom geo = bk::gemm_geom(v, L.d, L.p);
         np.var = (int)v;
         np.tiles = geo.tm * geo.tn;
@@ -732,7 +732,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
 // sample to 16-row steps adds at most 1/8 to its rows, else with the weights on
 // g's fragments over the flat rows of the batch (Grad).
 bk::GemmVariant grad_variant(const bk_layer& L, bool bf16, int64_t B) {
-    const auto v = bk::gemm_variant(bf16, L.d, L.p, B * L.T, aligned16(L.x) && aligned16(L.g));
+    const auto v = bk::gemm_variant(bf16, L.d, L.p, B, aligned16(L.x) && aligned16(L.g));
     if (is_narrow(v)) return L.T < 64 ? bk::GemmVariant::Wide : v;   // narrow kernel: T >= 64
     if (v != bk::GemmVariant::Wide || B > bk::kDMaxB) return v;
     return L.T >= 64 && dl_padding_ok(L.T) ? bk::GemmVariant::GradDL : bk::GemmVariant::Grad;

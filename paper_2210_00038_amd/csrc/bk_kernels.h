@@ -134,9 +134,9 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 
 // Kernel variant of the a^T g GEMMs for one layer:
 //  Scalar: element loads, 128 x 128 (unaligned bf16 rows of fewer than 8
-//          columns, rows past 2^26 bytes);
-//  Vec   : 16-byte loads, register transpose, 128 x 128 (rows past 2^23 bytes
-//          in bf16, 2^26 in fp32);
+//          columns; fp32 past F32's limits);
+//  Vec   : 16-byte loads, register transpose, 128 x 128 (bf16 rows past 2^23
+//          bytes; fp32 past F32's limits);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
 //  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads, LDS DMA,
 //          the weights on g's fragments (B <= kDMaxB);
@@ -145,12 +145,14 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 //  Narrow32 / Narrow64: bf16, one side of d x p at most 32 / 64, tiles of
 //          256 along the long side (operands swapped when d < p).
 //  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns;
-//  F32 / F32Any: fp32, LDS DMA, 128 x 128; 16-byte rows / rows of any alignment.
+//  F32 / F32Any: fp32, LDS DMA, 128 x 128; 16-byte rows / rows of any alignment
+//          (rows up to 2^26 bytes, B <= kF32MaxB).
 enum class GemmVariant {
     Scalar = 0, Vec = 1, Wide = 2, Grad = 3, GradDL = 4, Narrow32 = 5, Narrow64 = 6, WideAny = 7, F32 = 8, F32Any = 9
 };
 constexpr int kGemmVariants = 10;
 constexpr int kDMaxB = 4096;
+constexpr int64_t kF32MaxB = (int64_t)1 << 29;   // fp32 kernel: C within 32-bit byte offsets
 constexpr int kDLStageRows = 32;   // k rows per stage of the GradDL kernel
 constexpr int kDLBuffers = 4;      // its LDS stage buffers (the ping-pong schedule takes four)
 // Output tiles of the a^T g kernels (plan.cpp and the kernels share them):
@@ -159,7 +161,8 @@ constexpr int kDLBuffers = 4;      // its LDS stage buffers (the ping-pong sched
 constexpr int kWideM = 256, kWideN = 128, kWideK = 64;
 constexpr int kGradM = 256, kGradN = 256;
 constexpr int kNarrowM = 256;
-GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, bool aligned);
+// `weights`: the clip weights that the launch reads (0: an instantiated norm).
+GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t weights, bool aligned);
 // Output tiles of a d x p layer on variant v: tm x tn tiles of tile_elems
 // floats (a K-split partial tile), rows along p when swap.
 struct GemmGeom {

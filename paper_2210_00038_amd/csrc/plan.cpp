@@ -27,14 +27,14 @@ GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p) {
     }
 }
 
-GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, bool aligned) {
+GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t weights, bool aligned) {
     const int64_t es = bf16 ? 2 : 4;
     const bool vec = aligned && (d * es) % 16 == 0 && (p * es) % 16 == 0;
-    if (!bf16 && 4 * 32 * std::max(d, p) < ((int64_t)1 << 31))   // a stage of 32 rows takes 32-bit offsets
+    // 32-bit offsets: a stage of 32 rows, and the clip weights.
+    if (!bf16 && 4 * 32 * std::max(d, p) < ((int64_t)1 << 31) && weights <= kF32MaxB)
         return vec ? GemmVariant::F32 : GemmVariant::F32Any;
     // The wide and narrow kernels address one K stage of rows at a time with
     // 32-bit offsets (rows_rsrc): a stage must fit in 2^31 bytes.
-    (void)rows;
     const bool stage = bf16 && 4 * kWideK * std::max(d, p) * es < ((int64_t)1 << 31);
     // bf16 rows of any alignment, 8 columns or more on both sides.
     if (!vec) return stage && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;

@@ -148,6 +148,18 @@ int main() {
         (void)bk_weighted_grad(a, g, nullptr, dt, -B - 1, T, d, p, out, nullptr, 0, nullptr);
         (void)bk_layer_norms(nullptr, 3, dt, B, out, nullptr, 0, nullptr);
     }
+    {   // batches of a thousand million one-token samples
+        for (int64_t B : {(int64_t)1 << 28, ((int64_t)1 << 30) - 4, (int64_t)1 << 30, (int64_t)INT32_MAX})
+            for (int64_t d : {1, 4}) {
+                const size_t w = bk_workspace_size(BK_OP_WEIGHTED_GRAD, BK_F32, B, 1, d, 4);
+                float* out = static_cast<float*>(fake(3));
+                const bk_status st = bk_weighted_grad(fake(1), fake(2), out, BK_F32, B, 1, d, 4, out, set_ws(w), w, nullptr);
+                if (st != BK_OK) {
+                    std::fprintf(stderr, "a clipped gradient of %lld samples was refused\n", (long long)B);
+                    return 1;
+                }
+            }
+    }
     {   // grouped noise over many tensors (more than one launch's table)
         std::vector<float*> G(400);
         std::vector<int64_t> nel(400);

@@ -93,6 +93,9 @@ hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant
         const GemmGeom geo = gemm_geom(v, L.d, L.p);
         need(L.tm == geo.tm && L.tn == geo.tn, "gemm tiles");
         const int64_t tiles = (int64_t)L.tm * L.tn;
+        // the fp32 kernel reads C through a 32-bit buffer descriptor
+        if (!inst && (v == GemmVariant::F32 || v == GemmVariant::F32Any))
+            need((uint64_t)a.B * 4 < 0xFFFFFFF0u, "fp32 clip weights within 32-bit offsets");
         if (inst && v == GemmVariant::GradDL) {
             // one workgroup per (sample, tile), never split, no clip weights
             need(L.ksplit <= 1 && a.C == nullptr && (int64_t)a.B * L.T < ((int64_t)1 << 31) && L.T >= 64,
