@@ -719,7 +719,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
             r.L[k].part_off2 = (int32_t)(it.part_off + B * it.np.npart);
             r.L[k].npart2 = (int32_t)it.np.aff_chunks;
         }
-        hipError_t e = bk::launch_reduce(r, (int)(cnt * B), s);
+        hipError_t e = bk::launch_reduce(r, s);
         if (e != hipSuccess) return hip_fail(e, "norm reduction launch");
     }
     return BK_OK;
@@ -1205,7 +1205,7 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
     r.L[0].out = norm_sq;
     r.L[0].part_off = 0;
     r.L[0].npart = (int32_t)np.npart;
-    e = bk::launch_reduce(r, (int)B, s);
+    e = bk::launch_reduce(r, s);
     return e == hipSuccess ? BK_OK : hip_fail(e, "norm reduction launch");
 }
 

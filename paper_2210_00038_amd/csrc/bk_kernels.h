@@ -114,6 +114,15 @@ struct ReduceArgs {
     ReduceLayer L[kMaxReduce];
 };
 
+// Grid of the reduction with clip factors (n <= kMaxReduce layers): a workgroup
+// of kReducePairs threads takes kReducePairs / n whole samples; thread t of
+// workgroup wg sums layer t / (kReducePairs / n) of the sample given here.  All
+// in 64 bits: the last workgroup's samples may pass 2^31.
+constexpr int kReducePairs = 256;
+static_assert(kMaxReduce <= kReducePairs, "one thread per (layer, sample)");
+constexpr int64_t reduce_clip_wgs(int n, int64_t B) { return (B + kReducePairs / n - 1) / (kReducePairs / n); }
+constexpr int64_t reduce_clip_sample(uint32_t wg, int per_wg, int t) { return (int64_t)wg * per_wg + t % per_wg; }
+
 // ---- noise ------------------------------------------------------------------
 struct NoiseLayer {
     float* G;
@@ -257,7 +266,7 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
 // the split layers' reduction workgroups.
 hipError_t launch_split_reduce(const GemmArgs& args, int n_wg, bool inst_norm, GemmVariant v,
                                hipStream_t s);
-hipError_t launch_reduce(const ReduceArgs& args, int n_threads, hipStream_t s);
+hipError_t launch_reduce(const ReduceArgs& args, hipStream_t s);
 hipError_t launch_clip(const float* norm_sq, int64_t L, int64_t B, int mode, float R, float gamma,
                        float* C, float* total_sq, hipStream_t s);
 hipError_t launch_noise(const NoiseArgs& args, int n_wg, hipStream_t s);

@@ -51,18 +51,16 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs args) {
 // as clip_kernel).  Both are launch latency: the two kernels took 4.3 us (one
 // layer, 4 samples) to 11.7 us (21 layers, split ones among them), this one
 // 2.2 to 5.3.
-constexpr int kPairs = 256;
-static_assert(kMaxReduce <= kPairs, "one thread per (layer, sample)");
-__global__ __launch_bounds__(kPairs) void reduce_clip_kernel(const ReduceArgs args, int per_wg) {
-    __shared__ float norm[kPairs];
-    const int i0 = blockIdx.x * per_wg, l = threadIdx.x / per_wg, j = threadIdx.x - l * per_wg;
-    if (l < args.n && i0 + j < args.B) {
-        const float s = reduce_partials(args, args.L[l], i0 + j);
-        args.L[l].out[i0 + j] = s;
+__global__ __launch_bounds__(kReducePairs) void reduce_clip_kernel(const ReduceArgs args, int per_wg) {
+    __shared__ float norm[kReducePairs];
+    const int l = threadIdx.x / per_wg;
+    const int64_t i = reduce_clip_sample(blockIdx.x, per_wg, threadIdx.x);
+    if (l < args.n && i < args.B) {
+        const float s = reduce_partials(args, args.L[l], (int)i);
+        args.L[l].out[i] = s;
         norm[threadIdx.x] = s;
     }
     __syncthreads();
-    const int i = i0 + threadIdx.x;
     if ((int)threadIdx.x >= per_wg || i >= args.B) return;
     double s = 0.0;
     for (int k = 0; k < args.n; ++k) s += (double)norm[k * per_wg + threadIdx.x];
@@ -150,14 +148,15 @@ __global__ __launch_bounds__(256) void philox_raw_kernel(uint64_t seed, uint32_t
 
 }  // namespace
 
-hipError_t launch_reduce(const ReduceArgs& args, int n_threads, hipStream_t s) {
-    if (n_threads <= 0) return hipSuccess;
+hipError_t launch_reduce(const ReduceArgs& args, hipStream_t s) {
+    if (args.n <= 0 || args.B <= 0) return hipSuccess;
     if (args.C) {
-        const int per_wg = kPairs / args.n;
-        hipLaunchKernelGGL(reduce_clip_kernel, dim3((args.B + per_wg - 1) / per_wg), dim3(kPairs), 0, s, args, per_wg);
+        hipLaunchKernelGGL(reduce_clip_kernel, dim3((unsigned)reduce_clip_wgs(args.n, args.B)), dim3(kReducePairs), 0,
+                           s, args, kReducePairs / args.n);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(reduce_kernel, dim3((n_threads + 255) / 256), dim3(256), 0, s, args);
+    const int64_t threads = (int64_t)args.n * args.B;
+    hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, args);
     return hipGetLastError();
 }
 

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "bk.h"
+#include "bk_kernels.h"
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
@@ -160,6 +161,19 @@ int main() {
                 }
             }
     }
+    // the fused reduction's grid covers every sample once, threads past the
+    // batch stay past it, up to the largest batch
+    for (int64_t B : {(int64_t)1, (int64_t)255, (int64_t)257, (int64_t)INT32_MAX - 255, (int64_t)INT32_MAX})
+        for (int n : {1, 2, 3, 85, 129, bk::kMaxReduce}) {
+            const int per = bk::kReducePairs / n;
+            const int64_t wgs = bk::reduce_clip_wgs(n, B);
+            const int64_t first = bk::reduce_clip_sample((uint32_t)(wgs - 1), per, 0);
+            const int64_t last = bk::reduce_clip_sample((uint32_t)(wgs - 1), per, 2 * per - 1);
+            if (first >= B || first + per < B || last != first + per - 1 || per * n > bk::kReducePairs) {
+                std::fprintf(stderr, "fused reduction grid: B=%lld n=%d\n", (long long)B, n);
+                return 1;
+            }
+        }
     {   // grouped noise over many tensors (more than one launch's table)
         std::vector<float*> G(400);
         std::vector<int64_t> nel(400);
