@@ -295,49 +295,61 @@ void demote_small_full(std::vector<NormPlan>& plans, const bk_layer* layers, int
 // 50257 columns and 8 samples ran on 8 of 256 CUs).  When all such layers of a
 // call give fewer than kGhostSplitBelow workgroups, their rows are cut into
 // column slices towards kGhostSplitTo workgroups, each slice at least
-// kGhostSplitChunks 128-byte chunks wide (its partial Gram, 48 KB written and
-// read back through the caches, against 256 KB of rows streamed), if that
-// gives at least kGhostSplitMin of them: the second kernel takes 15 us or more,
-// so that two slices for each of 96 workgroups lost (27 us against 21 + 18).
-// The partial Grams are only taken while the norms' workspace stays within
-// kGhostSplitWs, so that a call that fits the allocation-free scratch without
-// them still does.
+// kGhostSplitChunks 128-byte chunks wide (its partial Gram, at most 64 KB
+// written and read back through the caches, against 256 KB of rows streamed), if
+// that gives at least kGhostSplitMin of them: the second kernel takes 15 us or
+// more, so that two slices for each of 96 workgroups lost (27 us against 21 + 18).
+// Norms of a head 768 -> 50257 at T = 128, 8 / 16 / 32 / 63 samples: bf16 43 / 59
+// / 113 / 202 us (whole rows: 513 at 16, 679 at 32), fp32 123 / 230 / 439 / 908
+// (whole rows: 5595 at 16).
+// All optional slices of a call keep the norms' workspace within kSliceWs, so
+// that a call that fits the allocation-free scratch without them still does:
+// where the partial Grams do not fit, each pair takes fewer slices.
 constexpr int64_t kGhostSplitBelow = 64, kGhostSplitTo = 512, kGhostSplitMin = 4, kGhostSplitChunks = 16, kGhostSplitMax = 64;
-constexpr size_t kGhostSplitWs = (size_t)32 << 20;
+constexpr size_t kSliceWs = BK_NOALLOC_SCRATCH_BYTES;
 void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     auto small = [](const NormPlan& np) { return np.path == Path::Ghost && np.var <= 1 && np.nwg > 0; };
     int64_t wg = 0;
     for (const NormPlan& np : plans) wg += small(np) ? np.nwg : 0;
     if (wg == 0 || wg >= kGhostSplitBelow) return;
     const int64_t epc = 128 / (int64_t)elem_bytes(dt);
-    std::vector<NormPlan> split = plans;
-    size_t need = 0;
-    for (size_t l = 0; l < plans.size(); ++l) {
-        NormPlan& np = split[l];
-        if (small(np)) {
-            const int64_t ca = cdiv(layers[l].d, epc), cg = cdiv(layers[l].p, epc);
-            const int64_t ks = std::min({kGhostSplitTo / wg, (ca + cg) / kGhostSplitChunks, kGhostSplitMax});
-            if (ks >= kGhostSplitMin && ca > 0 && cg > 0) {
-                np.ksplit = ks;
-                np.ka = std::clamp<int64_t>((2 * ks * ca + ca + cg) / (2 * (ca + cg)), 1, ks - 1);
-                finish_norm_plan(np, layers[l], B);
+    size_t whole = 0;
+    for (const NormPlan& np : plans) whole += norm_ws_bytes(np, B);
+    if (whole > kSliceWs) return;
+    for (int64_t most = std::min(kGhostSplitTo / wg, kGhostSplitMax); most >= kGhostSplitMin; --most) {
+        std::vector<NormPlan> split = plans;
+        size_t need = 0;
+        for (size_t l = 0; l < plans.size(); ++l) {
+            NormPlan& np = split[l];
+            if (small(np)) {
+                const int64_t ca = cdiv(layers[l].d, epc), cg = cdiv(layers[l].p, epc);
+                const int64_t ks = std::min(most, (ca + cg) / kGhostSplitChunks);
+                if (ks >= kGhostSplitMin && ca > 0 && cg > 0) {
+                    np.ksplit = ks;
+                    np.ka = std::clamp<int64_t>((2 * ks * ca + ca + cg) / (2 * (ca + cg)), 1, ks - 1);
+                    finish_norm_plan(np, layers[l], B);
+                }
             }
+            need += norm_ws_bytes(np, B);
         }
-        need += norm_ws_bytes(np, B);
+        if (need <= kSliceWs) {
+            plans.swap(split);
+            return;
+        }
     }
-    if (need <= kGhostSplitWs) plans.swap(split);
 }
 
 // The few-token kernel streams the whole rows of its samples in one
 // workgroup; layers of long rows (d + p of kSmallLongRow bytes or more) whose
 // launch gives fewer than kGhostSplitBelow workgroups go back to the pair
-// kernel, which split_small_ghost cuts into column slices.  So do all of them
-// when they would not fill the chip in a launch of their own next to one of
-// the pair kernel (kSmallMixedBelow workgroups, at most kSmallMixedB samples:
-// the late layers and the classifier of ResNet-18 with 16 samples, 53 us in one
-// launch against 29 + 33 + 12 us in three).
+// kernel where split_small_ghost cuts them into column slices, and stay where it
+// does not (8192 -> 8192, 200 samples of 2 tokens: 41 us here, 111 on the pair
+// kernel's whole rows).  So do all of them when they would not fill the chip in a launch of
+// their own next to one of the pair kernel (kSmallMixedBelow workgroups, at most
+// kSmallMixedB samples: the late layers and the classifier of ResNet-18 with 16
+// samples, 53 us in one launch against 29 + 33 + 12 us in three).
 constexpr int64_t kSmallLongRow = 16384, kSmallMixedBelow = 256, kSmallMixedB = 64;
-void demote_few_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+void split_few_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     int64_t wg = 0, pair = 0;
     for (const NormPlan& np : plans) {
         if (np.path != Path::Ghost) continue;
@@ -345,15 +357,20 @@ void demote_few_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_d
         else if (np.var <= 1) pair += np.nwg;
     }
     const bool mixed = pair > 0 && wg < kSmallMixedBelow && B <= kSmallMixedB;
-    if (wg == 0 || (wg >= kGhostSplitBelow && !mixed)) return;
-    for (size_t l = 0; l < plans.size(); ++l) {
-        NormPlan& np = plans[l];
-        const bk_layer& L = layers[l];
-        const int64_t es = (int64_t)elem_bytes(dt);
-        if (np.path != Path::Ghost || np.var < 4 || (!mixed && (L.d + L.p) * es < kSmallLongRow)) continue;
-        np.var = ghost_rows16(L, dt) ? 1 : 0;
-        finish_norm_plan(np, L, B);
-    }
+    const std::vector<NormPlan> before = plans;
+    if (wg > 0 && (wg < kGhostSplitBelow || mixed))
+        for (size_t l = 0; l < plans.size(); ++l) {
+            NormPlan& np = plans[l];
+            const bk_layer& L = layers[l];
+            const int64_t es = (int64_t)elem_bytes(dt);
+            if (np.path != Path::Ghost || np.var < 4 || (!mixed && (L.d + L.p) * es < kSmallLongRow)) continue;
+            np.var = ghost_rows16(L, dt) ? 1 : 0;
+            finish_norm_plan(np, L, B);
+        }
+    split_small_ghost(plans, layers, dt, B);
+    if (!mixed)
+        for (size_t l = 0; l < plans.size(); ++l)
+            if (before[l].path == Path::Ghost && before[l].var >= 4 && plans[l].ksplit == 1) plans[l] = before[l];
 }
 
 // fp32 instantiated norms: one workgroup per (sample, tile), a 16-row stage of
@@ -362,7 +379,7 @@ void demote_few_small(std::vector<NormPlan>& plans, const bk_layer* layers, bk_d
 // long after the others (the stem of a ResNet: one or two tiles per sample over
 // thousands of rows): its tiles are cut into slices of about S stages, at
 // least kF32InstStages.  As for the column slices, only while the norms'
-// workspace stays within kGhostSplitWs.
+// workspace stays within kSliceWs.
 constexpr int64_t kF32InstSlots = 384, kF32InstStages = 16;
 void split_long_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B) {
     auto f32 = [](const NormPlan& np) {
@@ -386,7 +403,7 @@ void split_long_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers, i
         }
         need += norm_ws_bytes(np, B);
     }
-    if (any && need <= kGhostSplitWs) plans.swap(split);
+    if (any && need <= kSliceWs) plans.swap(split);
 }
 
 // bf16 instantiated norms on the 256 x 256 tiles of the LDS-DMA kernel (one
@@ -426,8 +443,7 @@ void promote_inst_dl(std::vector<NormPlan>& plans, const bk_layer* layers, int64
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     promote_inst_dl(plans, layers, B);
     demote_small_full(plans, layers, B);
-    demote_few_small(plans, layers, dt, B);
-    split_small_ghost(plans, layers, dt, B);
+    split_few_ghost(plans, layers, dt, B);
     if (dt == BK_F32) split_long_f32_inst(plans, layers, B);
 }
 

@@ -3,6 +3,7 @@
 // launchers stubbed (launch_stubs.cpp).  Device pointers are fake, aligned
 // addresses: the host code never dereferences them.  Prints "ok" and exits 0
 // when every call returned (sanitizer reports abort the run).
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -14,6 +15,7 @@
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
+extern long g_ghost_wgs;
 extern std::map<uintptr_t, int> g_noised;
 
 namespace {
@@ -160,6 +162,48 @@ int main() {
                     return 1;
                 }
             }
+    }
+    // long rows, few samples: the rows are cut into column slices at every batch
+    for (const bk_dtype dt : {BK_BF16, BK_F32})
+        for (int64_t B = 1; B < 64; ++B) {
+            struct { int64_t T, d, p; } const heads[] = {{128, 768, 50257}, {128, 768, 50264}, {100, 2048, 128256}, {128, 768, 8192},
+                                                         {50, 4096, 6000}, {128, 770, 50257}};
+            for (const auto& h : heads) {
+                if (h.p * B * h.T > INT32_MAX) continue;
+                bk_layer y{};
+                y.kind = BK_LINEAR;
+                y.T = h.T;
+                y.d = h.d;
+                y.p = h.p;
+                y.x = fake(1);
+                y.g = fake(2);
+                const size_t w = bk_layer_norms_workspace_size(&y, 1, dt, B);
+                g_ghost_wgs = 0;
+                const bk_status st = bk_layer_norms(&y, 1, dt, B, static_cast<float*>(fake(3)), set_ws(w), w, nullptr);
+                // at least 4 slices a sample, and towards 512 where 128-byte chunks allow 16 to a slice
+                const int64_t epc = dt == BK_BF16 ? 64 : 32, ch = (h.d + epc - 1) / epc + (h.p + epc - 1) / epc;
+                const int64_t want = B * std::min({(int64_t)64, ch / 16, 512 / B});
+                if (st != BK_OK || g_ghost_wgs < want) {
+                    std::fprintf(stderr, "column slices: dtype %d B=%lld T=%lld %lld -> %lld: %ld workgroups, %lld wanted\n", (int)dt,
+                                 (long long)B, (long long)h.T, (long long)h.d, (long long)h.p, g_ghost_wgs, (long long)want);
+                    return 1;
+                }
+            }
+        }
+    // few tokens of long rows whose pairs get no slices stay on the few-token
+    // kernel (32 / T samples to a workgroup)
+    for (const bk_dtype dt : {BK_BF16, BK_F32}) {
+        bk_layer y{};
+        y.kind = BK_LINEAR;
+        y.T = 2;
+        y.d = y.p = 8192;
+        y.x = fake(1);
+        y.g = fake(2);
+        const size_t w = bk_layer_norms_workspace_size(&y, 1, dt, 200);
+        if (bk_layer_norms(&y, 1, dt, 200, static_cast<float*>(fake(3)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs != 13) {
+            std::fprintf(stderr, "few tokens of long rows: %ld workgroups\n", g_ghost_wgs);
+            return 1;
+        }
     }
     // the fused reduction's grid covers every sample once, threads past the
     // batch stay past it, up to the largest batch

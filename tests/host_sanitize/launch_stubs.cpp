@@ -17,6 +17,7 @@
 
 uintptr_t g_ws_lo = 0, g_ws_hi = 0;   // [lo, hi): the caller's workspace
 long g_launches = 0;
+long g_ghost_wgs = 0;                 // workgroups of the last ghost-norm launch
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
 namespace {
@@ -70,8 +71,21 @@ hipError_t launch_ghost_full(const GhostArgs& a, int n_wg, bool, hipStream_t) {
 }
 hipError_t launch_ghost(const GhostArgs& a, int n_wg, bool, bool, bool, hipStream_t) {
     ++g_launches;
+    g_ghost_wgs = n_wg;
     monotone(a.L, a.n, kMaxGhost, n_wg, "ghost descriptors");
-    for (int k = 0; k < a.n; ++k) in_ws(a.part, a.L[k].part_off, (int64_t)a.B * a.L[k].npairs, 4, "ghost partials");
+    int64_t red = 0;
+    for (int k = 0; k < a.n; ++k) {
+        const GhostLayer& L = a.L[k];
+        in_ws(a.part, L.part_off, (int64_t)a.B * L.npairs, 4, "ghost partials");
+        need(L.red_begin == red, "ghost slice reduction");
+        if (L.ksplit <= 1) continue;
+        // column slices: every pair's partial Grams, and kGhostSplitParts partials
+        const int64_t pairs = (int64_t)L.nsb * (L.nsb + 1) / 2;
+        need(L.npairs == pairs * kGhostSplitParts && L.ka >= 1 && L.ka < L.ksplit && !L.Pb, "ghost slices");
+        in_ws(a.tiles, L.tile_off, a.B * pairs * L.ksplit * kGhostSplitTile, 4, "ghost partial Grams");
+        red += (int64_t)a.B * L.npairs;
+    }
+    need(a.n_red == red && (red == 0 || !a.small), "ghost slice reduction grid");
     return hipSuccess;
 }
 hipError_t launch_embed_join(const GhostArgs& a, int n_wg, bool, int ct, hipStream_t) {
