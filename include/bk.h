@@ -25,7 +25,11 @@
  *  - Tensor pointers are DEVICE pointers owned by the caller; the library never
  *    allocates, frees or keeps them.  Workspaces are caller-provided device
  *    buffers of at least the size the matching *_workspace_size call returns
- *    (a NULL workspace is accepted when that size is 0).
+ *    (a NULL workspace is accepted when that size is 0).  The size for a
+ *    batch of B samples, B <= 4096, also serves every smaller batch of the same
+ *    layers, with one exception: bf16 layers whose norms are instantiated cut
+ *    their contraction into K slices when a batch gives few output tiles, so
+ *    with such layers the size has to be asked for each batch size.
  *  - Layout: row-major, contiguous.  a is [B, T, d], g = dL/ds is [B, T, p]
  *    (sample-major, then token, then feature), both of the dtype `dt`; token
  *    ids are int64 [B, T].  Outputs are float32 and are OVERWRITTEN.  Outputs

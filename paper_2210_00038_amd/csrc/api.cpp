@@ -124,9 +124,10 @@ int64_t inst_ksplit(int64_t B, int64_t tiles, int64_t T) {
 }
 
 // K slices of a clipped-gradient tile (agrad kernels): a layer with fewer than
-// 8 output tiles and at least 64 stages gets slices of about 32 stages.
+// 8 output tiles and at least kOwnMinStages stages gets slices of about 32 stages.
+constexpr int64_t kOwnMinStages = 64;
 int64_t grad_ksplit(int64_t tiles, int64_t nst) {
-    if (tiles >= 8 || nst < 64) return 1;
+    if (tiles >= 8 || nst < kOwnMinStages) return 1;
     return std::min<int64_t>(256, cdiv(nst, 32));
 }
 
@@ -151,7 +152,7 @@ bool ghost_rows16(const bk_layer& L, bk_dtype dt) {
            (L.T + bk::kSuper) * std::max(L.d, L.p) * es < ((int64_t)1 << 31);
 }
 
-void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
+void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt) {
     const size_t es = elem_bytes(dt);
     if (np.path == Path::Affine) {
         np.npart = 0;
@@ -266,7 +267,7 @@ NormPlan norm_plan(const bk_layer& L, bk_dtype dt, int64_t B) {
     } else {
         np.path = layer_ghost(L) ? Path::Ghost : Path::Inst;
     }
-    set_norm_variant(np, L, dt, B);
+    set_norm_variant(np, L, dt);
     finish_norm_plan(np, L, B);
     return np;
 }
@@ -512,10 +513,55 @@ bk_status check_layer(const char* fn, const bk_layer& L, int64_t l, int64_t B, b
 // ---------------------------------------------------------------------------
 // Grouped execution
 // ---------------------------------------------------------------------------
+// Workspace of the norms: what the plans take, or, where a smaller batch would
+// take optional slices (split_small_ghost, split_long_f32_inst), what it would at
+// most: a workspace sized for the full batch then serves a smaller last one.
+// As the slices themselves, the reserve ends at kSliceWs.  (Not covered: the K
+// slices of bf16 instantiated layers, inst_ksplit, whose partial tiles at B = 1
+// can be gigabytes.)
+size_t norms_ws(const std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
+    size_t exact = 0, whole = 0, small = 0;
+    int64_t ghost = 0, inst = 0;     // partial Grams, fp32 partial tiles of a smaller batch at most
+    const int64_t epc = 128 / (int64_t)elem_bytes(dt);
+    for (size_t l = 0; l < plans.size(); ++l) {
+        const bk_layer& L = layers[l];
+        NormPlan np = plans[l];
+        exact += norm_ws_bytes(np, B);
+        const bool f32inst = dt == BK_F32 && np.path == Path::Inst;
+        if (np.path == Path::Ghost || f32inst) {       // before the launch-wide choices
+            np.ksplit = 1;
+            set_norm_variant(np, L, dt);
+            finish_norm_plan(np, L, B);
+        }
+        whole += norm_ws_bytes(np, B);
+        if (B == 0 || L.T == 0) continue;
+        const int64_t nsb = cdiv(L.T, bk::kSuper), pairs = nsb * (nsb + 1) / 2, st = cdiv(L.T, 16);
+        if (np.path == Path::Ghost && np.var != 3 && pairs < kGhostSplitBelow) {
+            const int64_t ca = cdiv(L.d, epc), cg = cdiv(L.p, epc);
+            const int64_t ks = std::min((ca + cg) / kGhostSplitChunks, kGhostSplitMax);
+            const int64_t bias = (L.flags & BK_LAYER_BIAS) ? cdiv(L.p, bk::kAffineCols) : 0;
+            int64_t parts = 0;
+            if (ks >= kGhostSplitMin) {
+                ghost += std::min(B, (kGhostSplitBelow - 1) / pairs) * pairs * ks;
+                parts = kGhostSplitBelow * bk::kGhostSplitParts;
+            }
+            // the pair kernel's own partials, and bias sums apart
+            if (np.var == 2) parts += std::min(B, kFullMinWG) * (pairs + bias);
+            else if (np.fused_bias) parts += std::min(B, kGhostSplitBelow) * bias;
+            small += align_up((size_t)parts * sizeof(float));
+        } else if (f32inst && st >= 2 * kF32InstStages) {
+            inst += B * np.tiles * (st / kF32InstStages);
+            small += align_up((size_t)(kF32InstSlots * (np.tile_elems / bk::kSplitRedWG)) * sizeof(float));
+        }
+    }
+    const int64_t tiles = std::min(ghost, kGhostSplitTo) * bk::kGhostSplitTile +
+                          std::min(inst, kF32InstSlots) * bk::kTile * bk::kTile;
+    const size_t reserved = whole + small + (size_t)tiles * sizeof(float);
+    return std::max(exact, std::min(reserved, kSliceWs));
+}
+
 size_t layer_norms_ws(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t B) {
-    size_t tot = 0;
-    for (const NormPlan& np : norm_plans(layers, n, dt, B)) tot += norm_ws_bytes(np, B);
-    return tot;
+    return norms_ws(norm_plans(layers, n, dt, B), layers, dt, B);
 }
 
 // The clip factors that follow the norms (bk_private_grad).
@@ -539,7 +585,8 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
     for (int64_t l = 0; l < n; ++l)
         if ((st = check_layer(fn, layers[l], l, B, false)) != BK_OK) return st;
     if (n * B > 0 && !norm_sq) return fail(BK_ERR_INVALID_VALUE, "%s: NULL norm output", fn);
-    const size_t need = layer_norms_ws(layers, n, dt, B);
+    const std::vector<NormPlan> plans = norm_plans(layers, n, dt, B);
+    const size_t need = norms_ws(plans, layers, dt, B);
     if (ws_bytes < need || (need > 0 && !ws))
         return fail(BK_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", fn, ws_bytes, need);
     if ((size_t)need / sizeof(float) > (size_t)INT32_MAX)
@@ -556,7 +603,6 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
     std::vector<Item> items;
     items.reserve((size_t)n);
     int64_t off = 0, toff = 0;
-    const std::vector<NormPlan> plans = norm_plans(layers, n, dt, B);
     for (int64_t l = 0; l < n; ++l) {
         const NormPlan& np = plans[(size_t)l];
         items.push_back({l, np, off, toff});
@@ -764,7 +810,7 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // samples: 14 + 10 us in one launch and 29 in two; 36 encoder layers of 64 x 37
 // rows, 648 tiles: 265 us against 295-310).
 constexpr int64_t kFlatMinTiles = 128, kFlatMinRows = 4096;
-std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B) {
+std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows) {
     std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
     int64_t tiles = 0, rows = 0;
     auto flat = [&](int64_t l) { return v[(size_t)l] == bk::GemmVariant::Grad && layers[l].T < 64; };
@@ -776,7 +822,7 @@ std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bo
         tiles += geo.tm * geo.tn;
         rows = std::max(rows, B * layers[l].T);
     }
-    if (tiles < kFlatMinTiles && rows < kFlatMinRows)
+    if (tiles < kFlatMinTiles && (rows < kFlatMinRows || few_rows))
         for (int64_t l = 0; l < n; ++l)
             if (flat(l)) v[(size_t)l] = bk::GemmVariant::Wide;
     return v;
@@ -825,7 +871,11 @@ int64_t device_cus() {
 // One grouped clipped-gradient launch: layers of one kernel variant, in
 // launch order.
 struct GradEntry { int64_t l; GradPlan gp; };
-struct GradGroup { bk::GemmVariant v; std::vector<GradEntry> e; };
+struct GradGroup {
+    bk::GemmVariant v;
+    std::vector<GradEntry> e;
+    int64_t reserve = 0;     // partial tiles that the launch takes at most with fewer samples
+};
 
 constexpr int64_t kTailMinStages = 8;    // stages per slice of a split tail tile, at least
 constexpr int64_t kTailMaxSplit = 16;    // K slices per tail tile, at most
@@ -848,8 +898,10 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     const int64_t T0 = layers[g.e[0].l].T;
     int64_t N = 0;
     size_t best = 0;
+    bool own = false;
     for (size_t k = 0; k < g.e.size(); ++k) {
-        if (g.e[k].gp.ksplit != 1 || layers[g.e[k].l].T != T0) return;   // unequal work
+        if (layers[g.e[k].l].T != T0) return;        // unequal work
+        own = own || g.e[k].gp.ksplit != 1;
         N += g.e[k].gp.tiles();
         if (g.e[k].gp.tiles() > g.e[best].gp.tiles()) best = k;
     }
@@ -858,8 +910,12 @@ void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     if (r == 0 || 2 * r > cus || (!all && g.e[best].gp.tiles() < r)) return;
     const int64_t nst = g.v == bk::GemmVariant::GradDL ? B * dl_stages_per_sample(T0)
                         : g.v == bk::GemmVariant::Grad ? cdiv(B * T0, 64) : cdiv(B * T0, 16);
-    const int64_t sp = std::min({cus / r, nst / kTailMinStages, kTailMaxSplit});
+    // Slices of their own (grad_ksplit) are unequal work too; with fewer than
+    // kOwnMinStages stages none has any.
+    const int64_t sp = std::min({cus / r, (own ? std::min(nst, kOwnMinStages - 1) : nst) / kTailMinStages, kTailMaxSplit});
     if (sp < 2) return;
+    g.reserve = r * sp;
+    if (own) return;
     if (all && g.e.size() > 1) {
         // In stages (about 1 us of 32 rows each): a slice's partial tile
         // written and read back, and the second launch, against the stages
@@ -908,6 +964,8 @@ void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
         int64_t slices = 0;
         for (const GradEntry& e : g.e)
             if (stages(e) >= 2 * S) slices += e.gp.tiles() * (stages(e) / S);
+        for (const GradEntry& e : g.e) g.reserve += e.gp.tiles() * (stages(e) / kF32MinStages);
+        g.reserve = std::min(g.reserve, std::min(P, kF32MaxSlices));     // S >= work / P
         if (slices > kF32MaxSlices) return;
         for (GradEntry& e : g.e)
             if (stages(e) >= 2 * S) e.gp.ksplit = stages(e) / S;
@@ -917,10 +975,11 @@ void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
         plan_tail(g, layers, B, cus);
         return;
     }
-    const int64_t c = stages(g.e[0]);
+    const int64_t c = stages(g.e[0]), most = std::min(c / kF32MinStages, kTailMaxSplit);
+    if (most >= 2) g.reserve = std::min(N * most, kF32MaxSlices);
     int64_t s = 1;
     double best = 1.0;
-    for (int64_t k = 2; k <= kTailMaxSplit && c / k >= kF32MinStages && N * k <= kF32MaxSlices; ++k) {
+    for (int64_t k = 2; k <= most && N * k <= kF32MaxSlices; ++k) {
         const double t = (double)cdiv(N * k, P) / (double)k + (double)(kF32SliceCost * N * k) / (double)(P * c);
         if (t < 0.95 * best) {
             best = t;
@@ -931,10 +990,10 @@ void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
 }
 
 // The grouped launches of bk_weighted_grads: by kernel variant, at most
-// kMaxGemm layers each.
-std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16, int64_t B) {
+// kMaxGemm layers each (few_rows: as with fewer than kFlatMinRows rows).
+std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows = false) {
     std::vector<GradGroup> out;
-    const std::vector<bk::GemmVariant> vars = grad_variants(layers, n, bf16, B);
+    const std::vector<bk::GemmVariant> vars = grad_variants(layers, n, bf16, B, few_rows);
     for (int var = 0; var < bk::kGemmVariants; ++var) {
         for (int64_t l = 0; l < n; ++l) {
             const bk_layer& L = layers[l];
@@ -957,18 +1016,23 @@ std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16,
     return out;
 }
 
+// Workspace of the clipped gradients: what the launches take, or what those of
+// a smaller batch would take at most where the slices depend on the batch
+// (GradGroup::reserve), as norms_ws.
 size_t weighted_grads_ws(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t B) {
     size_t tot = 0;
     for (int64_t l = 0; l < n; ++l)
         if (layers[l].kind == BK_EMBEDDING) tot = std::max(tot, embed_grad_ws_bytes(B, layers[l].T, layers[l].p));
     // Grouped launches follow each other on the stream: each one's partial
-    // tiles start at the workspace's beginning.
-    for (const GradGroup& g : grad_groups(layers, n, dt == BK_BF16, B)) {
-        size_t tiles = 0;
-        for (const GradEntry& e : g.e)
-            tiles += (size_t)(e.gp.split_tiles() * e.gp.ksplit * e.gp.tile_elems) * sizeof(float);
-        tot = std::max(tot, tiles);
-    }
+    // tiles start at the workspace's beginning.  With a smaller batch the layers
+    // of T < 64 may leave the launches of the 256 x 256 tiles (grad_variants).
+    for (const bool few_rows : {false, true})
+        for (const GradGroup& g : grad_groups(layers, n, dt == BK_BF16, B, few_rows)) {
+            int64_t tiles = 0;
+            for (const GradEntry& e : g.e) tiles += e.gp.split_tiles() * e.gp.ksplit * e.gp.tile_elems;
+            tiles = std::max(tiles, g.reserve * g.e[0].gp.tile_elems);
+            tot = std::max(tot, (size_t)tiles * sizeof(float));
+        }
     return tot;
 }
 
@@ -1158,11 +1222,11 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
     if (B > 0 && !norm_sq) return fail(BK_ERR_INVALID_VALUE, "%s: NULL norm output", fn);
     std::vector<NormPlan> one(1);
     one[0].path = want;
-    set_norm_variant(one[0], L, dt, B);
+    set_norm_variant(one[0], L, dt);
     finish_norm_plan(one[0], L, B);
     launch_wide(one, &L, dt, B);
     const NormPlan np = one[0];
-    const size_t need = norm_ws_bytes(np, B);
+    const size_t need = norms_ws(one, &L, dt, B);
     if (ws_bytes < need || (need > 0 && !ws))
         return fail(BK_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", fn, ws_bytes, need);
     if (B == 0) return BK_OK;
@@ -1265,7 +1329,7 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
                 L.kind = BK_EMBEDDING;
                 NormPlan np{};
                 np.path = Path::Embed;
-                set_norm_variant(np, L, dt, B);
+                set_norm_variant(np, L, dt);
                 npart = std::max(npart, np.npart);
                 return align_up((size_t)(B * npart) * sizeof(float));
             }
@@ -1276,10 +1340,10 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
                 L.x = L.g = reinterpret_cast<const void*>(mis);
                 std::vector<NormPlan> one(1);
                 one[0].path = Path::Ghost;
-                set_norm_variant(one[0], L, dt, B);
+                set_norm_variant(one[0], L, dt);
                 finish_norm_plan(one[0], L, B);
                 launch_wide(one, &L, dt, B);
-                need = std::max(need, norm_ws_bytes(one[0], B));
+                need = std::max(need, norms_ws(one, &L, dt, B));
             }
             return need;
         }
@@ -1288,10 +1352,10 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
             L.kind = BK_LINEAR;
             std::vector<NormPlan> one(1);
             one[0].path = Path::Inst;
-            set_norm_variant(one[0], L, dt, B);  // NULL pointers count as aligned
+            set_norm_variant(one[0], L, dt);  // NULL pointers count as aligned
             finish_norm_plan(one[0], L, B);
             launch_wide(one, &L, dt, B);
-            return std::max(small, norm_ws_bytes(one[0], B));
+            return std::max(small, norms_ws(one, &L, dt, B));
         }
         case BK_OP_WEIGHTED_GRAD:   // 16-byte aligned rows assumed (an upper bound)
             L.kind = BK_LINEAR;

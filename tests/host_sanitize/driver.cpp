@@ -190,6 +190,54 @@ int main() {
                 }
             }
         }
+    // The workspace of the full batch serves every smaller one, for stacks
+    // without bf16 instantiated layers, and its size never falls as B grows.
+    for (int it = 0; it < 400; ++it) {
+        const bk_dtype dt = rng() % 3 ? BK_BF16 : BK_F32;
+        const int n = 1 + (int)(rng() % 6);
+        std::vector<bk_layer> L((size_t)n);
+        for (int l = 0; l < n; ++l) {
+            bk_layer& y = L[(size_t)l];
+            const int r = (int)(rng() % 10);
+            y.kind = r < 8 ? BK_LINEAR : r < 9 ? BK_EMBEDDING : BK_NORM_AFFINE;
+            do {
+                y.T = pick({1, 2, 16, 37, 50, 64, 100, 128, 130, 197, 256, 300, 600, 1024});
+                y.p = pick({8, 60, 256, 264, 768, 1000, 3072, 4099, 8192, 50257});
+                y.d = y.kind == BK_EMBEDDING ? 50257 : y.kind == BK_NORM_AFFINE ? y.p : pick({8, 60, 264, 768, 1001, 4096});
+            } while (y.kind == BK_LINEAR && dt == BK_BF16 && !bk_use_ghost(y.T, y.d, y.p));
+            const bool mis = rng() % 6 == 0;
+            y.x = fake(4 * l + 1, mis && y.kind != BK_EMBEDDING);
+            y.g = fake(4 * l + 2, mis);
+            y.G = static_cast<float*>(fake(4 * l + 3));
+            y.flags = 0;
+            if (y.kind != BK_EMBEDDING && rng() % 3 == 0) {
+                y.flags |= BK_LAYER_BIAS;
+                y.Gb = static_cast<float*>(fake(0x100000 + l));
+                y.Pb = static_cast<float*>(fake(0x200000 + l));
+            }
+            if (y.kind == BK_NORM_AFFINE) y.P = static_cast<float*>(fake(0x300000 + l));
+        }
+        float* norm = static_cast<float*>(fake(0x400000));
+        float* C = static_cast<float*>(fake(0x400001));
+        const int64_t full = pick({16, 63, 64, 65, 128, 512, 600, 4096});
+        const size_t w = bk_private_grad_workspace_size(L.data(), n, dt, full);
+        size_t more = w;
+        for (int64_t B = full; B >= 0; B -= B > 700 ? 1 + (int64_t)(rng() % 400) : B > 80 ? 1 + (int64_t)(rng() % 40) : 1) {
+            const size_t need = bk_private_grad_workspace_size(L.data(), n, dt, B);
+            if (need > more) {
+                std::fprintf(stderr, "workspace grows as the batch shrinks (full %lld): %zu at B=%lld, %zu just above\n", (long long)full, need, (long long)B, more);
+                for (const bk_layer& y : L)
+                    std::fprintf(stderr, "  dtype %d kind %d T=%lld %lld -> %lld flags %d\n", (int)dt, y.kind, (long long)y.T, (long long)y.d, (long long)y.p, y.flags);
+                return 1;
+            }
+            more = need;
+            const bk_status st = bk_private_grad(L.data(), n, dt, B, BK_CLIP_AUTO, 1.f, 0.01f, 0.f, 7, 0, norm, C, nullptr, set_ws(w), w, nullptr);
+            if (st != BK_OK) {
+                std::fprintf(stderr, "B=%lld on the workspace of B=%lld: %s\n", (long long)B, (long long)full, bk_last_error());
+                return 1;
+            }
+        }
+    }
     // few tokens of long rows whose pairs get no slices stay on the few-token
     // kernel (32 / T samples to a workgroup)
     for (const bk_dtype dt : {BK_BF16, BK_F32}) {
