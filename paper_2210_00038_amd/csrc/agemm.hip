@@ -422,7 +422,9 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
     const int ks = max(L.ksplit, 1), local = wg - L.wg_begin;
     const int sample = INST ? local / (tiles * ks) : 0;
     const int rem = local - sample * tiles * ks;
-    const int tile = rem / ks, slice = rem - tile * ks;
+    // Clipped gradient: all tiles of a slice together, so that those running at
+    // once on an XCD read the same rows through its L2.
+    const int tile = INST ? rem / ks : rem % tiles, slice = INST ? rem - tile * ks : rem / tiles;
     const int mt = tile / tn, nt = tile - mt * tn;
     const int m0 = mt * kBM, n0 = nt * kBN;
 
@@ -1509,9 +1511,10 @@ hipError_t launch_split_reduce(const GemmArgs& args, int n_wg, bool inst_norm, G
                                hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
     const dim3 grid(n_wg), block(256);
-    if (inst_norm && (v == GemmVariant::Wide || v == GemmVariant::WideAny))
-        hipLaunchKernelGGL((split_reduce_kernel<kBM, kBN, true>), grid, block, 0, s, args);
-    else if (!inst_norm && (v == GemmVariant::Grad || v == GemmVariant::GradDL))
+    if (v == GemmVariant::Wide) {
+        if (inst_norm) hipLaunchKernelGGL((split_reduce_kernel<kBM, kBN, true>), grid, block, 0, s, args);
+        else hipLaunchKernelGGL((split_reduce_kernel<kBM, kBN, false>), grid, block, 0, s, args);
+    } else if (!inst_norm && (v == GemmVariant::Grad || v == GemmVariant::GradDL))
         hipLaunchKernelGGL((split_reduce_kernel<kGM, kGN, false>), grid, block, 0, s, args);
     else if (v == GemmVariant::Narrow32) {
         if (inst_norm) hipLaunchKernelGGL((split_reduce_kernel<kNM, 32, true>), grid, block, 0, s, args);

@@ -989,6 +989,26 @@ void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     for (GradEntry& e : g.e) e.gp.ksplit = s;
 }
 
+// K slices of a launch of 256 x 128 tiles with more samples than the 256 x 256
+// kernels' weight table holds (two workgroups per CU: P = 2 cus slots; 64-row
+// stages): tiles of twice the even share of stages per slot or more are cut into
+// slices of about that share, at least kWideMinStages.  At most P partial tiles
+// (64 MiB) in all.  4097 samples of 64 tokens, 256 -> 256: 7.3 ms on two
+// workgroups, 87 us in slices (4096 on the 256 x 256 tiles: 101); 150 tokens,
+// 264 -> 264: 19.6 ms, 302 us; one token, 768 -> 1000: 104 us, 31.
+constexpr int64_t kWideMinStages = 8;
+void plan_wide(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
+    auto stages = [&](const GradEntry& e) { return cdiv(B * layers[e.l].T, bk::kWideK); };
+    int64_t work = 0;
+    for (const GradEntry& e : g.e) work += e.gp.tiles() * stages(e);
+    const int64_t S = std::max(kWideMinStages, cdiv(work, 2 * cus));
+    for (GradEntry& e : g.e) {
+        if (stages(e) >= 2 * S) e.gp.ksplit = stages(e) / S;
+        g.reserve += e.gp.tiles() * (stages(e) / kWideMinStages);
+    }
+    g.reserve = std::min(g.reserve, 2 * cus);
+}
+
 // The grouped launches of bk_weighted_grads: by kernel variant, at most
 // kMaxGemm layers each (few_rows: as with fewer than kFlatMinRows rows).
 std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows = false) {
@@ -1008,9 +1028,11 @@ std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16,
     int64_t cus = 0;
     for (GradGroup& g : out) {
         const bool f32 = g.v == bk::GemmVariant::F32 || g.v == bk::GemmVariant::F32Any;
-        if (g.v != bk::GemmVariant::GradDL && g.v != bk::GemmVariant::Grad && !f32) continue;
+        const bool wide = g.v == bk::GemmVariant::Wide && B > bk::kDMaxB;
+        if (g.v != bk::GemmVariant::GradDL && g.v != bk::GemmVariant::Grad && !f32 && !wide) continue;
         if (cus == 0) cus = device_cus();
         if (f32) plan_f32(g, layers, B, cus);
+        else if (wide) plan_wide(g, layers, B, cus);
         else plan_tail(g, layers, B, cus);
     }
     return out;

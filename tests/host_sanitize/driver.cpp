@@ -15,7 +15,7 @@
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
-extern long g_ghost_wgs;
+extern long g_ghost_wgs, g_gemm_wgs;
 extern std::map<uintptr_t, int> g_noised;
 
 namespace {
@@ -190,6 +190,18 @@ int main() {
                 }
             }
         }
+    // clipped gradients of few tiles over many samples are cut into K slices,
+    // also past the 256 x 256 kernels' weight table
+    for (int64_t B : {bk::kDMaxB, bk::kDMaxB + 1, 2 * bk::kDMaxB})
+        for (int64_t T : {64, 70, 150})
+            for (int64_t d : {256, 264, 768}) {
+                const size_t w = bk_workspace_size(BK_OP_WEIGHTED_GRAD, BK_BF16, B, T, d, 256);
+                float* out = static_cast<float*>(fake(3));
+                if (bk_weighted_grad(fake(1), fake(2), out, BK_BF16, B, T, d, 256, out, set_ws(w), w, nullptr) != BK_OK || g_gemm_wgs < 128) {
+                    std::fprintf(stderr, "B=%lld T=%lld %lld -> 256: %ld workgroups\n", (long long)B, (long long)T, (long long)d, g_gemm_wgs);
+                    return 1;
+                }
+            }
     // The workspace of the full batch serves every smaller one, for stacks
     // without bf16 instantiated layers, and its size never falls as B grows.
     for (int it = 0; it < 400; ++it) {

@@ -18,6 +18,7 @@
 uintptr_t g_ws_lo = 0, g_ws_hi = 0;   // [lo, hi): the caller's workspace
 long g_launches = 0;
 long g_ghost_wgs = 0;                 // workgroups of the last ghost-norm launch
+long g_gemm_wgs = 0;                  // ... of the last a^T g launch
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
 namespace {
@@ -101,6 +102,7 @@ hipError_t launch_embed_join(const GhostArgs& a, int n_wg, bool, int ct, hipStre
 }
 hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant v, hipStream_t, int) {
     ++g_launches;
+    g_gemm_wgs = n_wg;
     monotone(a.L, a.n, kMaxGemm, n_wg, "gemm descriptors");
     for (int k = 0; k < a.n; ++k) {
         const GemmLayer& L = a.L[k];
@@ -126,9 +128,21 @@ hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant
     }
     return hipSuccess;
 }
-hipError_t launch_split_reduce(const GemmArgs& a, int n_wg, bool, GemmVariant, hipStream_t) {
+hipError_t launch_split_reduce(const GemmArgs& a, int n_wg, bool inst, GemmVariant v, hipStream_t) {
     ++g_launches;
     need(n_wg > 0 && a.n >= 1 && a.n <= kMaxGemm, "split reduce");
+    // the variants whose slices the kernel adds
+    need(v == GemmVariant::Wide || v == GemmVariant::Narrow32 || v == GemmVariant::Narrow64 || v == GemmVariant::F32 ||
+             v == GemmVariant::F32Any || (!inst && (v == GemmVariant::Grad || v == GemmVariant::GradDL)),
+         "split reduce variant");
+    int64_t red = 0;
+    for (int k = 0; k < a.n; ++k) {
+        const GemmLayer& L = a.L[k];
+        need(L.red_begin == red, "split reduce descriptors");
+        const int64_t tiles = (int64_t)L.tm * L.tn - L.split_from;
+        if (L.ksplit > 1) red += (inst ? a.B : 1) * tiles * (gemm_geom(v, L.d, L.p).tile_elems / kSplitRedWG);
+    }
+    need(red == n_wg, "split reduce grid");
     return hipSuccess;
 }
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t) {

@@ -225,6 +225,34 @@ def test_flat_weighted_grad(bk, B, T, d, p):
     assert torch.equal(Ga, G0 + Gw) and _frob(Gw.cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
 
 
+# More samples than the 256 x 256 kernels' weight table: 256 x 128 tiles in K
+# slices, which begin and end inside samples.
+@pytest.mark.parametrize("B,T,d,p", [
+    (4097, 64, 72, 80),      # one tile, hundreds of slices of whole samples
+    (4200, 3, 264, 136),     # 2 x 2 tiles, samples across stages and slices
+    (4100, 67, 72, 264),
+    (20000, 1, 304, 72),     # one token a sample
+])
+def test_weighted_grad_past_the_weight_table(bk, B, T, d, p):
+    assert bk.bk_workspace_size(bk.BK_OP_WEIGHTED_GRAD, bk.BK_BF16, B, T, d, p) > 0
+    gen = torch.Generator().manual_seed(B + T)
+    a, ah = _draw(B, T, d, BF, gen)
+    g, gh = _draw(B, T, p, BF, gen, 1e-2)
+    C = torch.rand(B, generator=gen) + 0.1
+    C[B // 2] = 0.0
+    G = bk.bk_weighted_grad(a, g, C.to(DEV))
+    assert torch.equal(G, bk.bk_weighted_grad(a, g, C.to(DEV)))
+    assert _frob(G.cpu().numpy(), oracle.weighted_grad(ah, gh, C)) <= GRAD_GUARD_ROUNDED
+    C2 = torch.exp2(torch.randint(-3, 4, (B,), generator=gen).float())       # exact in bf16
+    G2 = bk.bk_weighted_grad(a, g, C2.to(DEV))
+    assert _frob(G2.cpu().numpy(), oracle.weighted_grad(ah, gh, C2)) <= GRAD_GUARD_EXACT
+    G0 = torch.randn(d, p, generator=gen).to(DEV)
+    Ga = G0.clone()
+    arr = bk.make_layers([{"x": a, "g": g, "G": Ga, "accumulate": True}])
+    bk.bk_weighted_grads(arr, 1, C.to(DEV), bk.BK_BF16, B)
+    assert torch.equal(Ga, G0 + G)
+
+
 # The fp32 GEMM: 128 x 128 tiles, 16-row stages, rows of 16-byte multiples and
 # of any length, K slices, accumulation, per-sample gradients.
 @pytest.mark.parametrize("B,T,d,p,off", [
