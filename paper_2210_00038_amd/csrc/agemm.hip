@@ -343,8 +343,9 @@ __global__ __launch_bounds__(256) void agemm_kernel(const GemmArgs args) {
 // ANY (GemmVariant::WideAny): rows of any alignment.  Bound by the staging
 // path as the aligned form, plus loads that straddle cache lines: the head
 // 768 -> 50257 on 8 x 128 tokens takes 175 us (453 TFLOP/s) against 1140-1165 us
-// with the element loads of the 128 x 128 kernel, which now keeps only rows of
-// fewer than 8 columns.
+// with the element loads of the 128 x 128 kernel.  A launch with rows of fewer
+// than 8 columns takes the SHORT form (768 -> 2 on 32 x 128 tokens: 371 us with
+// element loads, 147 now; in the other launches its loads would cost 2%).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kOut = 0xFFFFFFF0u;           // buffer offset that loads zeros
 constexpr int kBM = kWideM, kBN = kWideN, kBK = kWideK;
@@ -408,8 +409,9 @@ __device__ __forceinline__ uint2 scale_half(const uint2& v, const float4& w) {
 }
 
 
-template <bool INST, bool ANY>
+template <bool INST, bool ANY, bool SHORT = false>
 __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args, int n_wg) {
+    static_assert(ANY || !SHORT, "short rows");
     __shared__ __attribute__((aligned(16))) char ldsA[kBK * kSA];
     __shared__ __attribute__((aligned(16))) char ldsB[kBK * kSB];
     __shared__ float red[4];
@@ -460,9 +462,22 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
     // reads the row's last 16 bytes (its tile columns are never stored or
     // summed, unless it begins before the end, when it is shifted into place
     // on its way to LDS), a row past the last one reads that one and is
-    // zeroed on its way to LDS.
-    const int colA = ANY ? tail_col<bf16_t>(m0 + ca, d) : 0, colB = ANY ? tail_col<bf16_t>(n0 + cb, p) : 0;
-    const bool edgeA = ANY && m0 + kBM > d, edgeB = ANY && n0 + kBN > p;   // uniform
+    // zeroed on its way to LDS.  SHORT: an operand of fewer than 8 columns (one
+    // piece per row) reads on into the rows that follow, the batch's last rows
+    // from its last 16 bytes, shifted likewise; tile columns past the row's end
+    // are never stored or summed.
+    const bool shortA = SHORT && d < 8, shortB = SHORT && p < 8;           // uniform
+    const size_t lastA = (size_t)args.B * nT * d - 8, lastB = (size_t)args.B * nT * p - 8;   // used where short
+    const int colA = ANY && !shortA ? tail_col<bf16_t>(m0 + ca, d) : 0;
+    const int colB = ANY && !shortB ? tail_col<bf16_t>(n0 + cb, p) : 0;
+    const bool edgeA = ANY && !shortA && m0 + kBM > d, edgeB = ANY && !shortB && n0 + kBN > p;   // uniform
+    auto load_short = [&](const void* X, int K, size_t last, uint32_t k) {
+        return load16_any<bf16_t>(reinterpret_cast<const bf16_t*>(X) + min((size_t)(row0 + k) * (uint32_t)K, last));
+    };
+    auto shift_short = [&](const uint4& v, int K, size_t last, uint32_t k) {
+        const size_t e = (size_t)(row0 + k) * (uint32_t)K;
+        return e > last ? shift_tail<bf16_t>(v, (int)min(e - last, (size_t)8), 8) : v;     // by e - last elements
+    };
 
     uint4 va[8], vb[4];
     float cw[4];
@@ -472,12 +487,14 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const uint32_t k = k0 + (uint32_t)(ka + 8 * j);
-                va[j] = load16_any<bf16_t>(baseA + (size_t)(last ? min(k, nrows - 1u) : k) * (uint32_t)d + colA);
+                const uint32_t r = last ? min(k, nrows - 1u) : k;
+                va[j] = shortA ? load_short(L.a, d, lastA, r) : load16_any<bf16_t>(baseA + (size_t)r * (uint32_t)d + colA);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t k = k0 + (uint32_t)(kb + 16 * j);
-                vb[j] = load16_any<bf16_t>(baseB + (size_t)(last ? min(k, nrows - 1u) : k) * (uint32_t)p + colB);
+                const uint32_t r = last ? min(k, nrows - 1u) : k;
+                vb[j] = shortB ? load_short(L.g, p, lastB, r) : load16_any<bf16_t>(baseB + (size_t)r * (uint32_t)p + colB);
             }
         } else {
             const __amdgpu_buffer_rsrc_t rA = rows_rsrc(baseA, rowA, k0, nrows, kBK);
@@ -524,6 +541,14 @@ __global__ __launch_bounds__(256, 2) void agemm_bf16_kernel(const GemmArgs args,
             if (edgeB) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) vb[j] = shift_tail<bf16_t>(vb[j], n0 + cb, p);
+            }
+            if (shortA) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) va[j] = shift_short(va[j], d, lastA, st * kBK + (uint32_t)(ka + 8 * j));
+            }
+            if (shortB) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) vb[j] = shift_short(vb[j], p, lastB, st * kBK + (uint32_t)(kb + 16 * j));
             }
             if ((st + 1) * kBK > nrows) {
 #pragma unroll
@@ -1549,8 +1574,12 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
         return hipGetLastError();
     }
     if (v == GemmVariant::WideAny) {
-        if (inst_norm) hipLaunchKernelGGL((agemm_bf16_kernel<true, true>), grid, block, 0, s, args, n_wg);
-        else hipLaunchKernelGGL((agemm_bf16_kernel<false, true>), grid, block, 0, s, args, n_wg);
+        bool is_short = false;
+        for (int k = 0; k < args.n; ++k) is_short = is_short || std::min(args.L[k].d, args.L[k].p) < 8;
+#define BK_ANY_GEMM(I, S) hipLaunchKernelGGL((agemm_bf16_kernel<I, true, S>), grid, block, 0, s, args, n_wg)
+        if (is_short) { if (inst_norm) BK_ANY_GEMM(true, true); else BK_ANY_GEMM(false, true); }
+        else          { if (inst_norm) BK_ANY_GEMM(true, false); else BK_ANY_GEMM(false, false); }
+#undef BK_ANY_GEMM
         return hipGetLastError();
     }
     if (v == GemmVariant::Narrow32) {

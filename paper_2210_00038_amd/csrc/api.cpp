@@ -152,13 +152,13 @@ bool ghost_rows16(const bk_layer& L, bk_dtype dt) {
            (L.T + bk::kSuper) * std::max(L.d, L.p) * es < ((int64_t)1 << 31);
 }
 
-void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt) {
+void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
     const size_t es = elem_bytes(dt);
     if (np.path == Path::Affine) {
         np.npart = 0;
         np.var = 0;
     } else if (np.path == Path::Inst) {
-        const auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, 0, aligned16(L.x) && aligned16(L.g));
+        const auto v = bk::gemm_variant(dt == BK_BF16, L.d, L.p, B * L.T, 0, aligned16(L.x) && aligned16(L.g));
         const bk::GemmGeom geo = bk::gemm_geom(v, L.d, L.p);
         np.var = (int)v;
         np.tiles = geo.tm * geo.tn;
@@ -267,7 +267,7 @@ NormPlan norm_plan(const bk_layer& L, bk_dtype dt, int64_t B) {
     } else {
         np.path = layer_ghost(L) ? Path::Ghost : Path::Inst;
     }
-    set_norm_variant(np, L, dt);
+    set_norm_variant(np, L, dt, B);
     finish_norm_plan(np, L, B);
     return np;
 }
@@ -530,7 +530,7 @@ size_t norms_ws(const std::vector<NormPlan>& plans, const bk_layer* layers, bk_d
         const bool f32inst = dt == BK_F32 && np.path == Path::Inst;
         if (np.path == Path::Ghost || f32inst) {       // before the launch-wide choices
             np.ksplit = 1;
-            set_norm_variant(np, L, dt);
+            set_norm_variant(np, L, dt, B);
             finish_norm_plan(np, L, B);
         }
         whole += norm_ws_bytes(np, B);
@@ -794,7 +794,7 @@ bk_status layer_norms(const char* fn, const bk_layer* layers, int64_t n, bk_dtyp
 // sample to 16-row steps adds at most 1/8 to its rows, else with the weights on
 // g's fragments over the flat rows of the batch (Grad).
 bk::GemmVariant grad_variant(const bk_layer& L, bool bf16, int64_t B) {
-    const auto v = bk::gemm_variant(bf16, L.d, L.p, B, aligned16(L.x) && aligned16(L.g));
+    const auto v = bk::gemm_variant(bf16, L.d, L.p, B * L.T, B, aligned16(L.x) && aligned16(L.g));
     if (is_narrow(v)) return L.T < 64 ? bk::GemmVariant::Wide : v;   // narrow kernel: T >= 64
     if (v != bk::GemmVariant::Wide || B > bk::kDMaxB) return v;
     return L.T >= 64 && dl_padding_ok(L.T) ? bk::GemmVariant::GradDL : bk::GemmVariant::Grad;
@@ -1244,7 +1244,7 @@ bk_status single_norm(const char* fn, Path want, const bk_layer& L, bk_dtype dt,
     if (B > 0 && !norm_sq) return fail(BK_ERR_INVALID_VALUE, "%s: NULL norm output", fn);
     std::vector<NormPlan> one(1);
     one[0].path = want;
-    set_norm_variant(one[0], L, dt);
+    set_norm_variant(one[0], L, dt, B);
     finish_norm_plan(one[0], L, B);
     launch_wide(one, &L, dt, B);
     const NormPlan np = one[0];
@@ -1351,7 +1351,7 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
                 L.kind = BK_EMBEDDING;
                 NormPlan np{};
                 np.path = Path::Embed;
-                set_norm_variant(np, L, dt);
+                set_norm_variant(np, L, dt, B);
                 npart = std::max(npart, np.npart);
                 return align_up((size_t)(B * npart) * sizeof(float));
             }
@@ -1362,7 +1362,7 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
                 L.x = L.g = reinterpret_cast<const void*>(mis);
                 std::vector<NormPlan> one(1);
                 one[0].path = Path::Ghost;
-                set_norm_variant(one[0], L, dt);
+                set_norm_variant(one[0], L, dt, B);
                 finish_norm_plan(one[0], L, B);
                 launch_wide(one, &L, dt, B);
                 need = std::max(need, norms_ws(one, &L, dt, B));
@@ -1374,7 +1374,7 @@ size_t bk_workspace_size(bk_op op, bk_dtype dt, int64_t B, int64_t T, int64_t d,
             L.kind = BK_LINEAR;
             std::vector<NormPlan> one(1);
             one[0].path = Path::Inst;
-            set_norm_variant(one[0], L, dt);  // NULL pointers count as aligned
+            set_norm_variant(one[0], L, dt, B);  // NULL pointers count as aligned
             finish_norm_plan(one[0], L, B);
             launch_wide(one, &L, dt, B);
             return std::max(small, norms_ws(one, &L, dt, B));

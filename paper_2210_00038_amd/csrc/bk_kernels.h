@@ -142,8 +142,8 @@ struct NoiseArgs {
 constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by one workgroup
 
 // Kernel variant of the a^T g GEMMs for one layer:
-//  Scalar: element loads, 128 x 128 (unaligned bf16 rows of fewer than 8
-//          columns; fp32 past F32's limits);
+//  Scalar: element loads, 128 x 128 (unaligned bf16 rows past 2^23 bytes, or
+//          operands of fewer than 8 elements in all; fp32 past F32's limits);
 //  Vec   : 16-byte loads, register transpose, 128 x 128 (bf16 rows past 2^23
 //          bytes; fp32 past F32's limits);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
@@ -153,7 +153,7 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 //          to whole stages of kDLStageRows rows).
 //  Narrow32 / Narrow64: bf16, one side of d x p at most 32 / 64, tiles of
 //          256 along the long side (operands swapped when d < p).
-//  WideAny: as Wide for bf16 rows of any alignment and at least 8 columns;
+//  WideAny: as Wide for bf16 rows of any alignment and length;
 //  F32 / F32Any: fp32, LDS DMA, 128 x 128; 16-byte rows / rows of any alignment
 //          (rows up to 2^26 bytes, B <= kF32MaxB).
 enum class GemmVariant {
@@ -170,8 +170,9 @@ constexpr int kDLBuffers = 4;      // its LDS stage buffers (the ping-pong sched
 constexpr int kWideM = 256, kWideN = 128, kWideK = 64;
 constexpr int kGradM = 256, kGradN = 256;
 constexpr int kNarrowM = 256;
-// `weights`: the clip weights that the launch reads (0: an instantiated norm).
-GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t weights, bool aligned);
+// `rows`: of the whole batch (B T); `weights`: the clip weights that the launch
+// reads (0: an instantiated norm).
+GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, int64_t weights, bool aligned);
 // Output tiles of a d x p layer on variant v: tm x tn tiles of tile_elems
 // floats (a K-split partial tile), rows along p when swap.
 struct GemmGeom {

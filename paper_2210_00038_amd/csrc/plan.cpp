@@ -27,7 +27,7 @@ GemmGeom gemm_geom(GemmVariant v, int64_t d, int64_t p) {
     }
 }
 
-GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t weights, bool aligned) {
+GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t rows, int64_t weights, bool aligned) {
     const int64_t es = bf16 ? 2 : 4;
     const bool vec = aligned && (d * es) % 16 == 0 && (p * es) % 16 == 0;
     // 32-bit offsets: a stage of 32 rows, and the clip weights.
@@ -36,8 +36,8 @@ GemmVariant gemm_variant(bool bf16, int64_t d, int64_t p, int64_t weights, bool 
     // The wide and narrow kernels address one K stage of rows at a time with
     // 32-bit offsets (rows_rsrc): a stage must fit in 2^31 bytes.
     const bool stage = bf16 && 4 * kWideK * std::max(d, p) * es < ((int64_t)1 << 31);
-    // bf16 rows of any alignment, 8 columns or more on both sides.
-    if (!vec) return stage && std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
+    // bf16 rows of any alignment; operands that hold one 16-byte piece.
+    if (!vec) return stage && rows * std::min(d, p) >= 8 ? GemmVariant::WideAny : GemmVariant::Scalar;
     if (stage) {
         const int64_t lo = std::min(d, p), hi = std::max(d, p);
         if (lo <= 64 && hi >= 128) return lo <= 32 ? GemmVariant::Narrow32 : GemmVariant::Narrow64;

@@ -15,7 +15,7 @@
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
-extern long g_ghost_wgs, g_gemm_wgs;
+extern long g_ghost_wgs, g_gemm_wgs, g_gemm_launches;
 extern std::map<uintptr_t, int> g_noised;
 
 namespace {
@@ -202,6 +202,25 @@ int main() {
                     return 1;
                 }
             }
+    // bf16 rows of every odd length share one launch
+    {
+        bk_layer L[3] = {};
+        const int64_t p[3] = {2, 9, 1031};
+        for (int l = 0; l < 3; ++l) {
+            L[l].T = 100;
+            L[l].d = 264;
+            L[l].p = p[l];
+            L[l].x = fake(3 * l + 1);
+            L[l].g = fake(3 * l + 2);
+            L[l].G = static_cast<float*>(fake(3 * l + 3));
+        }
+        const size_t w = bk_weighted_grads_workspace_size(L, 3, BK_BF16, 16);
+        g_gemm_launches = 0;
+        if (bk_weighted_grads(L, 3, static_cast<float*>(fake(20)), BK_BF16, 16, set_ws(w), w, nullptr) != BK_OK || g_gemm_launches != 1) {
+            std::fprintf(stderr, "unaligned bf16 gradients: %ld launches\n", g_gemm_launches);
+            return 1;
+        }
+    }
     // The workspace of the full batch serves every smaller one, for stacks
     // without bf16 instantiated layers, and its size never falls as B grows.
     for (int it = 0; it < 400; ++it) {

@@ -9,6 +9,7 @@
 // driver can check that every gradient gets its noise exactly once.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -19,6 +20,7 @@ uintptr_t g_ws_lo = 0, g_ws_hi = 0;   // [lo, hi): the caller's workspace
 long g_launches = 0;
 long g_ghost_wgs = 0;                 // workgroups of the last ghost-norm launch
 long g_gemm_wgs = 0;                  // ... of the last a^T g launch
+long g_gemm_launches = 0;
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
 namespace {
@@ -103,6 +105,7 @@ hipError_t launch_embed_join(const GhostArgs& a, int n_wg, bool, int ct, hipStre
 hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant v, hipStream_t, int) {
     ++g_launches;
     g_gemm_wgs = n_wg;
+    ++g_gemm_launches;
     monotone(a.L, a.n, kMaxGemm, n_wg, "gemm descriptors");
     for (int k = 0; k < a.n; ++k) {
         const GemmLayer& L = a.L[k];
@@ -112,6 +115,8 @@ hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant
         // the fp32 kernel reads C through a 32-bit buffer descriptor
         if (!inst && (v == GemmVariant::F32 || v == GemmVariant::F32Any))
             need((uint64_t)a.B * 4 < 0xFFFFFFF0u, "fp32 clip weights within 32-bit offsets");
+        // 16-byte pieces of rows of fewer than 8 columns end inside the batch
+        if (v == GemmVariant::WideAny) need((int64_t)a.B * L.T * std::min(L.d, L.p) >= 8, "unaligned bf16 rows");
         if (inst && v == GemmVariant::GradDL) {
             // one workgroup per (sample, tile), never split, no clip weights
             need(L.ksplit <= 1 && a.C == nullptr && (int64_t)a.B * L.T < ((int64_t)1 << 31) && L.T >= 64,

@@ -88,6 +88,10 @@ def test_ghost_rows_and_column_slices(bk, B, T, d, p, dtype, off):
     (5, 13, 1000, 15, 0),      # several samples per stage
     (2, 130, 264, 136, 1),     # 16-byte row lengths, misaligned base
     (130, 1, 300, 10, 0),      # one token a sample
+    (3, 65, 300, 2, 0),        # rows of fewer than 8 elements: two, one
+    (4, 70, 1, 131, 0),
+    (3, 100, 7, 3, 1),         # both sides, the batch ends inside a piece
+    (8, 1, 1, 72, 0),          # one piece in all
 ])
 def test_gemm_rows_of_any_alignment(bk, B, T, d, p, off):
     gen = torch.Generator().manual_seed(B + 10 * T + d)
