@@ -325,7 +325,7 @@ bk_status bk_philox_raw(uint64_t seed, uint32_t tensor_id, uint32_t step, uint64
  * rows of few tokens) give fewer than 64 workgroups, their rows are cut into
  * column slices; instantiated norms take larger tiles, and long fp32 ones K
  * slices, by what the call's instantiated layers give together (the clipped
- * gradients' K slices likewise).  Every result is
+ * gradients' K slices, and the fp32 kernel for few rows, likewise).  Every result is
  * deterministic.  The bk_layer array is read on the host during the call only.
  * ------------------------------------------------------------------------- */
 

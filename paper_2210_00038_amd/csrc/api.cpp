@@ -440,12 +440,29 @@ void promote_inst_dl(std::vector<NormPlan>& plans, const bk_layer* layers, int64
         }
 }
 
+// fp32 instantiated norms of 16-byte rows, T <= kF32FewInst in all such layers:
+// the register-transposing kernel, as for the gradients (grad_variants): 10.2 us
+// against 11.1 at T = 16 and 32, 16 or 256 samples; T = 49 11.5 against 11.1.
+constexpr int64_t kF32FewInst = 32;
+void few_rows_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers) {
+    auto f32 = [](const NormPlan& np) { return np.path == Path::Inst && np.var == (int)bk::GemmVariant::F32; };
+    int64_t T = 0;
+    for (size_t l = 0; l < plans.size(); ++l)
+        if (f32(plans[l])) T = std::max(T, layers[l].T);
+    if (T > kF32FewInst) return;
+    for (NormPlan& np : plans)
+        if (f32(np)) np.var = (int)bk::GemmVariant::Vec;      // the same tiles
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     promote_inst_dl(plans, layers, B);
     demote_small_full(plans, layers, B);
     split_few_ghost(plans, layers, dt, B);
-    if (dt == BK_F32) split_long_f32_inst(plans, layers, B);
+    if (dt == BK_F32) {
+        few_rows_f32_inst(plans, layers);
+        split_long_f32_inst(plans, layers, B);
+    }
 }
 
 // The norm plans of a call's layers (norm_plan each, then launch_wide).
@@ -809,14 +826,26 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // run on the 256 x 128 tiles, two to a CU (a small ResNet at 224 x 224, 7
 // samples: 14 + 10 us in one launch and 29 in two; 36 encoder layers of 64 x 37
 // rows, 648 tiles: 265 us against 295-310).
-constexpr int64_t kFlatMinTiles = 128, kFlatMinRows = 4096;
+// fp32 layers: the LDS-DMA kernel's ring takes three stages of 16 rows to fill,
+// the register-transposing kernel's one of 32: it is the faster one while every
+// layer of the call has at most kF32FewRows rows (one 64 x 64 layer of 64 rows:
+// 10.0 us against 13.6; 12 of 768 wide, 16 rows: 33 against 38), or twice that
+// with at most kF32FewTiles tiles (1024 x 1024, 96 rows: 14.6 against 17.3, 128
+// rows: 17.9 against 19.4; 1296 tiles, 96 rows: 69 against 65).  Rows of any
+// alignment: kF32FewRows, and four times the tiles, its loads being single
+// elements there (24 of 265 x 265, 64 rows: 16.5 against 17.4 us; three of 1031
+// x 4097: 43 against 41; one of 265 x 265, 96 rows: the same).
+constexpr int64_t kFlatMinTiles = 128, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
 std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows) {
     std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
-    int64_t tiles = 0, rows = 0;
+    int64_t tiles = 0, rows = 0, rows32 = 0, vec32 = 0, any32 = 0;
     auto flat = [&](int64_t l) { return v[(size_t)l] == bk::GemmVariant::Grad && layers[l].T < 64; };
     for (int64_t l = 0; l < n; ++l) {
         if (!gemm_grad(layers[l])) continue;
         v[(size_t)l] = grad_variant(layers[l], bf16, B);
+        if (!bf16) rows32 = std::max(rows32, B * layers[l].T);
+        if (!bf16)
+            (v[(size_t)l] == bk::GemmVariant::F32Any ? any32 : vec32) += cdiv(layers[l].d, bk::kTile) * cdiv(layers[l].p, bk::kTile);
         if (!flat(l)) continue;
         const bk::GemmGeom geo = bk::gemm_geom(bk::GemmVariant::Grad, layers[l].d, layers[l].p);
         tiles += geo.tm * geo.tn;
@@ -825,6 +854,11 @@ std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bo
     if (tiles < kFlatMinTiles && (rows < kFlatMinRows || few_rows))
         for (int64_t l = 0; l < n; ++l)
             if (flat(l)) v[(size_t)l] = bk::GemmVariant::Wide;
+    const bool few = rows32 <= kF32FewRows, few2 = rows32 <= 2 * kF32FewRows && vec32 <= kF32FewTiles;
+    for (bk::GemmVariant& x : v) {
+        if (x == bk::GemmVariant::F32 && (few || few2)) x = bk::GemmVariant::Vec;
+        if (x == bk::GemmVariant::F32Any && few && any32 <= 4 * kF32FewTiles) x = bk::GemmVariant::Scalar;
+    }
     return v;
 }
 

@@ -143,9 +143,10 @@ constexpr int kNoiseBlocksPerWG = 4 * 256;   // most counter blocks handled by o
 
 // Kernel variant of the a^T g GEMMs for one layer:
 //  Scalar: element loads, 128 x 128 (unaligned bf16 rows past 2^23 bytes, or
-//          operands of fewer than 8 elements in all; fp32 past F32's limits);
+//          operands of fewer than 8 elements in all; fp32 calls of few rows or
+//          past F32's limits);
 //  Vec   : 16-byte loads, register transpose, 128 x 128 (bf16 rows past 2^23
-//          bytes; fp32 past F32's limits);
+//          bytes; fp32 calls of few rows or past F32's limits);
 //  Wide  : bf16, LDS transpose reads, larger tiles;
 //  Grad  : bf16 clipped gradient only, 256 x 256 tiles, 512 threads, LDS DMA,
 //          the weights on g's fragments (B <= kDMaxB);

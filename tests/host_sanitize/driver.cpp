@@ -16,6 +16,7 @@
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
 extern long g_ghost_wgs, g_gemm_wgs, g_gemm_launches;
+extern bk::GemmVariant g_gemm_variant;
 extern std::map<uintptr_t, int> g_noised;
 
 namespace {
@@ -202,6 +203,22 @@ int main() {
                     return 1;
                 }
             }
+    // fp32 calls of few rows: the register-transposing kernel
+    {
+        struct { int64_t B, T, d, p; bk::GemmVariant v; } const cs[] = {
+            {4, 16, 64, 64, bk::GemmVariant::Vec},        {64, 1, 4096, 4096, bk::GemmVariant::Vec},
+            {1, 128, 1024, 1024, bk::GemmVariant::Vec},   {1, 65, 4096, 4096, bk::GemmVariant::F32},
+            {1, 129, 64, 64, bk::GemmVariant::F32},       {64, 1, 65, 63, bk::GemmVariant::Scalar},
+            {65, 1, 65, 63, bk::GemmVariant::F32Any},     {4, 16, 4097, 4095, bk::GemmVariant::F32Any}};
+        for (const auto& c : cs) {
+            const size_t w = bk_workspace_size(BK_OP_WEIGHTED_GRAD, BK_F32, c.B, c.T, c.d, c.p);
+            float* out = static_cast<float*>(fake(3));
+            if (bk_weighted_grad(fake(1), fake(2), out, BK_F32, c.B, c.T, c.d, c.p, out, set_ws(w), w, nullptr) != BK_OK || g_gemm_variant != c.v) {
+                std::fprintf(stderr, "fp32 B=%lld T=%lld %lld -> %lld: kernel variant %d\n", (long long)c.B, (long long)c.T, (long long)c.d, (long long)c.p, (int)g_gemm_variant);
+                return 1;
+            }
+        }
+    }
     // bf16 rows of every odd length share one launch
     {
         bk_layer L[3] = {};

@@ -21,6 +21,7 @@ long g_launches = 0;
 long g_ghost_wgs = 0;                 // workgroups of the last ghost-norm launch
 long g_gemm_wgs = 0;                  // ... of the last a^T g launch
 long g_gemm_launches = 0;
+bk::GemmVariant g_gemm_variant = bk::GemmVariant::Scalar;   // ... of the last one
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
 namespace {
@@ -106,6 +107,7 @@ hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant
     ++g_launches;
     g_gemm_wgs = n_wg;
     ++g_gemm_launches;
+    g_gemm_variant = v;
     monotone(a.L, a.n, kMaxGemm, n_wg, "gemm descriptors");
     for (int k = 0; k < a.n; ++k) {
         const GemmLayer& L = a.L[k];

@@ -258,7 +258,8 @@ def test_weighted_grad_past_the_weight_table(bk, B, T, d, p):
 
 
 # The fp32 GEMM: 128 x 128 tiles, 16-row stages, rows of 16-byte multiples and
-# of any length, K slices, accumulation, per-sample gradients.
+# of any length, K slices, accumulation, per-sample gradients (calls of few rows
+# on the register-transposing kernel; next to the longer layer below, not).
 @pytest.mark.parametrize("B,T,d,p,off", [
     (1, 1, 4, 4, 0),           # one row, one piece
     (3, 5, 128, 132, 0),       # 15 rows; one piece past a tile
@@ -269,6 +270,9 @@ def test_weighted_grad_past_the_weight_table(bk, B, T, d, p):
     (6, 50, 64, 200, 1),       # misaligned base
     (5, 100, 1, 77, 0),        # one column
     (2, 1030, 136, 24, 0),     # long samples: per-sample gradients in K slices too
+    (2, 64, 264, 200, 0),      # the most rows of few tiles on the register-transposing kernel,
+    (3, 43, 264, 200, 0),      # and one more
+    (1, 65, 131, 71, 0),       # the same of odd rows
 ])
 def test_f32_gemm(bk, B, T, d, p, off):
     gen = torch.Generator().manual_seed(B + T + d + p)
