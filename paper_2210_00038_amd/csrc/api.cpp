@@ -345,33 +345,67 @@ void split_small_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_
 // launch gives fewer than kGhostSplitBelow workgroups go back to the pair
 // kernel where split_small_ghost cuts them into column slices, and stay where it
 // does not (8192 -> 8192, 200 samples of 2 tokens: 41 us here, 111 on the pair
-// kernel's whole rows).  So do all of them when they would not fill the chip in a launch of
-// their own next to one of the pair kernel (kSmallMixedBelow workgroups, at most
-// kSmallMixedB samples: the late layers and the classifier of ResNet-18 with 16
-// samples, 53 us in one launch against 29 + 33 + 12 us in three).
+// kernel's whole rows).
+//
+// Layers of few tokens (fp32: up to 128) also go there when they would not fill
+// the chip in a launch of their own next to one of the pair kernel
+// (kSmallMixedBelow workgroups, at most kSmallMixedB samples): the late layers
+// and the classifier of ResNet-18 with 16 samples take 53 us in one launch, 29 +
+// 33 + 12 us in three; three 512 x 512 at 49 tokens beside a 768 x 768 at 100, 16
+// samples, 18 against 33; in fp32 three 768 x 768 at 100 tokens beside one at
+// 160, 4 samples, 104 against 173.  Not rows much longer than the pair kernel's
+// own (mixed_row), which would end the launch alone, unless they are cut into
+// slices there (2048 x 2048 at 16 tokens beside 576 x 256 at 196: 16 samples 34
+// against 28, fp32 254 against 109; 4 samples, sliced, 25 against 28), and not
+// where the pair kernel's layers would lose their column slices (fp32 768 x 3072
+// at 200 tokens, 4 samples, beside 512 x 512 at 49: 252 against 153).
 constexpr int64_t kSmallLongRow = 16384, kSmallMixedBelow = 256, kSmallMixedB = 64;
+// Rows as long as this times the pair kernel's longest join its launch: bf16
+// (768 x 1000 at 1 token beside 576 x 256: 19 against 22, ratio 2.1), fp32 of T <=
+// 64 (115 against 76) and of more tokens, whose MFMAs bind (512 x 2048 at 128
+// beside 768 x 768 at 160, 16 samples: 175 against 222, ratio 1.7; 4 x 768 x 768 at
+// 100 beside 576 x 256: 104 against 130, ratio 1.8).
+double mixed_row(bk_dtype dt, int64_t T) { return dt == BK_BF16 ? 2.5 : T <= bk::kGhostSmallT ? 1.5 : 4.0; }
 void split_few_ghost(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
-    int64_t wg = 0, pair = 0;
-    for (const NormPlan& np : plans) {
+    int64_t wg = 0, pair = 0, longest = 0;
+    for (size_t l = 0; l < plans.size(); ++l) {
+        const NormPlan& np = plans[l];
         if (np.path != Path::Ghost) continue;
-        if (np.var >= 4) wg += np.nwg;
-        else if (np.var <= 1) pair += np.nwg;
-    }
-    const bool mixed = pair > 0 && wg < kSmallMixedBelow && B <= kSmallMixedB;
-    const std::vector<NormPlan> before = plans;
-    if (wg > 0 && (wg < kGhostSplitBelow || mixed))
-        for (size_t l = 0; l < plans.size(); ++l) {
-            NormPlan& np = plans[l];
-            const bk_layer& L = layers[l];
-            const int64_t es = (int64_t)elem_bytes(dt);
-            if (np.path != Path::Ghost || np.var < 4 || (!mixed && (L.d + L.p) * es < kSmallLongRow)) continue;
-            np.var = ghost_rows16(L, dt) ? 1 : 0;
-            finish_norm_plan(np, L, B);
+        if (np.var >= 4) {
+            wg += np.nwg;
+        } else if (np.var <= 1) {
+            pair += np.nwg;
+            longest = std::max(longest, layers[l].d + layers[l].p);
         }
-    split_small_ghost(plans, layers, dt, B);
-    if (!mixed)
-        for (size_t l = 0; l < plans.size(); ++l)
-            if (before[l].path == Path::Ghost && before[l].var >= 4 && plans[l].ksplit == 1) plans[l] = before[l];
+    }
+    auto moved = [&](bool mixed) {
+        std::vector<NormPlan> v = plans;
+        auto joins = [&](size_t l) {     // the launch of the pair kernel, sliced or not
+            return mixed && (double)(layers[l].d + layers[l].p) <= mixed_row(dt, layers[l].T) * (double)longest;
+        };
+        auto few = [&](size_t l) { return plans[l].path == Path::Ghost && plans[l].var >= 4; };
+        for (size_t l = 0; l < v.size(); ++l) {
+            const bk_layer& L = layers[l];
+            const bool long_row = wg < kGhostSplitBelow && (L.d + L.p) * (int64_t)elem_bytes(dt) >= kSmallLongRow;
+            if (!few(l) || !(mixed || long_row)) continue;
+            v[l].var = ghost_rows16(L, dt) ? 1 : 0;
+            finish_norm_plan(v[l], L, B);
+        }
+        split_small_ghost(v, layers, dt, B);
+        for (size_t l = 0; l < v.size(); ++l)
+            if (few(l) && !joins(l) && v[l].ksplit == 1) v[l] = plans[l];
+        return v;
+    };
+    if (wg > 0 && pair > 0 && wg < kSmallMixedBelow && B <= kSmallMixedB) {
+        std::vector<NormPlan> one = moved(true);
+        bool lost = false;
+        if (pair < kGhostSplitBelow) {
+            const std::vector<NormPlan> apart = moved(false);
+            for (size_t l = 0; l < plans.size(); ++l) lost = lost || (plans[l].path == Path::Ghost && apart[l].ksplit > 1 && one[l].ksplit == 1);
+        }
+        if (!lost) return plans.swap(one);
+    }
+    if (wg > 0 || pair > 0) plans = moved(false);
 }
 
 // fp32 instantiated norms: one workgroup per (sample, tile), a 16-row stage of

@@ -296,8 +296,26 @@ int main() {
         y.x = fake(1);
         y.g = fake(2);
         const size_t w = bk_layer_norms_workspace_size(&y, 1, dt, 200);
+        g_ghost_wgs = 0;
         if (bk_layer_norms(&y, 1, dt, 200, static_cast<float*>(fake(3)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs != 13) {
             std::fprintf(stderr, "few tokens of long rows: %ld workgroups\n", g_ghost_wgs);
+            return 1;
+        }
+    }
+    // few-token layers beside layers of the pair kernel leave it its slices
+    {
+        bk_layer L[7] = {};
+        for (int l = 0; l < 7; ++l) {
+            L[l].T = l < 3 ? 49 : 200;
+            L[l].d = l < 3 ? 512 : 768;
+            L[l].p = l < 3 ? 512 : 3072;
+            L[l].x = fake(2 * l + 1);
+            L[l].g = fake(2 * l + 2);
+        }
+        const size_t w = bk_layer_norms_workspace_size(L, 7, BK_F32, 4);
+        g_ghost_wgs = 0;
+        if (bk_layer_norms(L, 7, BK_F32, 4, static_cast<float*>(fake(40)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs < 4 * 48) {
+            std::fprintf(stderr, "pair kernel beside few tokens: %ld workgroups\n", g_ghost_wgs);
             return 1;
         }
     }
