@@ -304,17 +304,17 @@ int main() {
     }
     // few-token layers beside layers of the pair kernel leave it its slices
     {
-        bk_layer L[7] = {};
-        for (int l = 0; l < 7; ++l) {
-            L[l].T = l < 3 ? 49 : 200;
-            L[l].d = l < 3 ? 512 : 768;
-            L[l].p = l < 3 ? 512 : 3072;
+        bk_layer L[8] = {};
+        for (int l = 0; l < 8; ++l) {
+            L[l].T = l < 4 ? 49 : 200;
+            L[l].d = l < 4 ? 512 : 768;
+            L[l].p = l < 4 ? 512 : 3072;
             L[l].x = fake(2 * l + 1);
             L[l].g = fake(2 * l + 2);
         }
-        const size_t w = bk_layer_norms_workspace_size(L, 7, BK_F32, 4);
+        const size_t w = bk_layer_norms_workspace_size(L, 8, BK_F32, 4);
         g_ghost_wgs = 0;
-        if (bk_layer_norms(L, 7, BK_F32, 4, static_cast<float*>(fake(40)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs < 4 * 48) {
+        if (bk_layer_norms(L, 8, BK_F32, 4, static_cast<float*>(fake(40)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs < 4 * 48) {
             std::fprintf(stderr, "pair kernel beside few tokens: %ld workgroups\n", g_ghost_wgs);
             return 1;
         }
