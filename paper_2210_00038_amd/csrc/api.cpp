@@ -1057,13 +1057,15 @@ void plan_f32(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     for (GradEntry& e : g.e) e.gp.ksplit = s;
 }
 
-// K slices of a launch of 256 x 128 tiles with more samples than the 256 x 256
-// kernels' weight table holds (two workgroups per CU: P = 2 cus slots; 64-row
-// stages): tiles of twice the even share of stages per slot or more are cut into
+// K slices of a launch of 256 x 128 tiles, where its layers are left alone there:
+// with more samples than the 256 x 256 kernels' weight table holds, or narrow
+// layers of T < 64 whose neighbours run on those kernels' flat form.  Two
+// workgroups per CU, P = 2 cus slots, 64-row stages: tiles of twice the even share of stages per slot or more are cut into
 // slices of about that share, at least kWideMinStages.  At most P partial tiles
 // (64 MiB) in all.  4097 samples of 64 tokens, 256 -> 256: 7.3 ms on two
 // workgroups, 87 us in slices (4096 on the 256 x 256 tiles: 101); 150 tokens,
-// 264 -> 264: 19.6 ms, 302 us; one token, 768 -> 1000: 104 us, 31.
+// 264 -> 264: 19.6 ms, 302 us; one token, 768 -> 1000: 104 us, 31.  A 1000 -> 64
+// layer beside 768 -> 5000, 256 samples of 50 tokens: both 444 us, 147 in slices.
 constexpr int64_t kWideMinStages = 8;
 void plan_wide(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
     auto stages = [&](const GradEntry& e) { return cdiv(B * layers[e.l].T, bk::kWideK); };
@@ -1093,10 +1095,12 @@ std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16,
             out.back().e.push_back(GradEntry{l, grad_plan(L, v, B)});
         }
     }
+    bool flat = false;
+    for (int64_t l = 0; l < n; ++l) flat = flat || (vars[(size_t)l] == bk::GemmVariant::Grad && layers[l].T < 64);
     int64_t cus = 0;
     for (GradGroup& g : out) {
         const bool f32 = g.v == bk::GemmVariant::F32 || g.v == bk::GemmVariant::F32Any;
-        const bool wide = g.v == bk::GemmVariant::Wide && B > bk::kDMaxB;
+        const bool wide = g.v == bk::GemmVariant::Wide && (B > bk::kDMaxB || flat);
         if (g.v != bk::GemmVariant::GradDL && g.v != bk::GemmVariant::Grad && !f32 && !wide) continue;
         if (cus == 0) cus = device_cus();
         if (f32) plan_f32(g, layers, B, cus);

@@ -15,7 +15,7 @@
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
-extern long g_ghost_wgs, g_gemm_wgs, g_gemm_launches;
+extern long g_ghost_wgs, g_gemm_wgs, g_gemm_launches, g_gemm_min_wgs;
 extern bk::GemmVariant g_gemm_variant;
 extern std::map<uintptr_t, int> g_noised;
 
@@ -203,6 +203,24 @@ int main() {
                     return 1;
                 }
             }
+    // a narrow layer of few tokens beside layers on the flat 256 x 256 tiles
+    {
+        bk_layer L[2] = {};
+        for (int l = 0; l < 2; ++l) {
+            L[l].T = 50;
+            L[l].d = l ? 768 : 1000;
+            L[l].p = l ? 5000 : 64;
+            L[l].x = fake(3 * l + 1);
+            L[l].g = fake(3 * l + 2);
+            L[l].G = static_cast<float*>(fake(3 * l + 3));
+        }
+        const size_t w = bk_weighted_grads_workspace_size(L, 2, BK_BF16, 256);
+        g_gemm_min_wgs = 0;
+        if (bk_weighted_grads(L, 2, static_cast<float*>(fake(20)), BK_BF16, 256, set_ws(w), w, nullptr) != BK_OK || g_gemm_min_wgs < 64) {
+            std::fprintf(stderr, "narrow layer beside flat ones: %ld workgroups\n", g_gemm_min_wgs);
+            return 1;
+        }
+    }
     // fp32 calls of few rows: the register-transposing kernel
     {
         struct { int64_t B, T, d, p; bk::GemmVariant v; } const cs[] = {

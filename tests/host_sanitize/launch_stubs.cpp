@@ -21,6 +21,7 @@ long g_launches = 0;
 long g_ghost_wgs = 0;                 // most workgroups of a ghost-norm launch
 long g_gemm_wgs = 0;                  // ... of the last a^T g launch
 long g_gemm_launches = 0;
+long g_gemm_min_wgs = 0;              // ... of the smallest one (0: none yet)
 bk::GemmVariant g_gemm_variant = bk::GemmVariant::Scalar;   // ... of the last one
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
@@ -89,6 +90,14 @@ hipError_t launch_ghost(const GhostArgs& a, int n_wg, bool, bool, bool, hipStrea
         in_ws(a.tiles, L.tile_off, a.B * pairs * L.ksplit * kGhostSplitTile, 4, "ghost partial Grams");
         red += (int64_t)a.B * L.npairs;
     }
+    for (int k = 0; k < a.n && a.small; ++k) {
+        // whole samples to a workgroup: their rows fit its block
+        const int rows = a.small == 1 ? 32 : a.small == 2 ? 64 : a.small == 3 ? 96 : 128;
+        const int64_t last = k + 1 < a.n ? a.L[k + 1].wg_begin : n_wg;
+        need(a.L[k].T >= 1 && (int64_t)a.L[k].nsb * a.L[k].T <= rows && (a.small == 1 || a.L[k].nsb == 1) &&
+                 (last - a.L[k].wg_begin) * a.L[k].nsb >= a.B,
+             "few-token samples");
+    }
     need(a.n_red == red && (red == 0 || !a.small), "ghost slice reduction grid");
     return hipSuccess;
 }
@@ -106,6 +115,7 @@ hipError_t launch_embed_join(const GhostArgs& a, int n_wg, bool, int ct, hipStre
 hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant v, hipStream_t, int) {
     ++g_launches;
     g_gemm_wgs = n_wg;
+    g_gemm_min_wgs = g_gemm_min_wgs == 0 ? n_wg : std::min(g_gemm_min_wgs, (long)n_wg);
     ++g_gemm_launches;
     g_gemm_variant = v;
     monotone(a.L, a.n, kMaxGemm, n_wg, "gemm descriptors");
