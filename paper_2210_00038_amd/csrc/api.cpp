@@ -204,6 +204,9 @@ void set_norm_variant(NormPlan& np, const bk_layer& L, bk_dtype dt, int64_t B) {
     }
 }
 
+// Samples per workgroup of a few-token variant.
+int32_t ghost_small_samples(int64_t T, int var) { return var == 4 ? bk::ghost_small_samples(T) : 1; }
+
 // Workgroup count, and the K split of instantiated norms on the wide and
 // narrow kernels (a split layer reports one partial per slice-reduction chunk)
 // and of ghost layers whose column split (np.ksplit, split_small_ghost) is set.
@@ -219,7 +222,7 @@ void finish_norm_plan(NormPlan& np, const bk_layer& L, int64_t B) {
         if (np.ksplit > 1) np.npart = np.tiles * (np.tile_elems / bk::kSplitRedWG);
     }
     const bool small = np.path == Path::Ghost && np.var >= 4;
-    np.nwg = small ? cdiv(B, bk::ghost_small_samples(L.T)) : np.path == Path::Inst || np.ksplit > 1 ? B * np.tiles * np.ksplit : B * np.npart;
+    np.nwg = small ? cdiv(B, ghost_small_samples(L.T, np.var)) : np.path == Path::Inst || np.ksplit > 1 ? B * np.tiles * np.ksplit : B * np.npart;
     const bool affine = L.kind == BK_NORM_AFFINE || (L.kind == BK_LINEAR && (L.flags & BK_LAYER_BIAS));
     // A ghost layer on the 16-byte path with one 128-row block per sample
     // sums its bias terms while its g passes through LDS for the Gram.
@@ -248,7 +251,7 @@ hipError_t launch_ghost_var(const bk::GhostArgs& a, int n_wg, bool bf16, bool em
                                 : bk::launch_ghost(a, n_wg, bf16, embed, var == 1, s);
 }
 int32_t ghost_nsb(int64_t T, int var) {
-    if (var >= 4) return bk::ghost_small_samples(T);
+    if (var >= 4) return ghost_small_samples(T, var);
     return (int32_t)cdiv(T, var == 2 ? bk::kFullSub : var == 3 ? bk::kLongSuper : bk::kSuper);
 }
 
@@ -488,11 +491,33 @@ void few_rows_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers) {
         if (f32(np)) np.var = (int)bk::GemmVariant::Vec;      // the same tiles
 }
 
+// Layers of T <= 32 and of 32 < T <= 64 are launches of their own, and so are
+// fp32 ones of T <= 96 and above: where both together give at most kSmallJoin
+// workgroups (of one sample each), the shorter ones run as the longer (four 768 x
+// 768 at 16 tokens and four at 50: 32 samples 21.3 -> 13.8 us, 64 22.6 -> 16.7, 128,
+// apart, 27.6 against 33 in one launch of the pair kernel; fp32 at 80 and 120
+// tokens, 16 samples, 69 -> 43).
+constexpr int64_t kSmallJoin = 512;
+void join_small(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B) {
+    for (const int var : {4, 6}) {
+        int64_t n[2] = {0, 0};
+        for (const NormPlan& np : plans)
+            if (np.path == Path::Ghost && (np.var == var || np.var == var + 1)) ++n[np.var - var];
+        if (n[0] == 0 || n[1] == 0 || (n[0] + n[1]) * B > kSmallJoin) continue;
+        for (size_t l = 0; l < plans.size(); ++l)
+            if (plans[l].path == Path::Ghost && plans[l].var == var) {
+                plans[l].var = var + 1;
+                finish_norm_plan(plans[l], layers[l], B);
+            }
+    }
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     promote_inst_dl(plans, layers, B);
     demote_small_full(plans, layers, B);
     split_few_ghost(plans, layers, dt, B);
+    join_small(plans, layers, B);
     if (dt == BK_F32) {
         few_rows_f32_inst(plans, layers);
         split_long_f32_inst(plans, layers, B);

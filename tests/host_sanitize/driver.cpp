@@ -15,7 +15,7 @@
 
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
-extern long g_ghost_wgs, g_gemm_wgs, g_gemm_launches, g_gemm_min_wgs;
+extern long g_ghost_wgs, g_ghost_launches, g_gemm_wgs, g_gemm_launches, g_gemm_min_wgs;
 extern bk::GemmVariant g_gemm_variant;
 extern std::map<uintptr_t, int> g_noised;
 
@@ -334,6 +334,22 @@ int main() {
         g_ghost_wgs = 0;
         if (bk_layer_norms(L, 8, BK_F32, 4, static_cast<float*>(fake(40)), set_ws(w), w, nullptr) != BK_OK || g_ghost_wgs < 4 * 48) {
             std::fprintf(stderr, "pair kernel beside few tokens: %ld workgroups\n", g_ghost_wgs);
+            return 1;
+        }
+    }
+    // small calls: samples of few and of more tokens in one launch (fp32: two)
+    for (const bk_dtype dt : {BK_BF16, BK_F32}) {
+        bk_layer L[4] = {};
+        for (int l = 0; l < 4; ++l) {
+            L[l].T = l == 0 ? 5 : l == 1 ? 50 : l == 2 ? (dt == BK_F32 ? 80 : 20) : (dt == BK_F32 ? 120 : 33);
+            L[l].d = L[l].p = 768;
+            L[l].x = fake(2 * l + 1);
+            L[l].g = fake(2 * l + 2);
+        }
+        const size_t w = bk_layer_norms_workspace_size(L, 4, dt, 16);
+        g_ghost_launches = 0;
+        if (bk_layer_norms(L, 4, dt, 16, static_cast<float*>(fake(40)), set_ws(w), w, nullptr) != BK_OK || g_ghost_launches != (dt == BK_F32 ? 2 : 1)) {
+            std::fprintf(stderr, "few and more tokens: %ld launches\n", g_ghost_launches);
             return 1;
         }
     }

@@ -19,6 +19,7 @@
 uintptr_t g_ws_lo = 0, g_ws_hi = 0;   // [lo, hi): the caller's workspace
 long g_launches = 0;
 long g_ghost_wgs = 0;                 // most workgroups of a ghost-norm launch
+long g_ghost_launches = 0;
 long g_gemm_wgs = 0;                  // ... of the last a^T g launch
 long g_gemm_launches = 0;
 long g_gemm_min_wgs = 0;              // ... of the smallest one (0: none yet)
@@ -76,6 +77,7 @@ hipError_t launch_ghost_full(const GhostArgs& a, int n_wg, bool, hipStream_t) {
 }
 hipError_t launch_ghost(const GhostArgs& a, int n_wg, bool, bool, bool, hipStream_t) {
     ++g_launches;
+    ++g_ghost_launches;
     g_ghost_wgs = std::max(g_ghost_wgs, (long)n_wg);
     monotone(a.L, a.n, kMaxGhost, n_wg, "ghost descriptors");
     int64_t red = 0;

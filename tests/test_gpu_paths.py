@@ -153,6 +153,23 @@ def test_ghost_few_tokens(bk, B, T, d, p, off, dtype):
     assert _rel(got[1][:n], ref[:n]) <= _norm_bound(dtype)
 
 
+# Samples of few and of more tokens in one small call: the shorter ones run in
+# the launch of the longer, one sample to a workgroup, bias sums too.
+@pytest.mark.parametrize("dtype,B,Ts,d,p", [
+    (BF, 3, (1, 16, 40), 200, 136), (BF, 7, (5, 33), 130, 1000), (F32, 2, (17, 64), 68, 200), (F32, 3, (4, 50, 80, 120), 257, 260)])
+def test_ghost_few_and_more_tokens_together(bk, dtype, B, Ts, d, p):
+    gen = torch.Generator().manual_seed(B + d)
+    xs = [(_draw(B, T, d, dtype, gen), _draw(B, T, p, dtype, gen, 1e-2)) for T in Ts]
+    assert all(oracle.use_ghost(T, d, p) for T in Ts)
+    Pb, norm = torch.full((len(Ts), B, p), float("nan"), device=DEV), torch.empty(len(Ts), B, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "bias": True, "Pb": Pb[i]} for i, ((a, _), (g, _)) in enumerate(xs)])
+    bk.bk_layer_norms(arr, len(Ts), bk.BK_BF16 if dtype == BF else bk.BK_F32, B, norm)
+    for i, ((_, ah), (_, gh)) in enumerate(xs):
+        sb = oracle.bias_sums(gh)
+        assert _frob(Pb[i].cpu().numpy(), sb) <= 1e-6
+        assert _rel(norm[i].cpu().numpy(), oracle.linear_norm_sq(ah, gh) + (sb ** 2).sum(1)) <= _norm_bound(dtype)
+
+
 # Every way the few-token kernel's loop over chunks can end (a's and g's of one
 # chunk, an even and an odd number) and the whole-sample kernel's, without a
 # bias: right, and the same bits from every run.
