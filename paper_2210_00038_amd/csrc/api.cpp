@@ -880,11 +880,12 @@ bk::GemmVariant grad_variant(const bk_layer& L, bool bf16, int64_t B) {
 bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 && !keeps_grads(L); }
 
 // The variants of a call's layers.  Few 256 x 256 tiles of few rows leave CUs
-// idle and cost a launch of their own: unless the call's layers of T < 64 give
-// kFlatMinTiles of them or have kFlatMinRows rows (enough for K slices), they
-// run on the 256 x 128 tiles, two to a CU (a small ResNet at 224 x 224, 7
-// samples: 14 + 10 us in one launch and 29 in two; 36 encoder layers of 64 x 37
-// rows, 648 tiles: 265 us against 295-310).
+// idle and cost a launch of their own: unless the call's layers of T < 64 have
+// kFlatMinRows rows (enough for K slices), or kFlatManyRows and kFlatMinTiles of
+// them, they run on the 256 x 128 tiles, two to a CU (a small ResNet at 224 x
+// 224, 7 samples: 14 + 10 us in one launch and 29 in two; 3072 x 3072 of 64 rows:
+// 12.6 us against 16.8, 512 rows 25.8 against 26.4, 1024 rows 40.6 against 36.9;
+// 24 encoder layers of 64 x 37 rows, 648 tiles: 295-310 us against 265).
 // fp32 layers: the LDS-DMA kernel's ring takes three stages of 16 rows to fill,
 // the register-transposing kernel's one of 32: it is the faster one while every
 // layer of the call has at most kF32FewRows rows (one 64 x 64 layer of 64 rows:
@@ -894,7 +895,7 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // alignment: kF32FewRows, and four times the tiles, its loads being single
 // elements there (24 of 265 x 265, 64 rows: 16.5 against 17.4 us; three of 1031
 // x 4097: 43 against 41; one of 265 x 265, 96 rows: the same).
-constexpr int64_t kFlatMinTiles = 128, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
+constexpr int64_t kFlatMinTiles = 128, kFlatManyRows = 1024, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
 std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows) {
     std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
     int64_t tiles = 0, rows = 0, rows32 = 0, vec32 = 0, any32 = 0;
@@ -910,7 +911,7 @@ std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bo
         tiles += geo.tm * geo.tn;
         rows = std::max(rows, B * layers[l].T);
     }
-    if (tiles < kFlatMinTiles && (rows < kFlatMinRows || few_rows))
+    if (few_rows || rows < (tiles < kFlatMinTiles ? kFlatMinRows : kFlatManyRows))
         for (int64_t l = 0; l < n; ++l)
             if (flat(l)) v[(size_t)l] = bk::GemmVariant::Wide;
     const bool few = rows32 <= kF32FewRows, few2 = rows32 <= 2 * kF32FewRows && vec32 <= kF32FewTiles;
@@ -1105,7 +1106,7 @@ void plan_wide(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {
 }
 
 // The grouped launches of bk_weighted_grads: by kernel variant, at most
-// kMaxGemm layers each (few_rows: as with fewer than kFlatMinRows rows).
+// kMaxGemm layers each (few_rows: as with fewer than kFlatManyRows rows).
 std::vector<GradGroup> grad_groups(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows = false) {
     std::vector<GradGroup> out;
     const std::vector<bk::GemmVariant> vars = grad_variants(layers, n, bf16, B, few_rows);
