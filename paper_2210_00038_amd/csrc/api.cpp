@@ -512,9 +512,29 @@ void join_small(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B)
     }
 }
 
+// bf16 instantiated norms of a few columns by a few rows, all such layers of the
+// call (rows of fewer than 8 columns, d and p at most 64, max(d, p) T up to
+// kTinyInst): the 128 x 128 element-load kernel, four workgroups to a CU; with
+// more loads the 256 x 128 tiles' 16-byte ones win.  4096 samples: 64 -> 2 at 9 / 33 /
+// 64 tokens 42 / 47 / 63 us against 52 / 52 / 48, 16 -> 3 at 65 / 100 55 / 70 against 70.
+constexpr int64_t kTinyInst = 2200;
+void tiny_inst(std::vector<NormPlan>& plans, const bk_layer* layers, int64_t B) {
+    auto any = [](const NormPlan& np) { return np.path == Path::Inst && np.var == (int)bk::GemmVariant::WideAny; };
+    for (size_t l = 0; l < plans.size(); ++l) {
+        const int64_t hi = std::max(layers[l].d, layers[l].p), lo = std::min(layers[l].d, layers[l].p);
+        if (any(plans[l]) && (lo >= 8 || hi > 64 || hi * layers[l].T > kTinyInst)) return;
+    }
+    for (size_t l = 0; l < plans.size(); ++l)
+        if (any(plans[l])) {
+            plans[l].var = (int)bk::GemmVariant::Scalar;       // one tile as before
+            finish_norm_plan(plans[l], layers[l], B);
+        }
+}
+
 // The launch-wide choices over the norm plans of a call's layers.
 void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype dt, int64_t B) {
     promote_inst_dl(plans, layers, B);
+    if (dt == BK_BF16) tiny_inst(plans, layers, B);
     demote_small_full(plans, layers, B);
     split_few_ghost(plans, layers, dt, B);
     join_small(plans, layers, B);

@@ -231,6 +231,15 @@ int main() {
             return 1;
         }
     }
+    // instantiated norms of a few columns by a few rows
+    for (int64_t T : {33, 64}) {
+        const size_t w = bk_workspace_size(BK_OP_INST_NORM, BK_BF16, 4096, T, 64, 2);
+        if (bk_inst_norm(fake(1), fake(2), BK_BF16, 4096, T, 64, 2, static_cast<float*>(fake(3)), set_ws(w), w, nullptr) != BK_OK ||
+            g_gemm_variant != (T == 33 ? bk::GemmVariant::Scalar : bk::GemmVariant::WideAny)) {
+            std::fprintf(stderr, "64 -> 2 at %lld tokens: kernel variant %d\n", (long long)T, (int)g_gemm_variant);
+            return 1;
+        }
+    }
     // fp32 calls of few rows: the register-transposing kernel
     {
         struct { int64_t B, T, d, p; bk::GemmVariant v; } const cs[] = {
