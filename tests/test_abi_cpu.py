@@ -100,7 +100,7 @@ def test_workspace_sizes():
     # T = 1000: each sample padded to 32 stages of 32 rows, split the same way
     assert bk.bk_workspace_size(bk.BK_OP_WEIGHTED_GRAD, bk.BK_BF16, 16, 1000, 768, 768) == \
         9 * 16 * 256 * 256 * 4
-    # T = 70 (padding to 80 rows is over 1/8: the register-staged kernel, 64-row
+    # T = 70 (padding to 80 rows is over 1/8: the flat form, planned in 64-row
     # stages over all B T rows): 18 stages, slices of at least 8 stages
     assert bk.bk_workspace_size(bk.BK_OP_WEIGHTED_GRAD, bk.BK_BF16, 16, 70, 768, 768) == \
         9 * 2 * 256 * 256 * 4

@@ -1,8 +1,8 @@
 """GPU parity of the per-sample bias / normalization-affine terms and of
 gradient accumulation, through the grouped C ABI, against the oracle.
 
-Stacks mix the kernel variants that write clipped gradients (256 x 256 DMA and
-register-staged tiles, the wide kernel for T < 64, narrow tiles with and
+Stacks mix the kernel variants that write clipped gradients (256 x 256 DMA
+tiles in both forms, the wide kernel for T < 64, narrow tiles with and
 without operand swap, K-split tiles, BK-MixOpt weighted sums, the embedding
 scatter) so that every accumulate epilogue is exercised."""
 import numpy as np
@@ -127,7 +127,7 @@ def test_accumulation_over_physical_batches(bk, dtype):
     only.  Against the oracle's logical_batch (clip per physical batch)."""
     layers = [_L("linear", 48, 64, 96, bias=True),        # wide kernel (T < 64)
               _L("linear", 96, 256, 256),                 # 32 | T: DMA tiles
-              _L("linear", 100, 128, 200),                # register-staged tiles
+              _L("linear", 100, 128, 200),                # flat DMA tiles
               _L("linear", 512, 256, 256),                # one tile, K split (bf16)
               _L("linear", 512, 256, 24, bias=True),      # narrow, K split (bf16)
               _L("linear", 64, 40, 512),                  # narrow, operands swapped (bf16)

@@ -667,7 +667,7 @@ def test_inst_norm_k_split(bk, B, T, d, p):
     (8, 1000, 152, 64, []),          # the same, T not a multiple of 64
     (4, 1024, 264, 136, []),         # LDS-DMA kernel, two tiles, K slices
     (8, 1000, 264, 136, [5]),        # the same with padded samples (32 stages of 32 rows each)
-    (64, 70, 264, 136, [0]),         # register-staged kernel (T >= 64, padding over 1/8)
+    (64, 70, 264, 136, [0]),         # flat form (T >= 64, padding over 1/8)
     (6, 512, 264, 136, [0, 3]),      # zero weights at slice starts and inside
     (16, 256, 40, 24, [15]),         # tiny output, many slices
 ])
@@ -681,8 +681,8 @@ def test_weighted_grad_k_split(bk, B, T, d, p, zero):
 
 
 # A grouped launch of a 256 x 256 clipped-gradient kernel (one workgroup per
-# CU: the LDS-DMA kernel, or the register-staged one when padding T to 16-row
-# steps adds over 1/8) whose last round of tiles is under half full: those
+# CU: the weights on the accumulators, or on g's fragments when padding T to
+# 16-row steps adds over 1/8) whose last round of tiles is under half full: those
 # tiles run in K slices, dispatched after every whole tile, and are summed in
 # slice order.
 @pytest.mark.parametrize("shapes,B,T,zero", [
@@ -692,7 +692,7 @@ def test_weighted_grad_k_split(bk, B, T, d, p, zero):
     ([(768, 4096)] * 6, 4, 500, [2]),         # 32 does not divide T: samples padded to 16 stages
     ([(768, 768)], 3, 1000, []),              # the same, all split
     ([(768, 768)], 3, 197, [1]),              # 7 stages per sample, the last with one step
-    ([(768, 4096)] * 6, 16, 70, [3]),         # register-staged kernel (64-row stages)
+    ([(768, 4096)] * 6, 16, 70, [3]),         # weights on g's fragments, flat rows
     ([(768, 768)], 40, 70, []),               # the same, all split
     ([(768, 768)], 3, 200, []),               # too few stages per slice: not split
     ([(4096, 6400)], 2, 128, [1]),            # 400 tiles of 8 stages: a last round over half full, not split
@@ -1001,7 +1001,7 @@ def test_weighted_grad_beyond_2_31_bytes(bk, B, T, d, p):
 @pytest.mark.parametrize("B", [4096, 4097])
 def test_weighted_grad_largest_weight_table(bk, B):
     """B = 4096 is the largest batch whose clip weights the LDS-DMA kernel
-    keeps in LDS; one more sample takes the register-staged kernel."""
+    keeps in LDS; one more sample takes the 256 x 128 tiles, in K slices."""
     T, d, p = 64, 256, 256
     a, g = _pair(B, T, d, p, torch.bfloat16, seed=B)
     C = torch.rand(B, generator=torch.Generator().manual_seed(B)) + 0.1

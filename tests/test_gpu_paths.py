@@ -210,23 +210,31 @@ def test_weighted_sum_runs(bk, B, n, accum):
         assert torch.equal(Gb, want)
 
 
-# The 256 x 256 DMA tiles over the flat rows of the batch, weights on g's
-# fragments: several samples per 32-row stage and per 16-row step, last stages
-# of every kind, K slices of a launch without a whole round, zero weights,
-# batches past the weight table (the 256 x 128 tiles).
-@pytest.mark.parametrize("B,T,d,p", [
-    (1, 1, 256, 256),        # one row
-    (33, 1, 264, 136),       # one row past a stage
-    (3, 16, 128, 72),        # 48 rows: a last stage of one step
-    (5, 37, 512, 264),       # samples across stages, ragged tiles
-    (2, 63, 80, 520),
-    (9, 13, 300, 200),
-    (80, 20, 256, 512),      # 50 stages: K slices
-    (1100, 1, 768, 200),
-    (6, 65, 264, 264),       # T > 64, padding over 1/8
-    (4097, 1, 72, 80),       # past the weight table
+# Layers of T < 64 and others whose samples do not pad to 16-row steps.  `flat`:
+# the 256 x 256 DMA tiles over the flat rows of the batch, weights on g's
+# fragments (T > 64, or at least 4096 rows): several samples per 32-row stage and
+# per 16-row step, last stages of every kind, zero weights; their single layers
+# of few tiles run in K slices, which the workspace shows.  Else the 256 x 128
+# tiles, unsliced.
+@pytest.mark.parametrize("B,T,d,p,flat", [
+    (1, 1, 256, 256, False),       # one row
+    (33, 1, 264, 136, False),      # one row past a stage
+    (3, 16, 128, 72, False),       # 48 rows
+    (5, 37, 512, 264, False),      # samples across stages, ragged tiles
+    (2, 63, 80, 520, False),
+    (9, 13, 300, 200, False),      # odd rows
+    (80, 20, 256, 512, False),
+    (1100, 1, 768, 200, False),
+    (6, 65, 264, 264, False),      # flat, but too few stages for slices
+    (4096, 1, 768, 200, True),     # a sample per row, the fullest weight table
+    (206, 20, 256, 512, True),     # 4120 rows: samples of 20 across steps of 16
+    (316, 13, 304, 200, True),     # 4108: a last stage of one step
+    (111, 37, 512, 264, True),     # 4107 rows, ragged tiles
+    (70, 63, 264, 136, True),      # the longest T
+    (40, 70, 264, 264, True),      # T > 64, padding over 1/8
 ])
-def test_flat_weighted_grad(bk, B, T, d, p):
+def test_flat_weighted_grad(bk, B, T, d, p, flat):
+    assert (bk.bk_workspace_size(bk.BK_OP_WEIGHTED_GRAD, bk.BK_BF16, B, T, d, p) > 0) == flat
     gen = torch.Generator().manual_seed(B + T + d)
     a, ah = _draw(B, T, d, BF, gen)
     g, gh = _draw(B, T, p, BF, gen, 1e-2)
@@ -244,6 +252,25 @@ def test_flat_weighted_grad(bk, B, T, d, p):
     arr = bk.make_layers([{"x": a, "g": g, "G": Ga, "accumulate": True}, {"x": a, "g": g, "G": Gw}])
     bk.bk_weighted_grads(arr, 2, C.to(DEV), bk.BK_BF16, B)
     assert torch.equal(Ga, G0 + Gw) and _frob(Gw.cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
+
+
+# The flat form by its tiles: 16 x 9 = 144 of 256 x 256 from 1024 rows on (whole
+# tiles, no slices), one layer narrow (256 x 128 tiles in slices, beside them).
+@pytest.mark.parametrize("B,T", [(28, 37), (1024, 1), (79, 13)])
+def test_flat_weighted_grad_many_tiles(bk, B, T):
+    gen = torch.Generator().manual_seed(B)
+    a, ah = _draw(B, T, 768, BF, gen)
+    g, gh = _draw(B, T, 768, BF, gen, 1e-2)
+    n, nh = _draw(B, T, 32, BF, gen, 1e-2)
+    C = torch.rand(B, generator=gen) + 0.1
+    Gs = torch.full((16, 768, 768), float("nan"), device=DEV)
+    Gn = torch.empty(768, 32, device=DEV)
+    arr = bk.make_layers([{"x": a, "g": g, "G": Gs[i]} for i in range(16)] + [{"x": a, "g": n, "G": Gn}])
+    bk.bk_weighted_grads(arr, 17, C.to(DEV), bk.BK_BF16, B)
+    ref = oracle.weighted_grad(ah, gh, C)
+    assert _frob(Gs[0].cpu().numpy(), ref) <= GRAD_GUARD_ROUNDED
+    assert all(torch.equal(Gs[0], Gs[i]) for i in range(1, 16))
+    assert _frob(Gn.cpu().numpy(), oracle.weighted_grad(ah, nh, C)) <= GRAD_GUARD_ROUNDED
 
 
 # More samples than the 256 x 256 kernels' weight table: 256 x 128 tiles in K
