@@ -217,6 +217,7 @@ def cpu_baseline(w: wl.Workload, budget_s: float = 12.0, single_budget_s: float 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SOURCES = {"agrad_dl_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "agemm_f32_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
+                  "agemm_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "agemm_bf16_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "anarrow_kernel": "paper_2210_00038_amd/csrc/agemm.hip",
                   "ghost_norm_kernel": "paper_2210_00038_amd/csrc/ghost_norm.hip",
@@ -248,7 +249,7 @@ def norm_kernel(L, dtype: str = "bf16", time_rule: bool = False, B: int = 1) -> 
             return "ghost_norm_kernel"
         return "ghost_full_kernel" if L.T <= 256 else "ghost_long_kernel"
     if dtype != "bf16":
-        return "agemm_f32_kernel"
+        return "agemm_f32_kernel" if L.T > 32 else "agemm_kernel"
     if _narrow(L):
         return "anarrow_kernel"
     # 256 x 256 tiles on the DMA kernel when the call's layers give at least 128 of
@@ -259,14 +260,20 @@ def norm_kernel(L, dtype: str = "bf16", time_rule: bool = False, B: int = 1) -> 
     return "agemm_bf16_kernel"
 
 
-def grad_kernel(L, dtype: str = "bf16") -> str:
+def grad_kernel(L, w: wl.Workload) -> str:
     """Kernel that takes layer L's clipped gradient (same rule; a label only)."""
     if L.kind == "embed":
         return "embed_rows_kernel"
-    if dtype != "bf16":
-        return "agemm_f32_kernel"
+    gemm = [M for M in w.layers if M.kind != "embed"]
+    if w.dtype != "bf16":
+        return "agemm_f32_kernel" if max(w.B * M.T for M in gemm) > 64 else "agemm_kernel"
     if _narrow(L):
         return "agemm_bf16_kernel" if L.T < 64 else "anarrow_kernel"
+    if L.T < 64:     # the flat 256 x 256 form, where such layers give it enough rows and tiles
+        few = [M for M in gemm if M.T < 64 and not _narrow(M)]
+        tiles = sum(-(-M.d // 256) * -(-M.p // 256) for M in few)
+        if w.B > 4096 or w.B * max(M.T for M in few) < (1024 if tiles >= 128 else 4096):
+            return "agemm_bf16_kernel"
     return "agrad_dl_kernel"
 
 
@@ -278,7 +285,7 @@ def dominant_kernel(w: wl.Workload, phase: str, time_rule: bool = False) -> str:
             k = norm_kernel(L, w.dtype, time_rule, w.B)
             f = 2.0 * L.T * L.T * (L.p + L.d) if k.startswith("ghost_") else 2.0 * L.T * L.p * L.d
         else:
-            k, f = grad_kernel(L, w.dtype), 2.0 * L.T * L.p * L.d
+            k, f = grad_kernel(L, w), 2.0 * L.T * L.p * L.d
         share[k] = share.get(k, 0.0) + f
     return max(share, key=share.get)
 
@@ -522,7 +529,7 @@ def main():
         gk, what = "conv_prep_kernel", "unfold + token-major transpose of every conv layer, one launch"
     else:
         gk = dominant_kernel(w, dom, args.time_rule)
-        kinds = {grad_kernel(L, w.dtype) if dom == "weighted_grads" else norm_kernel(L, w.dtype, args.time_rule, w.B)
+        kinds = {grad_kernel(L, w) if dom == "weighted_grads" else norm_kernel(L, w.dtype, args.time_rule, w.B)
                  for L in w.layers}
         what = ("clipped gradients" if dom == "weighted_grads" else "per-sample norms") + \
                (", all layers in one launch" if len(kinds) == 1 else ", one launch per kernel variant")
