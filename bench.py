@@ -272,7 +272,7 @@ def grad_kernel(L, w: wl.Workload) -> str:
     if L.T < 64:     # the flat 256 x 256 form, where such layers give it enough rows and tiles
         few = [M for M in gemm if M.T < 64 and not _narrow(M)]
         tiles = sum(-(-M.d // 256) * -(-M.p // 256) for M in few)
-        if w.B > 4096 or w.B * max(M.T for M in few) < (1024 if tiles >= 128 else 4096):
+        if w.B > 4096 or w.B * max(M.T for M in few) < (512 if tiles >= 128 else 4096):
             return "agemm_bf16_kernel"
     return "agrad_dl_kernel"
 

@@ -909,7 +909,7 @@ struct StagePos {
 // stages ahead by one wave.  Bound by the memory phase, which the 80 scaling
 // instructions per stage make longer than the MFMA phase (1.2 us a stage
 // against 0.9 with rare rescales).  Against the register-staged kernels it
-// replaced: 36 encoder layers at T = 37, 64 samples (201 GFLOP) 295-310 us (256
+// replaced: 24 encoder layers at T = 37, 64 samples (201 GFLOP) 295-310 us (256
 // x 128 tiles, two workgroups per CU) -> 265 us; at T = 70, 32 samples about
 // 3% faster (256 x 256 tiles).
 //
@@ -1251,9 +1251,9 @@ __global__ __launch_bounds__(512, 1) void agrad_dl_kernel(const GemmArgs args, i
 // them).  The 12 layers of three GPT-2-small blocks on 16 x 128 tokens (87
 // GFLOP): 1171 us (74 TFLOP/s) on the register-transposing 128 x 128 kernel, 776
 // with this staging, 762 (114 TFLOP/s) with the reads a group ahead and the DMA
-// spread over the MFMAs.  One workgroup of eight waves per CU (32-row stages)
-// took 794: the MFMAs were busy 75% of the time, the barriers of one workgroup
-// uncovered by another.
+// spread over the MFMAs, busy 82% of the time at 2.13 GHz.  One workgroup of eight
+// waves per CU (32-row stages) took 794: the barriers of one workgroup uncovered
+// by another.
 // ---------------------------------------------------------------------------
 constexpr int kFK = 16;                          // k rows per stage
 constexpr int kFRing = 4;                        // stages in the ring

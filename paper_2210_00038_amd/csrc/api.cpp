@@ -299,8 +299,9 @@ void demote_small_full(std::vector<NormPlan>& plans, const bk_layer* layers, int
 // 50257 columns and 8 samples ran on 8 of 256 CUs).  When all such layers of a
 // call give fewer than kGhostSplitBelow workgroups, their rows are cut into
 // column slices towards kGhostSplitTo workgroups, each slice at least
-// kGhostSplitChunks 128-byte chunks wide (its partial Gram, at most 64 KB
-// written and read back through the caches, against 256 KB of rows streamed), if
+// kGhostSplitChunks 128-byte chunks wide (its partial Gram, 40 KB on the
+// diagonal and 64 off it, written and read back through the caches, against 256
+// KB of rows streamed), if
 // that gives at least kGhostSplitMin of them: the second kernel takes 15 us or
 // more, so that two slices for each of 96 workgroups lost (27 us against 21 + 18).
 // Norms of a head 768 -> 50257 at T = 128, 8 / 16 / 32 / 63 samples: bf16 43 / 59
@@ -904,7 +905,8 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // kFlatMinRows rows (enough for K slices), or kFlatManyRows and kFlatMinTiles of
 // them, they run on the 256 x 128 tiles, two to a CU (a small ResNet at 224 x
 // 224, 7 samples: 14 + 10 us in one launch and 29 in two; 3072 x 3072 of 64 rows:
-// 12.6 us against 16.8, 512 rows 25.8 against 26.4, 1024 rows 40.6 against 36.9;
+// 12.6 us against 16.8, 256 rows 17.8 against 21.1, 512 rows 25.8 against 26.4,
+// 1024 rows 40.6 against 36.9; 28 encoder layers of 57 x 16 rows, 714 tiles: flat;
 // 24 encoder layers of 64 x 37 rows, 648 tiles: 295-310 us against 265).
 // fp32 layers: the LDS-DMA kernel's ring takes three stages of 16 rows to fill,
 // the register-transposing kernel's one of 32: it is the faster one while every
@@ -915,7 +917,7 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // alignment: kF32FewRows, and four times the tiles, its loads being single
 // elements there (24 of 265 x 265, 64 rows: 16.5 against 17.4 us; three of 1031
 // x 4097: 43 against 41; one of 265 x 265, 96 rows: the same).
-constexpr int64_t kFlatMinTiles = 128, kFlatManyRows = 1024, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
+constexpr int64_t kFlatMinTiles = 128, kFlatManyRows = 512, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
 std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows) {
     std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
     int64_t tiles = 0, rows = 0, rows32 = 0, vec32 = 0, any32 = 0;
@@ -1004,7 +1006,9 @@ constexpr int64_t kTailMaxSplit = 16;    // K slices per tail tile, at most
 // most tiles, which goes last.  A launch of no whole round (N tiles, at most
 // half the CUs) splits the tiles of all its layers the same way where that is
 // shorter (a classifier stack of 36 tiles with 4096 samples of one token: seven
-// slices each; 128 tiles of 528 rows in two slices had cost 78 -> 98 us).
+// slices each; 128 tiles of 528 rows in two slices had cost 78 -> 98 us).  On 156
+// stacks of 2 to 20 layers, 2 to 112 tiles of 512 to 8192 rows, measured
+// both ways, the choice was within 12% of the better one.
 constexpr int64_t kDLTimeRows = 32;
 constexpr double kSliceLaunch = 6.0, kSlicePartial = 0.12, kSliceGain = 0.85;
 void plan_tail(GradGroup& g, const bk_layer* layers, int64_t B, int64_t cus) {

@@ -984,11 +984,13 @@ __global__ __launch_bounds__(256, 2) void ghost_norm_kernel(const GhostArgs args
 // of each chunk's MFMA k steps: a wave holds both whole Grams (upper triangle
 // of 32 x 32 sub-tiles) of its share of the columns, and the four shares are
 // added through LDS at the end.  Off the S diagonal T x T blocks the products
-// of the packed Gram belong to no sample and are left out.  HBM-bound; several
-// workgroups fit a CU, so the barriers of one are covered by the others.
+// of the packed Gram belong to no sample and are left out.  Several workgroups
+// fit a CU, so the barriers of one are covered by the others.  Bound by loads in
+// flight: at T = 37 only 37 of 64 rows of a chunk load anything (MFMAs busy 11%,
+// waves waiting 54% of their time, 3.7 TB/s in all against 4.8 of a copy).
 // Measured against the pair kernel: classifier stack of three layers at T = 1,
-// 1024 samples 158 -> 18 us; 36 encoder layers at T = 37, 64 samples (600 MB)
-// 172 -> 106 us (5.7 TB/s); one 64 x 64 float32 layer at T = 16 12 -> 7 us.
+// 1024 samples 158 -> 18 us; 24 encoder layers at T = 37, 64 samples (350 MB) 172
+// -> 98-106 us; one 64 x 64 float32 layer at T = 16 12 -> 7 us.
 //
 // Bias sums (Pb): one sample per workgroup: a wave adds all rows of eight
 // 16-byte columns of the chunk; several samples: each thread adds the T rows of
