@@ -249,7 +249,7 @@ def norm_kernel(L, dtype: str = "bf16", time_rule: bool = False, B: int = 1) -> 
             return "ghost_norm_kernel"
         return "ghost_full_kernel" if L.T <= 256 else "ghost_long_kernel"
     if dtype != "bf16":
-        return "agemm_f32_kernel" if L.T > 32 else "agemm_kernel"
+        return "agemm_f32_kernel"
     if _narrow(L):
         return "anarrow_kernel"
     # 256 x 256 tiles on the DMA kernel when the call's layers give at least 128 of

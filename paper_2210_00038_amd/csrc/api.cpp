@@ -478,20 +478,6 @@ void promote_inst_dl(std::vector<NormPlan>& plans, const bk_layer* layers, int64
         }
 }
 
-// fp32 instantiated norms of 16-byte rows, T <= kF32FewInst in all such layers:
-// the register-transposing kernel, as for the gradients (grad_variants): 10.2 us
-// against 11.1 at T = 16 and 32, 16 or 256 samples; T = 49 11.5 against 11.1.
-constexpr int64_t kF32FewInst = 32;
-void few_rows_f32_inst(std::vector<NormPlan>& plans, const bk_layer* layers) {
-    auto f32 = [](const NormPlan& np) { return np.path == Path::Inst && np.var == (int)bk::GemmVariant::F32; };
-    int64_t T = 0;
-    for (size_t l = 0; l < plans.size(); ++l)
-        if (f32(plans[l])) T = std::max(T, layers[l].T);
-    if (T > kF32FewInst) return;
-    for (NormPlan& np : plans)
-        if (f32(np)) np.var = (int)bk::GemmVariant::Vec;      // the same tiles
-}
-
 // Layers of T <= 32 and of 32 < T <= 64 are launches of their own, and so are
 // fp32 ones of T <= 96 and above: where both together give at most kSmallJoin
 // workgroups (of one sample each), the shorter ones run as the longer (four 768 x
@@ -539,10 +525,7 @@ void launch_wide(std::vector<NormPlan>& plans, const bk_layer* layers, bk_dtype 
     demote_small_full(plans, layers, B);
     split_few_ghost(plans, layers, dt, B);
     join_small(plans, layers, B);
-    if (dt == BK_F32) {
-        few_rows_f32_inst(plans, layers);
-        split_long_f32_inst(plans, layers, B);
-    }
+    if (dt == BK_F32) split_long_f32_inst(plans, layers, B);
 }
 
 // The norm plans of a call's layers (norm_plan each, then launch_wide).
@@ -911,9 +894,10 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // fp32 layers: the LDS-DMA kernel's ring takes three stages of 16 rows to fill,
 // the register-transposing kernel's one of 32: it is the faster one while every
 // layer of the call has at most kF32FewRows rows (one 64 x 64 layer of 64 rows:
-// 10.0 us against 13.6; 12 of 768 wide, 16 rows: 33 against 38), or twice that
-// with at most kF32FewTiles tiles (1024 x 1024, 96 rows: 14.6 against 17.3, 128
-// rows: 17.9 against 19.4; 1296 tiles, 96 rows: 69 against 65).  Rows of any
+// 10.0 us against 13.6; 12 of 768 wide, 16 rows: 33 against 38), or half as many
+// again with at most kF32FewTiles tiles (1024 x 1024, 96 rows: 14.6 against 17.3;
+// 1296 tiles, 96 rows: 69 against 65; two of 904 x 904 and one of 904 x 306, 105
+// rows: a step of 75 us against 72).  Rows of any
 // alignment: kF32FewRows, and four times the tiles, its loads being single
 // elements there (24 of 265 x 265, 64 rows: 16.5 against 17.4 us; three of 1031
 // x 4097: 43 against 41; one of 265 x 265, 96 rows: the same).
@@ -936,7 +920,7 @@ std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bo
     if (few_rows || rows < (tiles < kFlatMinTiles ? kFlatMinRows : kFlatManyRows))
         for (int64_t l = 0; l < n; ++l)
             if (flat(l)) v[(size_t)l] = bk::GemmVariant::Wide;
-    const bool few = rows32 <= kF32FewRows, few2 = rows32 <= 2 * kF32FewRows && vec32 <= kF32FewTiles;
+    const bool few = rows32 <= kF32FewRows, few2 = 2 * rows32 <= 3 * kF32FewRows && vec32 <= kF32FewTiles;
     for (bk::GemmVariant& x : v) {
         if (x == bk::GemmVariant::F32 && (few || few2)) x = bk::GemmVariant::Vec;
         if (x == bk::GemmVariant::F32Any && few && any32 <= 4 * kF32FewTiles) x = bk::GemmVariant::Scalar;
@@ -1168,15 +1152,23 @@ size_t weighted_grads_ws(const bk_layer* layers, int64_t n, bk_dtype dt, int64_t
     for (int64_t l = 0; l < n; ++l)
         if (layers[l].kind == BK_EMBEDDING) tot = std::max(tot, embed_grad_ws_bytes(B, layers[l].T, layers[l].p));
     // Grouped launches follow each other on the stream: each one's partial
-    // tiles start at the workspace's beginning.  With a smaller batch the layers
-    // of T < 64 may leave the launches of the 256 x 256 tiles (grad_variants).
-    for (const bool few_rows : {false, true})
-        for (const GradGroup& g : grad_groups(layers, n, dt == BK_BF16, B, few_rows)) {
+    // tiles start at the workspace's beginning.
+    bool flat = false;
+    auto largest = [&](const std::vector<GradGroup>& groups) {
+        for (const GradGroup& g : groups) {
             int64_t tiles = 0;
-            for (const GradEntry& e : g.e) tiles += e.gp.split_tiles() * e.gp.ksplit * e.gp.tile_elems;
+            for (const GradEntry& e : g.e) {
+                tiles += e.gp.split_tiles() * e.gp.ksplit * e.gp.tile_elems;
+                flat = flat || (g.v == bk::GemmVariant::Grad && layers[e.l].T < 64);
+            }
             tiles = std::max(tiles, g.reserve * g.e[0].gp.tile_elems);
             tot = std::max(tot, (size_t)tiles * sizeof(float));
         }
+    };
+    largest(grad_groups(layers, n, dt == BK_BF16, B));
+    // With a smaller batch the layers of T < 64 leave the launches of the 256 x
+    // 256 tiles (grad_variants).
+    if (flat) largest(grad_groups(layers, n, dt == BK_BF16, B, true));
     return tot;
 }
 

@@ -244,8 +244,8 @@ int main() {
     {
         struct { int64_t B, T, d, p; bk::GemmVariant v; } const cs[] = {
             {4, 16, 64, 64, bk::GemmVariant::Vec},        {64, 1, 4096, 4096, bk::GemmVariant::Vec},
-            {1, 128, 1024, 1024, bk::GemmVariant::Vec},   {1, 65, 4096, 4096, bk::GemmVariant::F32},
-            {1, 129, 64, 64, bk::GemmVariant::F32},       {64, 1, 65, 63, bk::GemmVariant::Scalar},
+            {1, 96, 1024, 1024, bk::GemmVariant::Vec},    {1, 65, 4096, 4096, bk::GemmVariant::F32},
+            {1, 97, 64, 64, bk::GemmVariant::F32},        {64, 1, 65, 63, bk::GemmVariant::Scalar},
             {65, 1, 65, 63, bk::GemmVariant::F32Any},     {4, 16, 4097, 4095, bk::GemmVariant::F32Any}};
         for (const auto& c : cs) {
             const size_t w = bk_workspace_size(BK_OP_WEIGHTED_GRAD, BK_F32, c.B, c.T, c.d, c.p);

@@ -314,8 +314,8 @@ def test_weighted_grad_past_the_weight_table(bk, B, T, d, p):
     (6, 50, 64, 200, 1),       # misaligned base
     (5, 100, 1, 77, 0),        # one column
     (2, 1030, 136, 24, 0),     # long samples: per-sample gradients in K slices too
-    (2, 64, 264, 200, 0),      # the most rows of few tiles on the register-transposing kernel,
-    (3, 43, 264, 200, 0),      # and one more
+    (3, 32, 264, 200, 0),      # the most rows of few tiles on the register-transposing kernel,
+    (97, 1, 264, 200, 0),      # and one more
     (1, 65, 131, 71, 0),       # the same of odd rows
 ])
 def test_f32_gemm(bk, B, T, d, p, off):
