@@ -901,15 +901,24 @@ bool gemm_grad(const bk_layer& L) { return L.kind == BK_LINEAR && L.d * L.p > 0 
 // alignment: kF32FewRows, and four times the tiles, its loads being single
 // elements there (24 of 265 x 265, 64 rows: 16.5 against 17.4 us; three of 1031
 // x 4097: 43 against 41; one of 265 x 265, 96 rows: the same).
+// bf16 rows of any alignment, one or two of them in all: the 128 x 128
+// element-load kernel, half the output per workgroup to store, while its tiles
+// run at once (1031 x 128: 7.6 us against 9.9 at one row, 8.2 against 10.3 at two,
+// level at three; 768 x 50257 43 against 38).
 constexpr int64_t kFlatMinTiles = 128, kFlatManyRows = 512, kFlatMinRows = 4096, kF32FewRows = 64, kF32FewTiles = 128;
+constexpr int64_t kAnyFewRows = 2, kAnyFewTiles = 512;
 std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bool bf16, int64_t B, bool few_rows) {
     std::vector<bk::GemmVariant> v((size_t)n, bk::GemmVariant::Scalar);
-    int64_t tiles = 0, rows = 0, rows32 = 0, vec32 = 0, any32 = 0;
+    int64_t tiles = 0, rows = 0, rows32 = 0, vec32 = 0, any32 = 0, rows_any = 0, tiles_any = 0;
     auto flat = [&](int64_t l) { return v[(size_t)l] == bk::GemmVariant::Grad && layers[l].T < 64; };
     for (int64_t l = 0; l < n; ++l) {
         if (!gemm_grad(layers[l])) continue;
         v[(size_t)l] = grad_variant(layers[l], bf16, B);
         if (!bf16) rows32 = std::max(rows32, B * layers[l].T);
+        if (v[(size_t)l] == bk::GemmVariant::WideAny) {
+            rows_any = std::max(rows_any, B * layers[l].T);
+            tiles_any += cdiv(layers[l].d, bk::kTile) * cdiv(layers[l].p, bk::kTile);
+        }
         if (!bf16)
             (v[(size_t)l] == bk::GemmVariant::F32Any ? any32 : vec32) += cdiv(layers[l].d, bk::kTile) * cdiv(layers[l].p, bk::kTile);
         if (!flat(l)) continue;
@@ -923,6 +932,7 @@ std::vector<bk::GemmVariant> grad_variants(const bk_layer* layers, int64_t n, bo
     const bool few = rows32 <= kF32FewRows, few2 = 2 * rows32 <= 3 * kF32FewRows && vec32 <= kF32FewTiles;
     for (bk::GemmVariant& x : v) {
         if (x == bk::GemmVariant::F32 && (few || few2)) x = bk::GemmVariant::Vec;
+        if (x == bk::GemmVariant::WideAny && rows_any <= kAnyFewRows && tiles_any <= kAnyFewTiles) x = bk::GemmVariant::Scalar;
         if (x == bk::GemmVariant::F32Any && few && any32 <= 4 * kF32FewTiles) x = bk::GemmVariant::Scalar;
     }
     return v;

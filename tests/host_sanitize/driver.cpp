@@ -231,6 +231,15 @@ int main() {
             return 1;
         }
     }
+    // one or two odd rows in all
+    for (int64_t B : {1, 2, 3}) {
+        float* out = static_cast<float*>(fake(3));
+        if (bk_weighted_grad(fake(1), fake(2), out, BK_BF16, B, 1, 1031, 128, out, nullptr, 0, nullptr) != BK_OK ||
+            g_gemm_variant != (B < 3 ? bk::GemmVariant::Scalar : bk::GemmVariant::WideAny)) {
+            std::fprintf(stderr, "%lld odd rows: kernel variant %d\n", (long long)B, (int)g_gemm_variant);
+            return 1;
+        }
+    }
     // instantiated norms of a few columns by a few rows
     for (int64_t T : {33, 64}) {
         const size_t w = bk_workspace_size(BK_OP_INST_NORM, BK_BF16, 4096, T, 64, 2);

@@ -88,6 +88,8 @@ def test_ghost_rows_and_column_slices(bk, B, T, d, p, dtype, off):
     (5, 13, 1000, 15, 0),      # several samples per stage
     (2, 130, 264, 136, 1),     # 16-byte row lengths, misaligned base
     (130, 1, 300, 10, 0),      # one token a sample
+    (2, 1, 300, 131, 0),       # two rows in all (the element-load kernel), and three
+    (3, 1, 300, 131, 0),
     (3, 65, 300, 2, 0),        # rows of fewer than 8 elements: two, one
     (4, 70, 1, 131, 0),
     (3, 100, 7, 3, 1),         # both sides, the batch ends inside a piece
