@@ -1593,7 +1593,7 @@ hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm
         return hipGetLastError();
     }
     if (v == GemmVariant::F32 || v == GemmVariant::F32Any) {
-        const int nr = n_remap > 0 && n_remap < n_wg ? n_remap : n_wg;
+        const int nr = n_remap < 0 ? 0 : n_remap > 0 && n_remap < n_wg ? n_remap : n_wg;
 #define BK_F32_GEMM(I, V) hipLaunchKernelGGL((agemm_f32_kernel<I, V>), grid, block, 0, s, args, nr)
         if (v == GemmVariant::F32) { if (inst_norm) BK_F32_GEMM(true, true); else BK_F32_GEMM(false, true); }
         else                       { if (inst_norm) BK_F32_GEMM(true, false); else BK_F32_GEMM(false, false); }

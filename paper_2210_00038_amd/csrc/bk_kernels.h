@@ -258,8 +258,9 @@ constexpr int kLongSuper = 256;
 hipError_t launch_ghost_full(const GhostArgs& args, int n_wg, bool long_t, hipStream_t s);
 hipError_t launch_ghost(const GhostArgs& args, int n_wg, bool bf16, bool embed, bool vec,
                         hipStream_t s);
-// n_remap (Grad, GradDL): the first n_remap workgroups are dealt to the XCDs in
-// contiguous runs; the rest (a launch's tail) run in launch order.  0: all.
+// n_remap (Grad, GradDL, F32): the first n_remap workgroups are dealt to the
+// XCDs in contiguous runs; the rest (a launch's tail) run in launch order.  0:
+// all; -1 (F32): none.
 hipError_t launch_gemm(const GemmArgs& args, int n_wg, bool bf16, bool inst_norm, GemmVariant v,
                        hipStream_t s, int n_remap = 0);
 // Adds the K slices of every split layer of `args` (launched with

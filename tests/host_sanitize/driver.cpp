@@ -16,6 +16,7 @@
 extern uintptr_t g_ws_lo, g_ws_hi;
 extern long g_launches;
 extern long g_ghost_wgs, g_ghost_launches, g_gemm_wgs, g_gemm_launches, g_gemm_min_wgs;
+extern int g_gemm_remap, g_gemm_first_T;
 extern bk::GemmVariant g_gemm_variant;
 extern std::map<uintptr_t, int> g_noised;
 
@@ -229,6 +230,25 @@ int main() {
             g_gemm_variant != (B < 512 ? bk::GemmVariant::Wide : bk::GemmVariant::Grad)) {
             std::fprintf(stderr, "3072 x 3072 of %lld rows: kernel variant %d\n", (long long)B, (int)g_gemm_variant);
             return 1;
+        }
+    }
+    // fp32 layers of different T: the largest tiles first, over all XCDs
+    {
+        bk_layer L[3] = {};
+        for (int l = 0; l < 3; ++l) {
+            L[l].T = l == 2 ? 300 : 40;
+            L[l].d = L[l].p = 768;
+            L[l].x = fake(3 * l + 1);
+            L[l].g = fake(3 * l + 2);
+            L[l].G = static_cast<float*>(fake(3 * l + 3));
+        }
+        for (int n : {2, 3}) {
+            const size_t w = bk_weighted_grads_workspace_size(L, n, BK_F32, 16);
+            if (bk_weighted_grads(L, n, static_cast<float*>(fake(20)), BK_F32, 16, set_ws(w), w, nullptr) != BK_OK ||
+                (g_gemm_remap == -1) != (n == 3) || g_gemm_first_T != (n == 3 ? 300 : 40)) {
+                std::fprintf(stderr, "fp32 layers of different T: deal %d, first T %d\n", g_gemm_remap, g_gemm_first_T);
+                return 1;
+            }
         }
     }
     // one or two odd rows in all

@@ -23,6 +23,7 @@ long g_ghost_launches = 0;
 long g_gemm_wgs = 0;                  // ... of the last a^T g launch
 long g_gemm_launches = 0;
 long g_gemm_min_wgs = 0;              // ... of the smallest one (0: none yet)
+int g_gemm_remap = 0, g_gemm_first_T = 0;   // its XCD deal, the T of its first layer
 bk::GemmVariant g_gemm_variant = bk::GemmVariant::Scalar;   // ... of the last one
 std::map<uintptr_t, int> g_noised;    // tensor -> launches that add noise to it
 
@@ -114,12 +115,15 @@ hipError_t launch_embed_join(const GhostArgs& a, int n_wg, bool, int ct, hipStre
     }
     return hipSuccess;
 }
-hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant v, hipStream_t, int) {
+hipError_t launch_gemm(const GemmArgs& a, int n_wg, bool, bool inst, GemmVariant v, hipStream_t, int n_remap) {
     ++g_launches;
     g_gemm_wgs = n_wg;
     g_gemm_min_wgs = g_gemm_min_wgs == 0 ? n_wg : std::min(g_gemm_min_wgs, (long)n_wg);
     ++g_gemm_launches;
     g_gemm_variant = v;
+    g_gemm_remap = n_remap;
+    g_gemm_first_T = a.n > 0 ? a.L[0].T : 0;
+    need(n_remap >= 0 || v == GemmVariant::F32 || v == GemmVariant::F32Any, "order of workgroups");
     monotone(a.L, a.n, kMaxGemm, n_wg, "gemm descriptors");
     for (int k = 0; k < a.n; ++k) {
         const GemmLayer& L = a.L[k];
